@@ -15,7 +15,7 @@
 //   3. orders the bin by (r, p), dummies last (a uniformly random order of
 //      the reals: random labels followed by a sort, the construction of
 //      Section 4.1).  The network sorts one 64-bit word per slot, the top
-//      64 - log2 Z bits of r with p below them, which is the (r, p) order
+//      62 - log2 Z bits of r with p below them, which is the (r, p) order
 //      while no two reals share their top key bits; the keys depend on
 //      (seed, attempt, bin, p) only, and when two of a bin's reals (or its
 //      last real and first dummy) do share them, a flag that depends on no
@@ -69,48 +69,38 @@ __device__ __forceinline__ ElemRK<T> e_xor(const ElemRK<T>& a) {
   return ElemRK<T>{lane_xor<X>(a.r), lane_xor<X>(a.klo), lane_xor<X>(a.khi), lane_xor<X>(a.aux)};
 }
 
-// Comparators of the networks below: CMP 0 = e_less of the element type
-// (record order, or the packed key words of the fast launch), 2 = (random
-// key, record).
-template <int CMP, typename E>
-__device__ __forceinline__ bool lt(const E& a, const E& b) {
-  if constexpr (CMP == 0) return e_less(a, b);
-  else return (a.key < b.key) | ((a.key == b.key) & f_less(a.r, b.r));
+template <uint32_t X>
+__device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {
+  return uint64_t(lane_xor<X>(uint32_t(v))) | (uint64_t(lane_xor<X>(uint32_t(v >> 32))) << 32);
 }
+template <uint32_t X>
+__device__ __forceinline__ FRec<8> f_xor(const FRec<8>& a) { return {lane_xor64<X>(a.k)}; }
+template <uint32_t X>
+__device__ __forceinline__ FRec<16> f_xor(const FRec<16>& a) { return {lane_xor64<X>(a.k), lane_xor64<X>(a.p)}; }
+template <uint32_t X, int R>
+__device__ __forceinline__ FE1<R> e_xor(const FE1<R>& a) { return {f_xor<X>(a.r)}; }
 
-// Compare-exchange of two registers (x gets the smaller when ascending) and
-// with the element of lane lq ^ X (the lower lane keeps the smaller when
-// ascending).  Elements equal under the comparator are byte-identical.
-template <int CMP, typename E>
-__device__ __forceinline__ void cx_r(E& x, E& y, bool asc) {
-  const bool sw = lt<CMP>(y, x) == asc;
-  const E nx = e_sel(sw, y, x), ny = e_sel(sw, x, y);
-  x = nx;
-  y = ny;
-}
-template <int CMP, uint32_t X, typename E>
+// Compare-exchange with the element of lane lq ^ X (the lower lane keeps the
+// smaller when ascending).  Elements equal under the comparator are
+// byte-identical.
+template <uint32_t X, typename E>
 __device__ __forceinline__ void cx_xor(E& x, bool is_lo, bool asc) {
   const E p = e_xor<X>(x);
-  const bool take = lt<CMP>(p, x) == (is_lo == asc);
-  x = e_sel(take, p, x);
+  const bool take = e_less(p, x) == (is_lo == asc);
+  x = e_pick(take, p, x);
 }
 
 // Phase KK (merges of 2^KK slots), stages JJ = KK-1 .. 0, on layout P held
 // entirely in registers and lane exchanges (LZ <= 10).
-template <int LZ, int KK, int JJ, int CMP, typename E>
+template <int LZ, int KK, int JJ, typename E>
 __device__ __forceinline__ void reg_stages(E (&v)[16], uint32_t lq) {
   if constexpr (JJ >= 0) {
     if constexpr (JJ < 4) {
-      constexpr uint32_t hb = 1u << JJ;
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        if (e & hb) continue;
-        bool asc;
-        if constexpr (KK == LZ) asc = true;
-        else if constexpr (KK < 4) asc = ((e >> KK) & 1u) == 0u;
-        else asc = ((lq >> (KK - 4)) & 1u) == 0u;
-        cx_r<CMP>(v[e], v[e | hb], asc);
-      }
+      cx_stage<(1u << JJ)>(v, [&](uint32_t e) {
+        if constexpr (KK == LZ) return true;
+        else if constexpr (KK < 4) return ((e >> KK) & 1u) == 0u;
+        else return ((lq >> (KK - 4)) & 1u) == 0u;
+      });
     } else {
       constexpr uint32_t X = 1u << (JJ - 4);
       const bool is_lo = (lq & X) == 0u;
@@ -118,16 +108,16 @@ __device__ __forceinline__ void reg_stages(E (&v)[16], uint32_t lq) {
       if constexpr (KK == LZ) asc = true;
       else asc = ((lq >> (KK - 4)) & 1u) == 0u;
 #pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) cx_xor<CMP, X>(v[e], is_lo, asc);
+      for (uint32_t e = 0; e < 16; ++e) cx_xor<X>(v[e], is_lo, asc);
     }
-    reg_stages<LZ, KK, JJ - 1, CMP>(v, lq);
+    reg_stages<LZ, KK, JJ - 1>(v, lq);
   }
 }
-template <int LZ, int KK, int CMP, typename E>
+template <int LZ, int KK, typename E>
 __device__ __forceinline__ void reg_phases(E (&v)[16], uint32_t lq) {
   if constexpr (KK <= LZ) {
-    reg_stages<LZ, KK, KK - 1, CMP>(v, lq);
-    reg_phases<LZ, KK + 1, CMP>(v, lq);
+    reg_stages<LZ, KK, KK - 1>(v, lq);
+    reg_phases<LZ, KK + 1>(v, lq);
   }
 }
 
@@ -144,89 +134,61 @@ __host__ __device__ inline uint32_t finish_lds_bytes(int rec, uint32_t lz, bool 
 
 namespace finish_detail {
 
-// A record as the words that order it: one 64-bit word (key << 32 | payload)
-// for 8-byte records, (key, payload) for 16-byte ones.
-template <int R> struct FRec;
-template <> struct FRec<8> {
-  uint64_t k;
-};
-template <> struct FRec<16> {
-  uint64_t k, p;
-};
-__device__ __forceinline__ bool f_less(const FRec<8>& a, const FRec<8>& b) { return a.k < b.k; }
-__device__ __forceinline__ bool f_less(const FRec<16>& a, const FRec<16>& b) {
-  return (a.k < b.k) | ((a.k == b.k) & (a.p < b.p));
-}
-__device__ __forceinline__ bool f_eq(const FRec<8>& a, const FRec<8>& b) { return a.k == b.k; }
-__device__ __forceinline__ bool f_eq(const FRec<16>& a, const FRec<16>& b) { return (a.k == b.k) & (a.p == b.p); }
-__device__ __forceinline__ FRec<8> f_sel(bool c, const FRec<8>& a, const FRec<8>& b) { return {c ? a.k : b.k}; }
-__device__ __forceinline__ FRec<16> f_sel(bool c, const FRec<16>& a, const FRec<16>& b) {
-  return {c ? a.k : b.k, c ? a.p : b.p};
-}
-template <uint32_t X>
-__device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {
-  return uint64_t(lane_xor<X>(uint32_t(v))) | (uint64_t(lane_xor<X>(uint32_t(v >> 32))) << 32);
-}
-template <uint32_t X>
-__device__ __forceinline__ FRec<8> f_xor(const FRec<8>& a) { return {lane_xor64<X>(a.k)}; }
-template <uint32_t X>
-__device__ __forceinline__ FRec<16> f_xor(const FRec<16>& a) { return {lane_xor64<X>(a.k), lane_xor64<X>(a.p)}; }
-__device__ __forceinline__ FRec<8> f_load(const uint2& r) { return {(uint64_t(r.x) << 32) | r.y}; }
-__device__ __forceinline__ FRec<16> f_load(const uint4& r) {
-  return {uint64_t(r.x) | (uint64_t(r.y) << 32), uint64_t(r.z) | (uint64_t(r.w) << 32)};
-}
-__device__ __forceinline__ uint2 f_store(const FRec<8>& f) { return make_uint2(uint32_t(f.k >> 32), uint32_t(f.k)); }
-__device__ __forceinline__ uint4 f_store(const FRec<16>& f) {
-  return make_uint4(uint32_t(f.k), uint32_t(f.k >> 32), uint32_t(f.p), uint32_t(f.p >> 32));
-}
-template <int R> __device__ __forceinline__ FRec<R> f_max();
-template <> __device__ __forceinline__ FRec<8> f_max<8>() { return {~0ull}; }
-template <> __device__ __forceinline__ FRec<16> f_max<16>() { return {~0ull, ~0ull}; }
-
-// Sort elements of the two per-bin sorts.
-template <int R>
-struct FE1 {  // record order
-  FRec<R> r;
-};
+// Sort elements of the two per-bin sorts (the record sort's are FE1).
 template <int R>
 struct FE2 {  // random-key order: key r (then the record, for ties)
   uint64_t key;
   FRec<R> r;
 };
 template <int R>
-__device__ __forceinline__ bool e_less(const FE1<R>& a, const FE1<R>& b) { return f_less(a.r, b.r); }
-template <int R>
-__device__ __forceinline__ FE1<R> e_sel(bool c, const FE1<R>& a, const FE1<R>& b) { return {f_sel(c, a.r, b.r)}; }
-template <int R>
-__device__ __forceinline__ FE2<R> e_sel(bool c, const FE2<R>& a, const FE2<R>& b) {
-  return {c ? a.key : b.key, f_sel(c, a.r, b.r)};
+__device__ __forceinline__ bool e_less(const FE2<R>& a, const FE2<R>& b) {
+  return (a.key < b.key) | ((a.key == b.key) & f_less(a.r, b.r));
 }
-template <uint32_t X, int R>
-__device__ __forceinline__ FE1<R> e_xor(const FE1<R>& a) { return {f_xor<X>(a.r)}; }
+template <int R>
+__device__ __forceinline__ FE2<R> e_msel(uint32_t m, const FE2<R>& a, const FE2<R>& b) {
+  return {msel64(m, a.key, b.key), f_msel(m, a.r, b.r)};
+}
 template <uint32_t X, int R>
 __device__ __forceinline__ FE2<R> e_xor(const FE2<R>& a) { return {lane_xor64<X>(a.key), f_xor<X>(a.r)}; }
 
-// Key-order element of the fast launch: the top 64 - LZ bits of the key with
-// the record rank p in the low LZ bits (dummies all ones).  While no two of a
-// bin's reals share their top key bits this orders the reals as (key, p).
+// Key-order element of the fast launch: 62 - LZ bits of the key with the
+// record rank p in the low LZ bits (dummies: 62 ones).  While no two of a
+// bin's reals share their kept key bits this orders the reals as (key, p).
+// Words below 2^62 are the bit patterns of finite doubles of positive sign, in
+// the same order, so a compare-exchange is one v_min_f64 and one v_max_f64
+// (exact: denormals are kept, there is no NaN and no zero of negative sign):
+// 9.0 cycles a pair measured, 21 with v_cmp_lt_u64 and v_cndmask.
 struct FE3 {
   uint64_t w;
 };
+constexpr uint64_t kKeyDummy = (1ull << 62) - 1ull;
 __device__ __forceinline__ bool e_less(const FE3& a, const FE3& b) { return a.w < b.w; }
-__device__ __forceinline__ FE3 e_sel(bool c, const FE3& a, const FE3& b) { return {c ? a.w : b.w}; }
+__device__ __forceinline__ FE3 e_msel(uint32_t m, const FE3& a, const FE3& b) { return {msel64(m, a.w, b.w)}; }
 template <uint32_t X>
 __device__ __forceinline__ FE3 e_xor(const FE3& a) { return {lane_xor64<X>(a.w)}; }
+// x gets the smaller (asc) or the larger word; asc is a constant
+__device__ __forceinline__ void cx_key(uint64_t& x, uint64_t& y, bool asc) {
+  uint64_t mn, mx;
+  asm("v_min_f64 %0, %1, %2" : "=v"(mn) : "v"(x), "v"(y));
+  asm("v_max_f64 %0, %1, %2" : "=v"(mx) : "v"(x), "v"(y));
+  x = asc ? mn : mx;
+  y = asc ? mx : mn;
+}
 
 // True when this lane holds two adjacent slots p, p+1 <= load (reals and the
 // first dummy) whose words agree in their key bits; the pair across the lane
 // boundary is checked by the lower lane.
 template <int LZ, uint32_t HL>
 __device__ __forceinline__ bool word_tie(const FE3 (&w)[16], uint32_t lq, uint32_t load) {
+  // (a ^ b) without the rank bits is zero
+  auto same = [](uint64_t a, uint64_t b) -> bool {
+    return (((uint32_t(a) ^ uint32_t(b)) & ~((1u << LZ) - 1u)) | (uint32_t(a >> 32) ^ uint32_t(b >> 32))) == 0u;
+  };
   bool tie = false;
 #pragma unroll
   for (uint32_t e = 0; e + 1 < 16; ++e) {
     const uint32_t p = 16u * lq + e;
-    tie |= (p < load) & ((w[e].w >> LZ) == (w[e + 1].w >> LZ));
+    tie |= (p < load) & same(w[e].w, w[e + 1].w);
   }
   if constexpr (HL > 1) {
     const uint32_t lane = threadIdx.x & 63u;
@@ -235,7 +197,7 @@ __device__ __forceinline__ bool word_tie(const FE3 (&w)[16], uint32_t lq, uint32
     const uint32_t hi = uint32_t(__shfl(int(uint32_t(w[0].w >> 32)), int(src), 64));
     const uint64_t nw = (uint64_t(hi) << 32) | lo;
     const uint32_t p = 16u * lq + 15u;
-    tie |= (lq + 1u < HL) & (p < load) & ((w[15].w >> LZ) == (nw >> LZ));
+    tie |= (lq + 1u < HL) & (p < load) & same(w[15].w, nw);
   }
   return tie;
 }
@@ -257,13 +219,7 @@ __device__ __forceinline__ uint32_t bslot(uint32_t l, uint32_t e) {
 template <int LZ, int KK, int G, int JB, typename E>
 __device__ __forceinline__ void lay_stages(E (&v)[16], uint32_t l) {
   if constexpr (JB >= 0) {
-    constexpr uint32_t hb = 1u << JB;
-#pragma unroll
-    for (uint32_t e = 0; e < 16; ++e) {
-      if (e & hb) continue;
-      const bool asc = KK == LZ || ((bslot<LZ, G>(l, e) >> KK) & 1u) == 0u;
-      cx_r<0>(v[e], v[e | hb], asc);
-    }
+    cx_stage<(1u << JB)>(v, [&](uint32_t e) { return KK == LZ || ((bslot<LZ, G>(l, e) >> KK) & 1u) == 0u; });
     lay_stages<LZ, KK, G, JB - 1>(v, l);
   }
 }
@@ -329,6 +285,75 @@ __device__ __forceinline__ void lay_phases(FE1<R> (&v)[16], FRec<R>* sb, uint32_
   }
 }
 
+// The same network over the key words (LZ = 8..10), one 64-bit LDS slot each.
+// Slots that sort descending in a phase hold their words with the sign bit
+// flipped, which reverses the doubles' order, so that every compare-exchange
+// whose direction is a lane's sorts ascending; the flip of one phase to the
+// next is one instruction a register.
+template <int LZ, int G>
+__device__ __forceinline__ void key_st(const FE3 (&w)[16], uint64_t* sb, uint32_t l, uint32_t trb) {
+  constexpr uint32_t st = pad_step<LZ, G>();
+  const uint32_t pb = pad_base<LZ, G>(l);
+#pragma unroll
+  for (uint32_t e = 0; e < 16; ++e) {
+    BOS_TR(0, 4, trb + pb + e * st);
+    sb[pb + e * st] = w[e].w;
+  }
+}
+template <int LZ, int G>
+__device__ __forceinline__ void key_ld(FE3 (&w)[16], const uint64_t* sb, uint32_t l, uint32_t trb) {
+  constexpr uint32_t st = pad_step<LZ, G>();
+  const uint32_t pb = pad_base<LZ, G>(l);
+#pragma unroll
+  for (uint32_t e = 0; e < 16; ++e) {
+    BOS_TR(0, 4, trb + pb + e * st);
+    w[e].w = sb[pb + e * st];
+  }
+}
+template <int JB, int KK>
+__device__ __forceinline__ void key_stages(FE3 (&w)[16]) {
+  if constexpr (JB >= 0) {
+    constexpr uint32_t hb = 1u << JB;
+#pragma unroll
+    for (uint32_t e = 0; e < 16; ++e) {
+      if (e & hb) continue;
+      cx_key(w[e].w, w[e | hb].w, KK >= 4 || ((e >> KK) & 1u) == 0u);
+    }
+    key_stages<JB - 1, KK>(w);
+  }
+}
+template <int LZ, int KK>
+__device__ __forceinline__ void key_phases(FE3 (&w)[16], uint64_t* sb, uint32_t l, uint32_t trb) {
+  if constexpr (KK <= LZ) {
+    if constexpr (KK >= 4) {
+      // descending in phase KK: slot bit KK (lane bit KK - 4); the previous
+      // phase's flips (KK > 4) are taken back
+      uint32_t f = KK < LZ ? l >> (KK - 4) : 0u;
+      if constexpr (KK > 4) f ^= l >> (KK - 5);
+      f <<= 31;
+#pragma unroll
+      for (uint32_t e = 0; e < 16; ++e) w[e].w ^= uint64_t(f) << 32;
+    }
+    if constexpr (KK >= 5) {
+      key_st<LZ, 0>(w, sb, l, trb);
+      lds_wave_sync();
+      if constexpr (KK >= 9) {
+        key_ld<LZ, 2>(w, sb, l, trb);
+        key_stages<KK - 1 - (LZ - 4), KK>(w);
+        key_st<LZ, 2>(w, sb, l, trb);
+        lds_wave_sync();
+      }
+      key_ld<LZ, 1>(w, sb, l, trb);
+      key_stages<(KK >= 9 ? LZ - 9 : KK - 5), KK>(w);
+      key_st<LZ, 1>(w, sb, l, trb);
+      lds_wave_sync();
+      key_ld<LZ, 0>(w, sb, l, trb);
+    }
+    key_stages<(KK >= 4 ? 3 : KK - 1), KK>(w);
+    key_phases<LZ, KK + 1>(w, sb, l, trb);
+  }
+}
+
 }  // namespace finish_detail
 
 // EXACT = false: the key sort compares the random keys alone and raises
@@ -346,6 +371,7 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
   const T* binned = static_cast<const T*>(a.binned);
   T* out = static_cast<T*>(a.out);
   extern __shared__ __align__(16) unsigned char smem[];
+  __builtin_amdgcn_s_setprio(1);  // lowered inside the networks' selects
   if constexpr (EXACT) {
     if (__hip_atomic_load(a.tie, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0ull) return;
   }
@@ -374,6 +400,7 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
     if constexpr (LZ <= 10) {
       // 1. record order, dummies (maximal record) last
       FE1<R> v[16];
+      FE3 w[(!EXACT && LZ >= 8) ? 16 : 1];
       if constexpr (!EXACT && LZ >= 8) {
         // the bin's reals read in layout Q (the bin's lanes take consecutive
         // slots), moved to layout P through the bin's LDS slots, then the
@@ -387,6 +414,24 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
           if (act && p < load) BOS_TR(0, 20, b0 + p);
           v[e] = FE1<R>{(act && p < load) ? f_load(binned[b0 + p]) : f_max<R>()};
         }
+        // 2. rank p's key r(gb*Z + p), its top bits with p below them.  The
+        // network sorts from any placement: register 4 i + q of lane lq takes
+        // rank 4 (HL i + lq) + q, so that the reals' ranks (p < load) fill the
+        // first registers of every lane and the Philox blocks past the load
+        // are not computed.  (Before the record sort: next to the sorted records
+        // the Philox registers would spill.)
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+          const uint32_t p0 = 4u * (HL * i + lq);
+#pragma unroll
+          for (uint32_t q = 0; q < 4; ++q) w[4 * i + q] = FE3{kKeyDummy};
+          if (4u * HL * i < load) {
+            const Philox4 ph = philox4x64_10(((gb << LZ) + p0) >> 2, a.attempt, a.seed, 1);
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+              if (p0 + q < load) w[4 * i + q].w = ((ph.v[q] >> (LZ + 2)) << LZ) | (p0 + q);
+          }
+        }
         lay_st<LZ, 2>(v, sb, lq, S * ZP);
         lds_wave_sync();
         lay_ld<LZ, 0>(v, sb, lq, S * ZP);
@@ -398,9 +443,57 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
           if (act && p < load) BOS_TR(0, 20, src + e);
           v[e] = FE1<R>{(act && p < load) ? f_load(binned[src + e]) : f_max<R>()};
         }
-        reg_phases<LZ, 1, 0>(v, lq);
+        reg_phases<LZ, 1>(v, lq);
       }
-      if constexpr (!EXACT) {
+      if constexpr (!EXACT && LZ >= 8) {
+        uint64_t* kb = reinterpret_cast<uint64_t*>(reinterpret_cast<T*>(smem) + S * ZP);
+        // 3. order by the words (their ranks then follow the keys); the
+        // records wait in registers while the network has the LDS slots
+        key_phases<LZ, 1>(w, kb, lq, S * ZP);
+        // 4. output slot j of the bin takes the record of rank w[j] mod Z: the
+        // ranks go through LDS into layout Q (consecutive lanes write
+        // consecutive records), then the records (rank p at padded slot
+        // p + p/16) are gathered
+        uint32_t* rb = reinterpret_cast<uint32_t*>(kb);
+        uint32_t rk[16];
+#pragma unroll
+        for (uint32_t e = 0; e < 16; ++e) {
+          BOS_TR(0, 4, S * ZP + 17u * lq + e);
+          rb[17u * lq + e] = uint32_t(w[e].w) & (Z - 1u);
+        }
+        lds_wave_sync();
+#pragma unroll
+        for (uint32_t e = 0; e < 16; ++e) {
+          const uint32_t i = pad_base<LZ, 2>(lq) + e * pad_step<LZ, 2>();
+          BOS_TR(0, 4, S * ZP + i);
+          rk[e] = rb[i];
+        }
+        lds_wave_sync();
+        FRec<R>* sbin = reinterpret_cast<FRec<R>*>(kb);
+#pragma unroll
+        for (uint32_t e = 0; e < 16; ++e) {
+          BOS_TR(0, 4, S * ZP + 17u * lq + e);
+          sbin[17u * lq + e] = v[e].r;
+        }
+        lds_wave_sync();
+        if (act) {
+#pragma unroll
+          for (uint32_t e = 0; e < 16; ++e) {
+            const uint32_t j = bslot<LZ, 2>(lq, e);
+            if (j < load && off + j < a.n) {
+              BOS_TR(0, 4, S * ZP + rk[e] + (rk[e] >> 4));
+              BOS_TR(0, 21, off + j);
+              out[off + j - a.out0] = f_store(sbin[rk[e] + (rk[e] >> 4)]);
+            }
+          }
+        }
+        lds_wave_sync();  // the bin's LDS slots are read before the next bin's records
+        // two reals with the same top key bits: the exact launch redoes it
+        if (act && word_tie<LZ, HL>(w, lq, load)) {
+          BOS_TR(0, 24, 0);
+          atomicOr(a.tie, 1ull);
+        }
+      } else if constexpr (!EXACT) {
         // the bin in record order to LDS (rank p at padded slot p + p/16;
         // the bin's lanes are one wave's)
         T* sbin = reinterpret_cast<T*>(smem) + S * ZP;
@@ -420,11 +513,11 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (uint32_t q = 0; q < 4; ++q) {
             const uint32_t e = 4u * e4 + q;
-            w[e] = FE3{p0 + q < load ? ((ph.v[q] >> LZ) << LZ) | (p0 + q) : ~0ull};
+            w[e] = FE3{p0 + q < load ? ((ph.v[q] >> (LZ + 2)) << LZ) | (p0 + q) : kKeyDummy};
           }
         }
         // 3. order by the words (their ranks then follow the keys)
-        reg_phases<LZ, 1, 0>(w, lq);
+        reg_phases<LZ, 1>(w, lq);
         lds_wave_sync();
         // 4. output slot j of the bin takes the record of rank w[j] mod Z
         if (act) {
@@ -460,7 +553,7 @@ __global__ __launch_bounds__(kFinishThreads) __attribute__((amdgpu_waves_per_eu(
         }
         // 3. order by (key, record), which is (key, p) as the reals are in
         //    record order
-        reg_phases<LZ, 1, 2>(w, lq);
+        reg_phases<LZ, 1>(w, lq);
         // 4. the reals to their place in the output
         if (act) {
 #pragma unroll

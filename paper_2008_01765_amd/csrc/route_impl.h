@@ -28,6 +28,8 @@
 #pragma once
 #include "bos_common.h"
 
+#include <type_traits>
+
 namespace bos {
 
 namespace route_detail {
@@ -103,14 +105,124 @@ template <> struct HalfOf<uint2> {
   static __device__ __forceinline__ H zero() { return 0u; }
 };
 
-// Swap decision of the compaction network for the pair at offset i of a node
-// of 2*half slots whose marks prefix is P0 at its start and Ph at its middle.
-__device__ __forceinline__ bool swap_bit(uint32_t P0, uint32_t Ph, uint32_t half, uint32_t i) {
-  if (half == 1u) return (Ph - P0) == (P0 & 1u);  // the rule below with half = 1
-  const uint32_t z = P0 & (2u * half - 1u), mm = Ph - P0;
-  const bool s = (((z & (half - 1u)) + mm) >= half) != (z >= half);
-  const uint32_t t = (z + mm) & (half - 1u);
-  return s != (i >= t);
+// Swap rule of the compaction network.  A node of 2*half slots starts at marks
+// prefix P0 and has prefix Ph at its middle; the recursion of Sasy, Johnson
+// and Goldberg swaps the pair at offset i when s != (i >= t), with z = P0 mod
+// 2*half, mm = Ph - P0, t = (z + mm) mod half and s = (z mod half + mm >= half)
+// != (z >= half).  Since z + mm = Ph (mod 2*half), t and s are the low and the
+// high part of Ph mod 2*half, and the rule is one bit: the pair is swapped when
+// bit log2(half) of Ph - 1 - i is set.  Prefixes are therefore kept as Ph - 1,
+// shifted left so that this bit is the sign bit ("scaled"), and a decision is
+// one subtraction and one arithmetic shift, a mask of all ones or zeros.
+//
+// The masks drive v_bitop3_b32 selects.  gfx950 issues the vector instructions
+// of two waves of a SIMD together when at least one of them is a "light" one:
+// measured with 4 waves per SIMD, v_bitop3, v_add/v_sub, v_and/v_or/v_xor and
+// right shifts take 2.4 cycles each, while v_cmp, v_cndmask, v_min, v_bfe,
+// left shifts and every DPP form take 4.5 on their own.  A conditional swap of
+// three words is 8 light instructions (17.5 cycles) and was v_cmp, a scalar
+// xor and 6 v_cndmask (28-30).
+//
+// The oldest wave wins arbitration, so a wave that runs light instructions
+// alone keeps a wave that waits at a heavy one out, and nothing issues
+// together until the first one stalls (8 heavy + 24 light instructions: 3.9
+// cycles each).  Raising a wave's priority while it runs its heavy ones (2.3
+// cycles each) lets it pass: kernels built on these networks run at priority
+// 1 and drop to 0 inside runs of light instructions (light_begin, light_end).
+__device__ __forceinline__ void light_begin() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_setprio(0);
+}
+__device__ __forceinline__ void light_end() {
+  __builtin_amdgcn_s_setprio(1);
+  __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ uint32_t sign_mask(uint32_t d) {
+  uint32_t m;
+  // (in C the compiler folds the shift into v_bfe_i32 or v_cmp + v_cndmask)
+  asm("v_ashrrev_i32 %0, 31, %1" : "=v"(m) : "v"(d));
+  return m;
+}
+// Mask of bit 0 of x.
+__device__ __forceinline__ uint32_t low_bit_mask(uint32_t x) {
+  uint32_t m;
+  asm("v_sub_u32 %0, 0, %1" : "=v"(m) : "v"(x & 1u));
+  return m;
+}
+// Per bit: m ? a : b.
+__device__ __forceinline__ uint32_t msel(uint32_t m, uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
+}
+__device__ __forceinline__ uint2 msel(uint32_t m, uint2 a, uint2 b) {
+  return make_uint2(msel(m, a.x, b.x), msel(m, a.y, b.y));
+}
+__device__ __forceinline__ uint4 msel(uint32_t m, uint4 a, uint4 b) {
+  return make_uint4(msel(m, a.x, b.x), msel(m, a.y, b.y), msel(m, a.z, b.z), msel(m, a.w, b.w));
+}
+// Exchange (a, ta) and (b, tb) where m is set.
+template <typename T>
+__device__ __forceinline__ void mswap(uint32_t m, T& a, uint32_t& ta, T& b, uint32_t& tb) {
+  const T na = msel(m, b, a), nb = msel(m, a, b);
+  const uint32_t nta = msel(m, tb, ta), ntb = msel(m, ta, tb);
+  a = na;
+  b = nb;
+  ta = nta;
+  tb = ntb;
+}
+
+// Stages on slot bits 0..3 of a lane's 16 consecutive slots (register pairs);
+// pm[e] = prefix - 1 at slot e of the lane.  Slot e is the middle of exactly
+// one node, of half 2^ctz(e).
+template <typename T>
+__device__ __forceinline__ void lane_stages(T (&rv)[16], uint32_t (&tv)[16], const uint32_t (&pm)[16]) {
+  uint32_t q[16];
+#pragma unroll
+  for (uint32_t e = 0; e < 16; ++e) q[e] = (e & 1u) ? pm[e] : pm[e] << (31u - __builtin_ctz(e | 16u));
+  light_begin();
+#pragma unroll
+  for (uint32_t eb = 0; eb < 4; ++eb) {
+    const uint32_t half = 1u << eb;
+#pragma unroll
+    for (uint32_t es = 0; es < 16; es += 2u * half) {
+#pragma unroll
+      for (uint32_t i = 0; i < half; ++i) {
+        const uint32_t m = eb == 0 ? low_bit_mask(q[es | half]) : sign_mask(q[es | half] - (i << (31u - eb)));
+        mswap(m, rv[es + i], tv[es + i], rv[es + i + half], tv[es + i + half]);
+      }
+    }
+  }
+  light_end();
+}
+
+// One stage between lanes: slot e of this lane and of its partner lane (DPP
+// control CTRL) swap where bit 31 of q - e * step is set.  The partners' words
+// of four slots are fetched (heavy), then selected (light).
+template <uint32_t CTRL, typename T>
+__device__ __forceinline__ void dpp_stage(T (&rv)[16], uint32_t (&tv)[16], uint32_t q, uint32_t step) {
+#pragma unroll
+  for (uint32_t e0 = 0; e0 < 16; e0 += 4) {
+    T pr[4];
+    uint32_t pt[4];
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      pr[e] = dpp<CTRL>(rv[e0 + e]);
+      pt[e] = dpp<CTRL>(tv[e0 + e]);
+    }
+    light_begin();
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      const uint32_t m = sign_mask(q - (e0 + e) * step);
+      rv[e0 + e] = msel(m, pr[e], rv[e0 + e]);
+      tv[e0 + e] = msel(m, pt[e], tv[e0 + e]);
+    }
+    light_end();
+  }
+}
+
+// Scaled prefix of lane lt's first slot (slot 16 lt of the node tree), the
+// middle of the node of half 2^(4 + ctz(lt)); top = the tree's lane count.
+__device__ __forceinline__ uint32_t lane_prefix(uint32_t pm0, uint32_t lt, uint32_t top) {
+  return pm0 << (27u - uint32_t(__builtin_ctz(lt | top)));
 }
 
 // DPP source with lanes outside the pattern (or rows outside ROW_MASK)
@@ -230,6 +342,67 @@ __device__ __forceinline__ ElemRK<T> e_dpp(const ElemRK<T>& a) {
   return ElemRK<T>{dpp<CTRL>(a.r), dpp<CTRL>(a.klo), dpp<CTRL>(a.khi), dpp<CTRL>(a.aux)};
 }
 
+// A record as the words that order it: one 64-bit word (key << 32 | payload)
+// for 8-byte records, (key, payload) for 16-byte ones.
+template <int R> struct FRec;
+template <> struct FRec<8> {
+  uint64_t k;
+};
+template <> struct FRec<16> {
+  uint64_t k, p;
+};
+__device__ __forceinline__ bool f_less(const FRec<8>& a, const FRec<8>& b) { return a.k < b.k; }
+__device__ __forceinline__ bool f_less(const FRec<16>& a, const FRec<16>& b) {
+  return (a.k < b.k) | ((a.k == b.k) & (a.p < b.p));
+}
+__device__ __forceinline__ bool f_eq(const FRec<8>& a, const FRec<8>& b) { return a.k == b.k; }
+__device__ __forceinline__ bool f_eq(const FRec<16>& a, const FRec<16>& b) { return (a.k == b.k) & (a.p == b.p); }
+__device__ __forceinline__ FRec<8> f_sel(bool c, const FRec<8>& a, const FRec<8>& b) { return {c ? a.k : b.k}; }
+__device__ __forceinline__ FRec<16> f_sel(bool c, const FRec<16>& a, const FRec<16>& b) {
+  return {c ? a.k : b.k, c ? a.p : b.p};
+}
+__device__ __forceinline__ FRec<8> f_load(const uint2& r) { return {(uint64_t(r.x) << 32) | r.y}; }
+__device__ __forceinline__ FRec<16> f_load(const uint4& r) {
+  return {uint64_t(r.x) | (uint64_t(r.y) << 32), uint64_t(r.z) | (uint64_t(r.w) << 32)};
+}
+__device__ __forceinline__ uint2 f_store(const FRec<8>& f) { return make_uint2(uint32_t(f.k >> 32), uint32_t(f.k)); }
+__device__ __forceinline__ uint4 f_store(const FRec<16>& f) {
+  return make_uint4(uint32_t(f.k), uint32_t(f.k >> 32), uint32_t(f.p), uint32_t(f.p >> 32));
+}
+template <int R> __device__ __forceinline__ FRec<R> f_max();
+template <> __device__ __forceinline__ FRec<8> f_max<8>() { return {~0ull}; }
+template <> __device__ __forceinline__ FRec<16> f_max<16>() { return {~0ull, ~0ull}; }
+
+template <int R>
+struct FE1 {  // sort element: a record in record order
+  FRec<R> r;
+};
+template <int R>
+__device__ __forceinline__ bool e_less(const FE1<R>& a, const FE1<R>& b) { return f_less(a.r, b.r); }
+template <int R>
+__device__ __forceinline__ FE1<R> e_sel(bool c, const FE1<R>& a, const FE1<R>& b) { return {f_sel(c, a.r, b.r)}; }
+__device__ __forceinline__ uint64_t msel64(uint32_t m, uint64_t a, uint64_t b) {
+  return (uint64_t(msel(m, uint32_t(a >> 32), uint32_t(b >> 32))) << 32) | msel(m, uint32_t(a), uint32_t(b));
+}
+__device__ __forceinline__ FRec<8> f_msel(uint32_t m, const FRec<8>& a, const FRec<8>& b) {
+  return {msel64(m, a.k, b.k)};
+}
+__device__ __forceinline__ FRec<16> f_msel(uint32_t m, const FRec<16>& a, const FRec<16>& b) {
+  return {msel64(m, a.k, b.k), msel64(m, a.p, b.p)};
+}
+template <int R>
+__device__ __forceinline__ FE1<R> e_msel(uint32_t m, const FE1<R>& a, const FE1<R>& b) {
+  return {f_msel(m, a.r, b.r)};
+}
+template <uint32_t CTRL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+  return uint64_t(dpp<CTRL>(uint32_t(v))) | (uint64_t(dpp<CTRL>(uint32_t(v >> 32))) << 32);
+}
+template <uint32_t CTRL>
+__device__ __forceinline__ FE1<8> e_dpp(const FE1<8>& a) { return {{dpp64<CTRL>(a.r.k)}}; }
+template <uint32_t CTRL>
+__device__ __forceinline__ FE1<16> e_dpp(const FE1<16>& a) { return {{dpp64<CTRL>(a.r.k), dpp64<CTRL>(a.r.p)}}; }
+
 // LDS views of the bins (padded slot index)
 // (tw: the trace buffer its accesses fold into in the digest build: 0 for
 // the routing and the per-bin finish, 1 for the comparison sort)
@@ -242,6 +415,19 @@ struct LdsR {
     return ElemR<T>{rec[i]};
   }
   __device__ void st(uint32_t i, const ElemR<T>& v) const {
+    BOS_TR(tw, 4, i);
+    rec[i] = v.r;
+  }
+};
+template <int R>
+struct LdsF {  // the ordering words themselves: no conversion between layouts
+  FRec<R>* rec;
+  uint32_t tw = 0;
+  __device__ FE1<R> ld(uint32_t i) const {
+    BOS_TR(tw, 4, i);
+    return FE1<R>{rec[i]};
+  }
+  __device__ void st(uint32_t i, const FE1<R>& v) const {
     BOS_TR(tw, 4, i);
     rec[i] = v.r;
   }
@@ -266,20 +452,65 @@ struct LdsRK {
   }
 };
 
-// Compare-exchange with one comparison: equal elements are byte-identical, so
-// swapping them or not is the same.
+template <typename T>
+__device__ __forceinline__ ElemR<T> e_msel(uint32_t m, const ElemR<T>& a, const ElemR<T>& b) {
+  return ElemR<T>{msel(m, a.r, b.r)};
+}
+template <typename T>
+__device__ __forceinline__ ElemRK<T> e_msel(uint32_t m, const ElemRK<T>& a, const ElemRK<T>& b) {
+  return ElemRK<T>{msel(m, a.r, b.r), msel(m, a.klo, b.klo), msel(m, a.khi, b.khi), msel(m, a.aux, b.aux)};
+}
+// c ? a : b of whole elements, by a word mask
 template <typename E>
-__device__ __forceinline__ void cx_reg(E& x, E& y, bool asc) {
-  const bool sw = e_less(y, x) == asc;
-  const E nx = e_sel(sw, y, x), ny = e_sel(sw, x, y);
-  x = nx;
-  y = ny;
+__device__ __forceinline__ E e_pick(bool c, const E& a, const E& b) {
+  if constexpr (std::is_same_v<E, ElemR<uint2>>) return e_sel(c, a, b);
+  else return e_msel(c ? ~0u : 0u, a, b);
+}
+
+// One stage on register pairs (e, e | HB) of a lane; asc(e): the pair sorts
+// ascending.  All comparisons first (heavy), then the selects on word masks
+// (light, see above): 16.1 cycles per pair of 64-bit words measured against
+// 20.5 with each comparison followed by its v_cndmask.  (Tiles of 8-byte
+// records keep the v_cndmask form, ElemR<uint2>: with four waves a SIMD, three
+// barriers a phase and LDS busy 58 % of the time the light form took 2.34 ms
+// for 2^28 records and that one 2.18; 16-byte tiles 0.385 ms for 2^24 records
+// and 0.426.)  Equal elements are byte-identical, so swapping them or not is
+// the same.
+template <uint32_t HB, typename E, typename ASC>
+__device__ __forceinline__ void cx_stage(E (&v)[16], ASC asc) {
+  if constexpr (std::is_same_v<E, ElemR<uint2>>) {
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) {
+      const uint32_t e = ((i & ~(HB - 1u)) << 1) | (i & (HB - 1u));
+      const bool sw = e_less(v[e | HB], v[e]) == asc(e);
+      const E x = e_sel(sw, v[e | HB], v[e]), y = e_sel(sw, v[e], v[e | HB]);
+      v[e] = x;
+      v[e | HB] = y;
+    }
+    return;
+  }
+  bool sw[8];
+#pragma unroll
+  for (uint32_t i = 0; i < 8; ++i) {
+    const uint32_t e = ((i & ~(HB - 1u)) << 1) | (i & (HB - 1u));
+    sw[i] = e_less(v[e | HB], v[e]) == asc(e);
+  }
+  light_begin();
+#pragma unroll
+  for (uint32_t i = 0; i < 8; ++i) {
+    const uint32_t e = ((i & ~(HB - 1u)) << 1) | (i & (HB - 1u));
+    const uint32_t m = sw[i] ? ~0u : 0u;
+    const E x = e_msel(m, v[e | HB], v[e]), y = e_msel(m, v[e], v[e | HB]);
+    v[e] = x;
+    v[e | HB] = y;
+  }
+  light_end();
 }
 template <uint32_t CTRL, typename E>
 __device__ __forceinline__ void cx_lane(E& x, bool is_lo, bool asc) {
   const E p = e_dpp<CTRL>(x);
   const bool take = e_less(p, x) == (is_lo == asc);
-  x = e_sel(take, p, x);
+  x = e_pick(take, p, x);
 }
 
 // Bitonic sort (ascending) of every bin; v holds layout P on entry and exit.
@@ -309,12 +540,7 @@ template <int LZ, int KK, int JJ, typename E>
 __device__ __forceinline__ void p_stages(E (&v)[16], const BinLane& bl) {
   if constexpr (JJ >= 0) {
     if constexpr (JJ < 4) {
-      constexpr uint32_t hb = 1u << JJ;
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        if (e & hb) continue;
-        cx_reg(v[e], v[e | hb], asc_p<LZ, KK>(e, bl));
-      }
+      cx_stage<(1u << JJ)>(v, [&](uint32_t e) { return asc_p<LZ, KK>(e, bl); });
     } else if constexpr (JJ == 4) {
       const bool asc = asc_p<LZ, KK>(0, bl);
 #pragma unroll
@@ -332,12 +558,7 @@ template <int LZ, int KK, int JJ, typename E>
 __device__ __forceinline__ void q_stages(E (&v)[16], const BinLane& bl) {
   if constexpr (JJ >= 6) {
     if constexpr (JJ >= LZ - 4) {
-      constexpr uint32_t hb = 1u << (JJ - (LZ - 4));
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        if (e & hb) continue;
-        cx_reg(v[e], v[e | hb], asc_q<LZ, KK>(e, bl));
-      }
+      cx_stage<(1u << (JJ - (LZ - 4)))>(v, [&](uint32_t e) { return asc_q<LZ, KK>(e, bl); });
     } else if constexpr (JJ == LZ - 5) {  // lane bit 1 of layout Q (2^LZ >= 2048)
 #pragma unroll
       for (uint32_t e = 0; e < 16; ++e) cx_lane<kDppXor2>(v[e], bl.lb1 == 0u, asc_q<LZ, KK>(e, bl));
@@ -498,34 +719,31 @@ __device__ __forceinline__ uint4 swz_xor(uint4 v) {
 }
 
 // One compaction stage at distance 16 HLX (< 512 slots): the partner slot is
-// held by lane lq ^ HLX, reached by a swizzle; P0 and Ph are the reals'
-// prefix counts at the node's start and middle (the bin's lane prefixes).
+// held by lane lq ^ HLX, reached by a swizzle; bpfx holds the scaled prefixes
+// of the bin's lanes, the node's middle is its lane HLX.
 template <uint32_t HLX, typename T>
 __device__ __forceinline__ void compact_xstage(T (&rv)[16], uint32_t (&tv)[16], const uint32_t* bpfx, uint32_t lq,
                                                bool active) {
-  constexpr uint32_t half = HLX * 16u;
-  const uint32_t node0 = lq & ~(2u * HLX - 1u);
-  if (active) {
-    BOS_TR(0, 6, node0);
-    BOS_TR(0, 6, node0 + HLX);
-  }
-  const uint32_t P0 = active ? bpfx[node0] : 0u, Ph = active ? bpfx[node0 + HLX] : 0u;
+  constexpr uint32_t LH = 4u + uint32_t(__builtin_ctz(HLX));  // log2 of the distance
+  const uint32_t mid = (lq & ~(2u * HLX - 1u)) + HLX;
+  if (active) BOS_TR(0, 6, mid);
+  // index in the node's half: 16 (lq mod HLX) + e
+  const uint32_t q = (active ? bpfx[mid] : 0u) - ((lq & (HLX - 1u)) << (35u - LH));
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
-    const uint32_t i = 16u * (lq & (HLX - 1u)) + e;  // index in the node's half
-    const bool b = active && swap_bit(P0, Ph, half, i);
+    const uint32_t m = sign_mask(q - (e << (31u - LH)));
     const T pr = swz_xor<HLX>(rv[e]);
     const uint32_t pt = swz_xor<HLX>(tv[e]);
-    rv[e] = sel(b, pr, rv[e]);
-    tv[e] = b ? pt : tv[e];
+    rv[e] = msel(m, pr, rv[e]);
+    tv[e] = msel(m, pt, tv[e]);
   }
 }
 
 // Oblivious compaction of every final bin in LDS: the bin's reals move to
 // its first slots.  The last level leaves each bin's reals interleaved with
 // dummies; this is the tight compaction network a MergeSplit level runs
-// (conditional swaps at distances 1, 2, .., Z/2, each decided by swap_bit from
-// the prefix counts of the reals), over one bin of Z slots with the reals as
+// (conditional swaps at distances 1, 2, .., Z/2, each decided by the swap rule
+// above from the prefix counts of the reals), over one bin of Z slots with the reals as
 // the marks.  Lane lq of the bin's Z/16 lanes holds slots 16 lq + e; stages at
 // distances below 16 pair registers, those up to 256 pair lanes by swizzles,
 // and longer ones exchange through the bin's own LDS slots.  On return rv
@@ -553,39 +771,25 @@ __device__ __forceinline__ void compact_bin(typename RecOf<R>::T* srec, uint32_t
       tv[e] = active ? stag[bbase + 17u * lq + e] : kDummyTag;
     }
   }
-  // prefix counts of the reals
+  // prefix counts of the reals, minus one (a dummy's tag is all ones, a
+  // label has its sign bit clear: 1 + the sign mask counts a real)
   uint32_t pm[16];
   uint32_t run = 0;
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
     pm[e] = run;
-    run += tv[e] != kDummyTag ? 1u : 0u;
+    run += 1u + sign_mask(tv[e]);
   }
   uint32_t tot;
-  const uint32_t excl = seg_scan<HL>(active ? run : 0u, swave, &tot);
+  const uint32_t excl = seg_scan<HL>(active ? run : 0u, swave, &tot) - 1u;
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) pm[e] += excl;
   if (active) {
     BOS_TR(0, 6, S * HL + lq);
-    spfx[S * HL + lq] = pm[0];
+    spfx[S * HL + lq] = lane_prefix(pm[0], lq, HL);
   }
   // distances 1, 2, 4, 8: register pairs
-#pragma unroll
-  for (uint32_t eb = 0; eb < 4; ++eb) {
-    const uint32_t half = 1u << eb;
-#pragma unroll
-    for (uint32_t e = 0; e < 16; ++e) {
-      if (e & half) continue;
-      const uint32_t e2 = e | half, es = e & ~(2u * half - 1u);
-      const bool b = swap_bit(pm[es], pm[es | half], half, e & (half - 1u));
-      const T r1 = rv[e], r2 = rv[e2];
-      const uint32_t t1 = tv[e], t2 = tv[e2];
-      rv[e] = sel(b, r2, r1);
-      rv[e2] = sel(b, r1, r2);
-      tv[e] = b ? t2 : t1;
-      tv[e2] = b ? t1 : t2;
-    }
-  }
+  lane_stages(rv, tv, pm);
   // distances 16 .. 256: the partner lane is lq ^ (half / 16), within 32 lanes
   lds_group_sync<HL>();  // every lane's prefix is in spfx
   const uint32_t* bpfx = spfx + S * HL;
@@ -595,7 +799,8 @@ __device__ __forceinline__ void compact_bin(typename RecOf<R>::T* srec, uint32_t
   if constexpr (HL >= 16) compact_xstage<8>(rv, tv, bpfx, lq, active);
   if constexpr (HL >= 32) compact_xstage<16>(rv, tv, bpfx, lq, active);
   // distances 512 .. Z/2 (Z >= 1024): through the bin's LDS slots
-  for (uint32_t half = 512; half < Z; half <<= 1) {
+#pragma unroll
+  for (uint32_t lh = 9; lh + 1 <= LZ; ++lh) {
     lds_group_sync<HL>();  // spfx written; the previous stage's reads are done
     if (active) {
 #pragma unroll
@@ -607,18 +812,14 @@ __device__ __forceinline__ void compact_bin(typename RecOf<R>::T* srec, uint32_t
       }
     }
     lds_group_sync<HL>();
-    const uint32_t hl = half >> 4;                   // lanes per half node
-    const uint32_t node0 = lq & ~(2u * hl - 1u);     // first lane of this lane's node
+    const uint32_t hl = 1u << (lh - 4u);                  // lanes per half node
+    const uint32_t mid = (lq & ~(2u * hl - 1u)) + hl;     // the node's middle lane
     const uint32_t plq = lq ^ hl;
-    if (active) {
-      BOS_TR(0, 6, S * HL + node0);
-      BOS_TR(0, 6, S * HL + node0 + hl);
-    }
-    const uint32_t P0 = active ? spfx[S * HL + node0] : 0u, Ph = active ? spfx[S * HL + node0 + hl] : 0u;
+    if (active) BOS_TR(0, 6, S * HL + mid);
+    const uint32_t q = (active ? bpfx[mid] : 0u) - ((lq & (hl - 1u)) << (35u - lh));
 #pragma unroll
     for (uint32_t e = 0; e < 16; ++e) {
-      const uint32_t i = 16u * (lq & (hl - 1u)) + e;  // index in the node's half
-      const bool b = active && swap_bit(P0, Ph, half, i);
+      const uint32_t m = sign_mask(q - (e << (31u - lh)));
       const uint32_t pi = bbase + 17u * plq + e;
       if (active) {
         BOS_TR(0, 4, pi);
@@ -626,8 +827,8 @@ __device__ __forceinline__ void compact_bin(typename RecOf<R>::T* srec, uint32_t
       }
       const T pr = active ? srec[pi] : zero_rec<T>();
       const uint32_t pt = active ? stag[pi] : kDummyTag;
-      rv[e] = sel(b, pr, rv[e]);
-      tv[e] = b ? pt : tv[e];
+      rv[e] = msel(m, pr, rv[e]);
+      tv[e] = msel(m, pt, tv[e]);
     }
   }
 }
@@ -822,6 +1023,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   uint32_t* srhi = smisc + 16;         // last pass, shuffle
   uint16_t* saux = reinterpret_cast<uint16_t*>(srhi + mp);
 
+  __builtin_amdgcn_s_setprio(1);  // light_begin / light_end lower it inside the networks
   const uint32_t tid = threadIdx.x, nthr = blockDim.x;
   const uint64_t n = a.n, B = a.buckets;
   const uint32_t L = a.levels, i0 = a.level0;
@@ -843,23 +1045,39 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   T rv[16];
   uint32_t tv[16];
 
+  // bucket slot that register e of the bucket's lane lh loads (passes after
+  // the first)
+  auto in_slot = [&](uint32_t e, uint32_t lh) -> uint32_t {
+    if constexpr (R == 8)
+      return (e >> 1) * (2u * HALF_LANES) + 2u * lh + (e & 1u);
+    else
+      return e * HALF_LANES + lh;
+  };
   auto issue_load = [&](uint32_t item, T* dr, uint32_t* dt) {
     const uint64_t r = uint64_t(item) & ((1ull << i0) - 1ull), h = uint64_t(item) >> i0;
     if constexpr (!FIRST) {
       const uint64_t bucket = (h << (i0 + klev)) + (uint64_t(S_load) << i0) + r;
-      const uint64_t gi = (bucket << LZ) + sb_load;
+      const uint64_t gi = bucket << LZ;
       // staged chunk: input segment S_load holds buckets (S_load, r in0 ..)
       const uint64_t si = a.staged ? ((((h - a.in_h0) << (i0 + klev)) + (uint64_t(S_load) << a.in_lseg) +
-                                       (r - a.in_r0)) << LZ) + sb_load
+                                       (r - a.in_r0)) << LZ)
                                    : gi;
+      // A bucket is a set, so its slots take the network's positions in the
+      // order that loads best: register pairs (e, e + 1) of a lane hold two
+      // consecutive slots and consecutive lanes consecutive pairs (16-byte
+      // records: consecutive lanes consecutive slots), so a wave's instruction
+      // reads whole lines.  (With lane lt holding slots 16 lt .. 16 lt + 15
+      // every instruction of a wave touched 64 lines.)
+      const uint32_t lh = lt % HALF_LANES;
 #pragma unroll
       for (uint32_t e = 0; e < 16; ++e) {
+        const uint32_t s = in_slot(e, lh);
         if (active) {
-          BOS_TR(0, 1, gi + e);
-          BOS_TR(0, 2, gi + e);
+          BOS_TR(0, 1, gi + s);
+          BOS_TR(0, 2, gi + s);
         }
-        dr[e] = active ? RI[si + e] : zero_rec<T>();
-        dt[e] = active ? a.tag_in[si + e] : kDummyTag;
+        dr[e] = active ? RI[si + s] : zero_rec<T>();
+        dt[e] = active ? a.tag_in[si + s] : kDummyTag;
       }
     } else {
       // group j = h*NB + S_load holds X[floor(jn/B), floor((j+1)n/B))
@@ -1070,30 +1288,52 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
           }
         }
       }
-      // prefix counts of (class-0 reals, dummies) in 16-bit halves
+      // prefix counts of class-0 reals (bits 0 ..) and dummies (bits FB ..).
+      // tag >> shift (arithmetic) is all ones for a dummy and a real's label
+      // down to its routing bit, below 2^FB while L <= FB; longer labels
+      // (L > FB) are cut to their routing bit first.
+      constexpr uint32_t FB = 31u - LQ;
       uint32_t pk[16];
       uint32_t run = 0;
+      uint32_t kf = (1u << FB) | 1u;
+      asm("" : "+v"(kf));  // v_bitop3 takes no literal
+      light_begin();
+      if (L <= FB) {
 #pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        const uint32_t tg = tv[e];
-        const bool real = tg != kDummyTag;
-        const bool c0 = real && ((tg >> shift) & 1u) == 0u;
-        pk[e] = run;
-        run += (c0 ? 1u : 0u) | (real ? 0u : 0x10000u);
+        for (uint32_t e = 0; e < 16; ++e) {
+          pk[e] = run;
+          const uint32_t x = uint32_t(int32_t(tv[e]) >> shift);
+          run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);  // (x & kf) ^ 1
+        }
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 16; ++e) {
+          pk[e] = run;
+          const uint32_t x = uint32_t(int32_t(tv[e]) >> shift) & (sign_mask(tv[e]) | 1u);
+          run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);
+        }
       }
+      light_end();
       uint32_t tot;
       const uint32_t excl = seg_scan<TPM>(active ? run : 0u, swave, &tot);
-      const uint32_t x = tot & 0xFFFFu, nd = tot >> 16, y = 2u * Z - x - nd;
+      const uint32_t x = tot & ((1u << FB) - 1u), nd = tot >> FB, y = 2u * Z - x - nd;
       const uint32_t need = x <= Z ? Z - x : 0u;
+      // marks before slot e: class-0 reals + min(dummies, need); pm[e] is one
+      // less, modulo 2Z.  The count fields are biased (2Z - 1 + need below,
+      // -need above), so that min(dummies, need) = need + min(upper field, 0).
+      const uint32_t bias = excl + (2u * Z - 1u + need) - (need << FB);
       uint32_t pm[16];
+      light_begin();
 #pragma unroll
       for (uint32_t e = 0; e < 16; ++e) {
-        const uint32_t pe = excl + pk[e];
-        pm[e] = (pe & 0xFFFFu) + min(pe >> 16, need);
+        const uint32_t pe = bias + pk[e];
+        pm[e] = (pe & ((1u << FB) - 1u)) + (uint32_t(int32_t(pe) >> FB) & sign_mask(pe));
       }
+      light_end();
+      const uint32_t qm = lane_prefix(pm[0], lt, TPM);
       if (active) {
         BOS_TR(0, 6, ms * TPM + lt);
-        spfx[ms * TPM + lt] = pm[0];
+        spfx[ms * TPM + lt] = qm;
         if (LAST && lt == 0 && d + 1 == klev) {
           // bin loads of this block: S0 keeps min(x, Z) reals, S1 the rest of
           // the pair's reals (exact even when the MergeSplit overflowed)
@@ -1112,46 +1352,14 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         }
       }
       // -- layout A, q bits 0..3: register pairs
-#pragma unroll
-      for (uint32_t eb = 0; eb < 4; ++eb) {
-        const uint32_t half = 1u << eb;
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          if (e & half) continue;
-          const uint32_t e2 = e | half, es = e & ~(2u * half - 1u);
-          const bool b = swap_bit(pm[es], pm[es | half], half, e & (half - 1u));
-          const T r1 = rv[e], r2 = rv[e2];
-          const uint32_t t1 = tv[e], t2 = tv[e2];
-          rv[e] = sel(b, r2, r1);
-          rv[e2] = sel(b, r1, r2);
-          tv[e] = b ? t2 : t1;
-          tv[e2] = b ? t1 : t2;
-        }
-      }
+      lane_stages(rv, tv, pm);
       // -- layout A, q bit 4: lanes l and l^1 (node = 2 lanes, half = 16)
       if constexpr (LQ >= 5) {
-        const uint32_t P0 = dpp<kDppB0022>(pm[0]), Ph = dpp<kDppB1133>(pm[0]);
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          const bool b = swap_bit(P0, Ph, 16u, e);
-          const T pr = dpp<kDppXor1>(rv[e]);
-          const uint32_t pt = dpp<kDppXor1>(tv[e]);
-          rv[e] = sel(b, pr, rv[e]);
-          tv[e] = b ? pt : tv[e];
-        }
+        dpp_stage<kDppXor1>(rv, tv, dpp<kDppB1133>(qm), 1u << 27);
       }
       // -- layout A, q bit 5: lanes l and l^2 (node = 4 lanes, half = 32)
       if constexpr (LQ >= 6) {
-        const uint32_t P0 = dpp<kDppB0000>(pm[0]), Ph = dpp<kDppB2222>(pm[0]);
-        const uint32_t ioff = 16u * (lt & 1u);
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          const bool b = swap_bit(P0, Ph, 32u, ioff + e);
-          const T pr = dpp<kDppXor2>(rv[e]);
-          const uint32_t pt = dpp<kDppXor2>(tv[e]);
-          rv[e] = sel(b, pr, rv[e]);
-          tv[e] = b ? pt : tv[e];
-        }
+        dpp_stage<kDppXor2>(rv, tv, dpp<kDppB2222>(qm) - ((lt & 1u) << 30), 1u << 26);
       }
       // lane lt in layout B: q = e << (LQ-4) | lb1 << (LQ-5) | lb0 << (LQ-6) | rest
       uint32_t baseB0 = 0, baseB1 = 0, lowB = 0;
@@ -1182,14 +1390,17 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
                       [&](uint32_t e) { return b_index(e, base0, base1, baseB0, baseB1, lowB); },
                       [] { lds_group_sync<TPM>(); });
         }
-        // marks prefix at node boundaries (multiples of 16 slots)
+        // scaled marks prefixes at the node middles (multiples of 16 slots)
         uint32_t pv[16], pvh[16];
 #pragma unroll
         for (uint32_t e = 0; e < 16; ++e) {
           const uint32_t q = e << (LQ - 4);
-          const uint32_t i1 = (q & 15u) == 0u ? (q >> 4) : 0u;
-          if (active) BOS_TR(0, 6, ms * TPM + i1);
-          pv[e] = active ? spfx[ms * TPM + i1] : 0u;
+          pv[e] = 0;
+          // slot q is the middle of a node of half 2^(LQ-4+ctz(e)), at least 64
+          if (e != 0 && LQ - 4 + __builtin_ctz(e | 16u) >= 6) {
+            if (active) BOS_TR(0, 6, ms * TPM + (q >> 4));
+            pv[e] = active ? spfx[ms * TPM + (q >> 4)] : 0u;
+          }
           if constexpr (LQ >= 11) {
             const uint32_t qh = q | (1u << (LQ - 5));
             if (active) BOS_TR(0, 6, ms * TPM + (qh >> 4));
@@ -1212,54 +1423,52 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         }
         // -- layout B, q bit LQ-6 (lane bit 0), only for Z = 2048
         if constexpr (LQ - 6 >= 6) {
-          const uint32_t half = 1u << (LQ - 6);
+          constexpr uint32_t LH = LQ - 6;
 #pragma unroll
           for (uint32_t e = 0; e < 16; ++e) {
-            // node: q bits 0..LQ-6 cleared; its start and middle are 16-aligned
-            const uint32_t qn = (e << (LQ - 4)) | (lb1 << (LQ - 5));
+            // node: q bits 0..LQ-6 cleared; its middle is 16-aligned
+            const uint32_t qn = (e << (LQ - 4)) | (lb1 << (LQ - 5)) | (1u << LH);
             BOS_TR(0, 6, ms * TPM + (qn >> 4));
-            BOS_TR(0, 6, ms * TPM + ((qn | half) >> 4));
-            const uint32_t P0 = spfx[ms * TPM + (qn >> 4)];
-            const uint32_t Ph = spfx[ms * TPM + ((qn | half) >> 4)];
-            const bool b = swap_bit(P0, Ph, half, rest);
+            const uint32_t m = sign_mask(spfx[ms * TPM + (qn >> 4)] - (rest << (31u - LH)));
             const T pr = dpp<kDppXor1>(rv[e]);
             const uint32_t pt = dpp<kDppXor1>(tv[e]);
-            rv[e] = sel(b, pr, rv[e]);
-            tv[e] = b ? pt : tv[e];
+            rv[e] = msel(m, pr, rv[e]);
+            tv[e] = msel(m, pt, tv[e]);
           }
         }
         // -- layout B, q bit LQ-5 (lane bit 1), for Z >= 1024
         if constexpr (LQ - 5 >= 6) {
-          const uint32_t half = 1u << (LQ - 5);
+          constexpr uint32_t LH = LQ - 5;
+          const uint32_t il = ((lb0 << (LQ - 6)) | rest) << (31u - LH);
 #pragma unroll
           for (uint32_t e = 0; e < 16; ++e) {
-            const bool b = swap_bit(pv[e], pvh[e], half, (lb0 << (LQ - 6)) | rest);
+            const uint32_t m = sign_mask(pvh[e] - il);
             const T pr = dpp<kDppXor2>(rv[e]);
             const uint32_t pt = dpp<kDppXor2>(tv[e]);
-            rv[e] = sel(b, pr, rv[e]);
-            tv[e] = b ? pt : tv[e];
+            rv[e] = msel(m, pr, rv[e]);
+            tv[e] = msel(m, pt, tv[e]);
           }
         }
         // -- layout B, q bits LQ-4 .. LQ-1: register pairs (those >= 6)
+        // the lane's part of the pair index, scaled for each of the four bits
+        const uint32_t ilB[4] = {lowB << (35u - LQ), lowB << (34u - LQ), lowB << (33u - LQ), lowB << (32u - LQ)};
+        light_begin();
 #pragma unroll
         for (uint32_t eb = 0; eb < 4; ++eb) {
           if (LQ - 4 + eb < 6) continue;
           const uint32_t hb = 1u << eb;
-          const uint32_t half = 1u << (LQ - 4 + eb);
+          const uint32_t il = ilB[eb];
 #pragma unroll
-          for (uint32_t e = 0; e < 16; ++e) {
-            if (e & hb) continue;
-            const uint32_t e2 = e | hb, es = e & ~(2u * hb - 1u);
-            const uint32_t i = ((e & (hb - 1u)) << (LQ - 4)) | lowB;
-            const bool b = swap_bit(pv[es], pv[es | hb], half, i);
-            const T r1 = rv[e], r2 = rv[e2];
-            const uint32_t t1 = tv[e], t2 = tv[e2];
-            rv[e] = sel(b, r2, r1);
-            rv[e2] = sel(b, r1, r2);
-            tv[e] = b ? t2 : t1;
-            tv[e2] = b ? t1 : t2;
+          for (uint32_t es = 0; es < 16; es += 2u * hb) {
+            const uint32_t q = pv[es | hb] - il;
+#pragma unroll
+            for (uint32_t i = 0; i < hb; ++i) {
+              const uint32_t m = sign_mask(q - (i << (31u - eb)));
+              mswap(m, rv[es + i], tv[es + i], rv[es + i + hb], tv[es + i + hb]);
+            }
           }
         }
+        light_end();
       }
       // -- hand the level's output to LDS (next level or last-pass finish)
       if (d + 1 < klev || LAST) {

@@ -100,19 +100,31 @@ __device__ __forceinline__ uint32_t tslot(uint32_t l, uint32_t e) {
   else return (e << 8) | l;
 }
 
+// Element and LDS view of the tile networks: 8-byte records as they are,
+// 16-byte ones as their two ordering words.
+template <int R> struct TileOf;
+template <> struct TileOf<8> {
+  using E = ElemR<uint2>;
+  using L = LdsR<uint2>;
+  using S = uint2;
+  static __device__ __forceinline__ E in(uint2 r) { return E{r}; }
+  static __device__ __forceinline__ uint2 out(const E& e) { return e.r; }
+};
+template <> struct TileOf<16> {
+  using E = FE1<16>;
+  using L = LdsF<16>;
+  using S = FRec<16>;
+  static __device__ __forceinline__ E in(uint4 r) { return E{f_load(r)}; }
+  static __device__ __forceinline__ uint4 out(const E& e) { return f_store(e.r); }
+};
+
 // Stages of phase KK (merges of 2^KK slots) on register bits JB .. 0 of
 // layout G (slot bits 4G + JB .. 4G); a pair sorts ascending when bit KK of
 // its slots is 0, and every pair does in the last phase.
 template <int KK, int G, int JB, typename E>
 __device__ __forceinline__ void tile_reg_stages(E (&v)[16], uint32_t l) {
   if constexpr (JB >= 0) {
-    constexpr uint32_t hb = 1u << JB;
-#pragma unroll
-    for (uint32_t e = 0; e < 16; ++e) {
-      if (e & hb) continue;
-      const bool asc = KK == 12 || ((tslot<G>(l, e) >> KK) & 1u) == 0u;
-      cx_reg(v[e], v[e | hb], asc);
-    }
+    cx_stage<(1u << JB)>(v, [&](uint32_t e) { return KK == 12 || ((tslot<G>(l, e) >> KK) & 1u) == 0u; });
     tile_reg_stages<KK, G, JB - 1>(v, l);
   }
 }
@@ -128,14 +140,14 @@ __device__ __forceinline__ uint32_t tpad_base(uint32_t l) {
 template <int G>
 constexpr uint32_t tpad_step() { return G == 0 ? 1u : G == 1 ? 17u : 272u; }
 
-template <int G, typename E, typename T>
-__device__ __forceinline__ void tile_to_lds(const E (&v)[16], const LdsR<T>& lds, uint32_t l) {
+template <int G, typename E, typename V>
+__device__ __forceinline__ void tile_to_lds(const E (&v)[16], const V& lds, uint32_t l) {
   const uint32_t b = tpad_base<G>(l);
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) lds.st(b + e * tpad_step<G>(), v[e]);
 }
-template <int G, typename E, typename T>
-__device__ __forceinline__ void tile_from_lds(E (&v)[16], const LdsR<T>& lds, uint32_t l) {
+template <int G, typename E, typename V>
+__device__ __forceinline__ void tile_from_lds(E (&v)[16], const V& lds, uint32_t l) {
   const uint32_t b = tpad_base<G>(l);
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) v[e] = lds.ld(b + e * tpad_step<G>());
@@ -144,8 +156,8 @@ __device__ __forceinline__ void tile_from_lds(E (&v)[16], const LdsR<T>& lds, ui
 // Phases KK .. 12 of the bitonic sort of a 4096-record tile; v holds layout P
 // on entry and exit.  A lane writes back exactly the slots it read in the same
 // layout, so only a change of layout needs a barrier.
-template <int KK, typename E, typename T>
-__device__ __forceinline__ void tile_phase(E (&v)[16], const LdsR<T>& lds, uint32_t l) {
+template <int KK, typename E, typename V>
+__device__ __forceinline__ void tile_phase(E (&v)[16], const V& lds, uint32_t l) {
   if constexpr (KK <= 12) {
     if constexpr (KK >= 5) {
       tile_to_lds<0>(v, lds, l);
@@ -175,11 +187,11 @@ template <int R, uint32_t TLOG>
 __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t tile, void* smp) {
   using T = typename RecOf<R>::T;
   extern __shared__ __align__(16) unsigned char smem[];
-  T* srec = reinterpret_cast<T*>(smem);
   T* B = static_cast<T*>(buf);
   const uint32_t lq = threadIdx.x;
-  ElemR<T> v[16];
-  LdsR<T> lds{srec};
+  __builtin_amdgcn_s_setprio(1);  // lowered inside the network's selects
+  typename TileOf<R>::E v[16];
+  typename TileOf<R>::L lds{reinterpret_cast<typename TileOf<R>::S*>(smem)};
   lds.tw = 1;
   if constexpr (TLOG == 12) {
     // Loads and stores in layout Q (register e of lane l is slot 256 e + l:
@@ -190,7 +202,7 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
     for (uint32_t e = 0; e < 16; ++e) {
       const uint64_t gi = t0 + (e << 8) + lq;
       if (gi < n) BOS_TR(1, 40, gi);
-      v[e] = ElemR<T>{gi < n ? B[gi] : max_rec<T>()};
+      v[e] = TileOf<R>::in(gi < n ? B[gi] : max_rec<T>());
     }
     tile_to_lds<2>(v, lds, lq);
     __syncthreads();
@@ -204,10 +216,10 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
       const uint64_t gi = t0 + (e << 8) + lq;
       if (gi < n) {
         BOS_TR(1, 40, gi);
-        B[gi] = v[e].r;
+        B[gi] = TileOf<R>::out(v[e]);
         if (smp && (gi & ((1ull << kSmpLog<R>) - 1)) == 0) {
           BOS_TR(1, 41, gi >> kSmpLog<R>);
-          static_cast<T*>(smp)[gi >> kSmpLog<R>] = v[e].r;
+          static_cast<T*>(smp)[gi >> kSmpLog<R>] = TileOf<R>::out(v[e]);
         }
       }
     }
@@ -217,16 +229,16 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
     if (base + e < n) BOS_TR(1, 40, base + e);
-    v[e] = ElemR<T>{base + e < n ? B[base + e] : max_rec<T>()};
+    v[e] = TileOf<R>::in(base + e < n ? B[base + e] : max_rec<T>());
   }
   bin_bitonic<TLOG>(v, lds, 0u, lq, true);
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e)
     if (base + e < n) {
       BOS_TR(1, 40, base + e);
-      B[base + e] = v[e].r;
+      B[base + e] = TileOf<R>::out(v[e]);
     }
-  write_sample<R>(smp, base, n, v[0].r);
+  write_sample<R>(smp, base, n, TileOf<R>::out(v[0]));
 }
 
 template <int R, uint32_t TLOG>
@@ -415,9 +427,9 @@ __device__ __forceinline__ void merge_tile_one(const void* src_, void* dst_, uin
 // reverse order when `mirror` (the first stage of a merge of two ascending
 // runs), else the same lane and registers.  The lower sub-tile keeps the
 // minima.  Sub-tiles exchange through their padded LDS regions (SP slots each).
-template <typename T, uint32_t SP>
-__device__ __forceinline__ void subtile_cross(ElemR<T> (&v)[16], T* s, uint32_t sub, uint32_t lq, uint32_t psub,
-                                              bool mirror) {
+template <int R, uint32_t SP>
+__device__ __forceinline__ void subtile_cross(typename TileOf<R>::E (&v)[16], typename TileOf<R>::S* s, uint32_t sub, uint32_t lq,
+                                              uint32_t psub, bool mirror) {
   __syncthreads();  // the LDS regions are free (the last network stage read them)
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) s[sub * SP + 17u * lq + e] = v[e].r;
@@ -426,9 +438,9 @@ __device__ __forceinline__ void subtile_cross(ElemR<T> (&v)[16], T* s, uint32_t 
   const bool keep_min = sub < psub;
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
-    const ElemR<T> p{s[psub * SP + 17u * plq + (mirror ? 15u - e : e)]};
+    const typename TileOf<R>::E p{s[psub * SP + 17u * plq + (mirror ? 15u - e : e)]};
     const bool take = e_less(p, v[e]) == keep_min;
-    v[e] = e_sel(take, p, v[e]);
+    v[e] = e_pick(take, p, v[e]);
   }
   __syncthreads();
 }
@@ -446,30 +458,45 @@ __device__ __forceinline__ void tile_sort_big_one(void* buf, uint64_t n, uint64_
   constexpr uint32_t kSub = 4096, kSubPad = kSub + kSub / 16;
   static_assert(TLOG == 13 || TLOG == 14, "two or four register tiles");
   extern __shared__ __align__(16) unsigned char smem[];
-  T* s = reinterpret_cast<T*>(smem);
+  typename TileOf<R>::S* s = reinterpret_cast<typename TileOf<R>::S*>(smem);
   T* B = static_cast<T*>(buf);
   const uint32_t tid = threadIdx.x, sub = tid / 256u, lq = tid % 256u;
-  const uint64_t base = (tile << TLOG) + uint64_t(sub) * kSub + 16u * lq;
-  const LdsR<T> lds{s};
-  ElemR<T> v[16];
+  __builtin_amdgcn_s_setprio(1);  // lowered inside the network's selects
+  const uint64_t t0 = (tile << TLOG) + uint64_t(sub) * kSub;
+  const typename TileOf<R>::L lds{s + sub * kSubPad};
+  typename TileOf<R>::E v[16];
+  // layout Q loads and stores, as the 4096-record tiles
 #pragma unroll
-  for (uint32_t e = 0; e < 16; ++e) v[e] = ElemR<T>{base + e < n ? B[base + e] : max_rec<T>()};
-  bin_bitonic<12>(v, lds, sub * kSubPad, lq, true);
-  auto cross = [&](uint32_t psub, bool mirror) { subtile_cross<T, kSubPad>(v, s, sub, lq, psub, mirror); };
+  for (uint32_t e = 0; e < 16; ++e) {
+    const uint64_t gi = t0 + (e << 8) + lq;
+    v[e] = TileOf<R>::in(gi < n ? B[gi] : max_rec<T>());
+  }
+  tile_to_lds<2>(v, lds, lq);
+  __syncthreads();
+  tile_from_lds<0>(v, lds, lq);
+  tile_phase<1>(v, lds, lq);
   // runs of 4096 -> 8192: sub-tiles 2j, 2j+1
-  cross(sub ^ 1u, true);
-  bin_bitonic_merge<12>(v, lds, sub * kSubPad, lq, true);
+  subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 1u, true);
+  tile_phase<12>(v, lds, lq);
   if constexpr (TLOG == 14) {
     // runs of 8192 -> 16384: mirror across the two runs, then the stage of
     // distance 4096 inside each run, then the stages inside every sub-tile
-    cross(3u - sub, true);
-    cross(sub ^ 1u, false);
-    bin_bitonic_merge<12>(v, lds, sub * kSubPad, lq, true);
+    subtile_cross<R, kSubPad>(v, s, sub, lq, 3u - sub, true);
+    subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 1u, false);
+    tile_phase<12>(v, lds, lq);
   }
+  __syncthreads();  // every lane's last reads of layout P are done
+  tile_to_lds<0>(v, lds, lq);
+  __syncthreads();
+  tile_from_lds<2>(v, lds, lq);
 #pragma unroll
-  for (uint32_t e = 0; e < 16; ++e)
-    if (base + e < n) B[base + e] = v[e].r;
-  write_sample<R>(smp, base, n, v[0].r);
+  for (uint32_t e = 0; e < 16; ++e) {
+    const uint64_t gi = t0 + (e << 8) + lq;
+    if (gi < n) {
+      B[gi] = TileOf<R>::out(v[e]);
+      if (smp && (gi & ((1ull << kSmpLog<R>) - 1)) == 0) static_cast<T*>(smp)[gi >> kSmpLog<R>] = TileOf<R>::out(v[e]);
+    }
+  }
 }
 
 template <int R, uint32_t TLOG>
@@ -1095,14 +1122,15 @@ __device__ __forceinline__ void bitonic_tile_one(const void* src_, void* dst_, u
   constexpr uint32_t kSub = 4096, kSubPad = kSub + kSub / 16, ts = 1u << TLOG;
   static_assert(TLOG >= 12 && TLOG <= 14, "one, two or four register sub-tiles");
   extern __shared__ __align__(16) unsigned char smem[];
-  T* s = reinterpret_cast<T*>(smem);
+  typename TileOf<R>::S* s = reinterpret_cast<typename TileOf<R>::S*>(smem);
   const T* S = static_cast<const T*>(src_);
   T* D = static_cast<T*>(dst_);
   const uint32_t tid = threadIdx.x, sub = tid / 256u, lq = tid % 256u;
   const uint64_t tbase = tile << TLOG;
   const uint32_t q0 = sub * kSub;  // the sub-tile's first slot
-  LdsR<T> lsub{s + sub * kSubPad};
-  ElemR<T> v[16];
+  __builtin_amdgcn_s_setprio(1);  // lowered inside the network's selects
+  typename TileOf<R>::L lsub{s + sub * kSubPad};
+  typename TileOf<R>::E v[16];
   // loads and stores in layout Q of the sub-tile (register e of lane l is its
   // slot 256 e + l: a wave reads and writes 64 consecutive records per
   // instruction); the networks are those of the comparison sort's tile sort
@@ -1110,7 +1138,7 @@ __device__ __forceinline__ void bitonic_tile_one(const void* src_, void* dst_, u
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
     const uint64_t g = tbase + q0 + (e << 8) + lq;
-    v[e] = ElemR<T>{MERGE || g < n_src ? S[g] : max_rec<T>()};
+    v[e] = TileOf<R>::in(MERGE || g < n_src ? S[g] : max_rec<T>());
   }
   if constexpr (!MERGE) {
     tile_to_lds<2>(v, lsub, lq);
@@ -1118,12 +1146,12 @@ __device__ __forceinline__ void bitonic_tile_one(const void* src_, void* dst_, u
     tile_from_lds<0>(v, lsub, lq);
     tile_phase<1>(v, lsub, lq);
     if constexpr (TLOG >= 13) {
-      subtile_cross<T, kSubPad>(v, s, sub, lq, sub ^ 1u, true);
+      subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 1u, true);
       tile_phase<12>(v, lsub, lq);
     }
     if constexpr (TLOG == 14) {
-      subtile_cross<T, kSubPad>(v, s, sub, lq, 3u - sub, true);
-      subtile_cross<T, kSubPad>(v, s, sub, lq, sub ^ 1u, false);
+      subtile_cross<R, kSubPad>(v, s, sub, lq, 3u - sub, true);
+      subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 1u, false);
       tile_phase<12>(v, lsub, lq);
     }
     __syncthreads();  // every lane's last reads of layout P are done
@@ -1134,8 +1162,8 @@ __device__ __forceinline__ void bitonic_tile_one(const void* src_, void* dst_, u
     // the cross-sub-tile strides pair the same (lane, register) of two
     // sub-tiles, in any layout; then phase 12 from layout Q: slot bits 11-8
     // in Q, 7-4 in R, 3-0 in P, and back to Q
-    if constexpr (TLOG == 14) subtile_cross<T, kSubPad>(v, s, sub, lq, sub ^ 2u, false);
-    if constexpr (TLOG >= 13) subtile_cross<T, kSubPad>(v, s, sub, lq, sub ^ 1u, false);
+    if constexpr (TLOG == 14) subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 2u, false);
+    if constexpr (TLOG >= 13) subtile_cross<R, kSubPad>(v, s, sub, lq, sub ^ 1u, false);
     tile_reg_stages<12, 2, 3>(v, lq);
     tile_to_lds<2>(v, lsub, lq);
     __syncthreads();
@@ -1155,7 +1183,7 @@ __device__ __forceinline__ void bitonic_tile_one(const void* src_, void* dst_, u
   for (uint32_t e = 0; e < 16; ++e) {
     const uint32_t p = q0 + (e << 8) + lq;
     const uint64_t o = tbase + (desc ? ts - 1u - p : p);
-    if (o < n_dst) D[o] = v[e].r;
+    if (o < n_dst) D[o] = TileOf<R>::out(v[e]);
   }
 }
 
