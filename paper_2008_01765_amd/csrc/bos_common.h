@@ -266,9 +266,16 @@ __host__ __device__ constexpr uint32_t lds_rec_bytes(int rec, uint32_t z, bool f
   return (z >= 64 && z <= 512 && !fused) ? uint32_t(rec) / 2u : uint32_t(rec);
 }
 
+// At Z = 512 (a MergeSplit is one wave) a wave needs kXWords words for its
+// layout changes (1024 slots and a pad word per 32) and for handing eight
+// slots of three words per lane to another wave.
+constexpr uint32_t kXWords = 1536;
+
 __host__ __device__ inline uint32_t pass_lds_bytes(int rec, uint32_t z, uint32_t klev, bool last_shuffle,
                                                    bool fused) {
   const uint32_t m = z << klev;
+  if (z == 512 && !fused && klev >= 1)
+    return ((m >> 10) * kXWords * 4u + (m >> 4) * 4u + (1u << klev) * 12u + 64u * 4u + 64u + 15u) & ~15u;
   const uint32_t mp = m + (m >> 4);
   uint32_t b = mp * lds_rec_bytes(rec, z, fused) + mp * 4u + (m >> 4) * 4u + (1u << klev) * 12u + 64u * 4u + 64u;
   if (last_shuffle) b += mp * 4u + mp * 2u;

@@ -16,11 +16,19 @@
 //     the 16 positions whose q bits LQ-4..LQ-1 vary (LQ = log2 2Z), so the
 //     remaining stages pair registers again.  Each level therefore moves the
 //     data through LDS twice: A -> B, and B -> next level's A (whose MergeSplits
-//     pair other buckets).
+//     pair other buckets).  At Z = 512 a MergeSplit is one wave: A -> B stays in
+//     the wave's own LDS words (no barrier), and between levels a wave keeps one
+//     of its buckets and hands the other to the wave it is paired with, half
+//     the traffic.
 //   * Blocks are persistent: a workgroup walks over several blocks of buckets,
-//     and several workgroups share a CU (three at 2^3 Z = 4096 slots of 8-byte
-//     records), so one workgroup's HBM loads overlap the others' networks.
-//     Barriers wait for LDS traffic only.
+//     and several workgroups share a CU, so one workgroup's HBM loads overlap
+//     the others' networks.  Barriers wait for LDS traffic only.
+//
+// What bounds a pass (n = 2^28 records of 8 bytes, Z = 512): HBM at k = 3 (2.94
+// ms for a middle pass, 4.4 TB/s of the 4.9 a copy reaches; 3.91 ms with the
+// compare-and-select networks of v_cmp and v_cndmask); at k = 4 the networks and
+// their LDS exchanges (3.46 ms, 3.8 before the wave-local exchanges), which
+// still makes the fewer passes the faster sort.
 //
 // Obliviousness: every HBM and LDS address is a function of (n, Z, klev,
 // level, block, lane, register) only; labels and records steer register
@@ -53,6 +61,14 @@ __device__ __forceinline__ void lds_barrier() {
 // wave's instructions in order.
 __device__ __forceinline__ void lds_wave_sync() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Keeps the compiler from moving this wave's LDS accesses across; the LDS
+// unit runs a wave's accesses in order, so its lanes need no wait between a
+// write and the read of another lane's word.
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
 
@@ -95,6 +111,21 @@ __device__ __forceinline__ uint32_t rec_lo(uint2 v) { return v.x; }
 __device__ __forceinline__ uint32_t rec_hi(uint2 v) { return v.y; }
 __device__ __forceinline__ void set_lo(uint2& v, uint32_t l) { v.x = l; }
 __device__ __forceinline__ void set_hi(uint2& v, uint32_t h) { v.y = h; }
+// 32-bit word w of a record.
+__device__ __forceinline__ uint32_t rec_word(const uint2& v, uint32_t w) { return w == 0 ? v.x : v.y; }
+__device__ __forceinline__ uint32_t rec_word(const uint4& v, uint32_t w) {
+  return w == 0 ? v.x : w == 1 ? v.y : w == 2 ? v.z : v.w;
+}
+__device__ __forceinline__ void set_word(uint2& v, uint32_t w, uint32_t x) {
+  if (w == 0) v.x = x;
+  else v.y = x;
+}
+__device__ __forceinline__ void set_word(uint4& v, uint32_t w, uint32_t x) {
+  if (w == 0) v.x = x;
+  else if (w == 1) v.y = x;
+  else if (w == 2) v.z = x;
+  else v.w = x;
+}
 template <typename T> struct HalfOf;
 template <> struct HalfOf<uint4> {
   using H = uint2;
@@ -137,18 +168,22 @@ __device__ __forceinline__ void light_end() {
   __builtin_amdgcn_s_setprio(1);
   __builtin_amdgcn_sched_barrier(0);
 }
-__device__ __forceinline__ uint32_t sign_mask(uint32_t d) {
-  uint32_t m;
-  // (in C the compiler folds the shift into v_bfe_i32 or v_cmp + v_cndmask)
-  asm("v_ashrrev_i32 %0, 31, %1" : "=v"(m) : "v"(d));
-  return m;
+// The shift amounts and the bit come from registers the compiler cannot see
+// through: with constants it folds these shifts into v_bfe_i32 or v_cmp and
+// v_cndmask.
+__device__ __forceinline__ uint32_t opaque31() {
+  uint32_t s;
+  asm("v_mov_b32 %0, 31" : "=v"(s));
+  return s;
 }
+__device__ __forceinline__ uint32_t opaque1() {
+  uint32_t s;
+  asm("v_mov_b32 %0, 1" : "=v"(s));
+  return s;
+}
+__device__ __forceinline__ uint32_t sign_mask(uint32_t d) { return uint32_t(int32_t(d) >> opaque31()); }
 // Mask of bit 0 of x.
-__device__ __forceinline__ uint32_t low_bit_mask(uint32_t x) {
-  uint32_t m;
-  asm("v_sub_u32 %0, 0, %1" : "=v"(m) : "v"(x & 1u));
-  return m;
-}
+__device__ __forceinline__ uint32_t low_bit_mask(uint32_t x) { return 0u - (x & opaque1()); }
 // Per bit: m ? a : b.
 __device__ __forceinline__ uint32_t msel(uint32_t m, uint32_t a, uint32_t b) {
   return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
@@ -841,18 +876,19 @@ __device__ __forceinline__ void compact_bin(typename RecOf<R>::T* srec, uint32_t
 // reals keep the order the last level left).
 // LOADED (FIN = 3): rv and tv already hold every bin's slots (layout P:
 // lane lq of bin S holds slots 16 lq .. 16 lq + 15); else they are read from
-// LDS.  rv and tv are scratch registers of the caller.
+// LDS.  rv and tv are scratch registers of the caller; S is the block's bin
+// that this lane's slots belong to.
 template <int R, int LZ, int FIN, bool FULL, bool LOADED>
 __device__ __forceinline__ void finish_split(const PassArgs& a, uint32_t blk, uint32_t klev,
                                              typename RecOf<R>::T* srec, uint32_t* stag, uint32_t* srhi,
                                              uint16_t* saux, const uint32_t* sload, uint32_t* spfx,
                                              uint32_t* swave, typename RecOf<R>::T (&rv)[16],
-                                             uint32_t (&tv)[16]) {
+                                             uint32_t (&tv)[16], uint32_t S) {
   using T = typename RecOf<R>::T;
   constexpr uint32_t Z = 1u << LZ, HL = Z >> 4;
   const uint32_t tid = threadIdx.x, NB = 1u << klev, m = Z << klev;
   const bool active = FULL || tid < (m >> 4);
-  const uint32_t S = active ? tid / HL : 0u, lq = active ? tid % HL : 0u;
+  const uint32_t lq = active ? tid % HL : 0u;
   if (tid == 0) {
     uint64_t agg = 0;
     for (uint32_t b = 0; b < NB; ++b) {
@@ -990,10 +1026,6 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   using T = typename RecOf<R>::T;
   constexpr bool FIRST = (MODE & 1) != 0, LAST = (MODE & 2) != 0, SPLIT = (MODE & 4) != 0;
   constexpr bool FULL = (MODE & 16) != 0;  // every lane holds slots: no lane guards
-  // a first pass whose groups all start on a multiple of 8 elements: built
-  // without the staged loads (and their registers)
-  constexpr bool ALIGNED = (MODE & 32) != 0;
-  static_assert(!ALIGNED || (FIRST && !LAST), "the aligned form is a first pass that is not also the last");
   static_assert(!SPLIT || (LAST && !FIRST), "the split form is a last pass that is not also the first");
   // the split form serves the sorts: it compacts its bins, and the strip puts
   // in order the bins that straddle a tile of the comparison sort's first
@@ -1010,12 +1042,18 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   constexpr bool HALF = lds_rec_bytes(R, Z, LAST && !SPLIT) < uint32_t(R);
   static_assert(!HALF || HAS_B, "two-half exchanges use layout B (Z >= 64)");
   using H = typename HalfOf<T>::H;
+  // Z = 512: a MergeSplit's lanes are one wave.  Only the change of buckets
+  // between levels crosses waves, and a wave keeps one of its two buckets
+  // there, so half of its slots move; layouts change word by word in the
+  // wave's own kXWords words, with no barrier.
+  constexpr bool WAVEX = HAS_B && TPM == 64 && (!LAST || SPLIT);
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t klev = a.klev, NB = 1u << klev, m = Z << klev, mp = NB * ZP;
   T* srec = reinterpret_cast<T*>(smem);
   H* shalf = reinterpret_cast<H*>(smem);  // HALF: one half record per slot
   uint32_t* stag = reinterpret_cast<uint32_t*>(smem + size_t(mp) * lds_rec_bytes(R, Z, LAST && !SPLIT));
-  uint32_t* spfx = stag + mp;          // m/16 marks-prefix entries (16-slot granularity)
+  // m/16 marks-prefix entries (16-slot granularity)
+  uint32_t* spfx = WAVEX ? reinterpret_cast<uint32_t*>(smem) + (m >> 10) * kXWords : stag + mp;
   uint32_t* sload = spfx + (m >> 4);   // NB bin loads (last pass)
   uint32_t* soff = sload + NB;         // 2*NB words: output offsets (last pass)
   uint32_t* swave = soff + 2 * NB;     // 64 scan words
@@ -1031,12 +1069,6 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   const uint32_t ms = active ? tid / TPM : 0u, lt = active ? tid % TPM : 0u;
   const T* RI = static_cast<const T*>(a.rec_in);
   const T* X = static_cast<const T*>(a.x_in);
-  // first pass: all groups start on a multiple of 8 elements (labels come from
-  // whole Philox blocks); otherwise inputs are staged through LDS
-  // (B = 2^L: divisions by B are shifts; a 64-bit division by a run-time
-  // value would be a long software sequence in every lane)
-  const bool aligned = ALIGNED || (n & ((8ull << L) - 1ull)) == 0;
-
   // ---- load one block into layout-A registers of level 0 -------------------
   // level 0 pairs LDS buckets 2ms and 2ms+1; lane lt holds slots 16*(lt mod
   // TPM/2) .. +15 of bucket 2ms + lt / (TPM/2).
@@ -1052,6 +1084,43 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       return (e >> 1) * (2u * HALF_LANES) + 2u * lh + (e & 1u);
     else
       return e * HALF_LANES + lh;
+  };
+  // first pass: elements 8c .. 8c + 7 that lie in [gs, ge), dummies elsewhere
+  // (tag 0 marks a real until label_block fills in its label)
+  auto load_block = [&](uint64_t c, uint64_t gs, uint64_t ge, T* dr, uint32_t* dt) {
+#pragma unroll
+    for (uint32_t i = 0; i < 8; i += 2) {
+      const uint64_t x = 8u * c + i;
+      const bool r0 = active && x >= gs && x < ge, r1 = active && x + 1 >= gs && x + 1 < ge;
+      if (r0) BOS_TR(0, 3, x);
+      if (r1) BOS_TR(0, 3, x + 1);
+      dr[i] = dr[i + 1] = zero_rec<T>();
+      if constexpr (R == 8) {
+        if (r0 && r1) {  // one 16-byte load (8-byte aligned: x_off may be odd)
+          typedef v4u __attribute__((aligned(8))) v4u8;
+          const v4u t = *reinterpret_cast<const v4u8*>(X + (x - a.x_off));
+          dr[i] = make_uint2(t.x, t.y);
+          dr[i + 1] = make_uint2(t.z, t.w);
+        } else {
+          if (r0) dr[i] = X[x - a.x_off];
+          if (r1) dr[i + 1] = X[x + 1 - a.x_off];
+        }
+      } else {
+        if (r0) dr[i] = X[x - a.x_off];
+        if (r1) dr[i + 1] = X[x + 1 - a.x_off];
+      }
+      dt[i] = r0 ? 0u : kDummyTag;
+      dt[i + 1] = r1 ? 0u : kDummyTag;
+    }
+  };
+  auto label_block = [&](uint64_t c, uint32_t* dt) {
+    const Philox4 ph = philox4x64_10(c, a.attempt, a.seed, 0);
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) {
+      const uint32_t w = uint32_t(ph.v[i >> 1] >> (32u * (i & 1u)));
+      // (a dummy's tag is all ones)
+      dt[i] |= L ? (w >> (32u - L)) : 0u;
+    }
   };
   auto issue_load = [&](uint32_t item, T* dr, uint32_t* dt) {
     const uint64_t r = uint64_t(item) & ((1ull << i0) - 1ull), h = uint64_t(item) >> i0;
@@ -1080,136 +1149,29 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         dt[e] = active ? a.tag_in[si + s] : kDummyTag;
       }
     } else {
-      // group j = h*NB + S_load holds X[floor(jn/B), floor((j+1)n/B))
+      // Group j = h*NB + S_load holds X[floor(jn/B), floor((j+1)n/B)), at most
+      // Z/2 elements.  Its slots take the network's positions in the order
+      // that labels best: registers 0..7 of the bucket's lane q hold the
+      // elements of the q-th Philox block of 8 that the group touches, and
+      // registers 8..15 those of block Z/16 + q (only a group of Z/2 elements
+      // that starts inside a block has one, in lane 0).  Other slots are
+      // dummies.
       const uint64_t j = h * NB + S_load;
-      const uint64_t gs = (j * n) >> L, gz = (((j + 1) * n) >> L) - gs;
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        const bool real = active && (sb_load + e) < gz;
-        if (real) BOS_TR(0, 3, gs + sb_load + e);
-        dr[e] = real ? X[gs + sb_load + e - a.x_off] : zero_rec<T>();
-        dt[e] = real ? 0u : kDummyTag;  // label filled in by finish_load
-      }
+      const uint64_t gs = (j * n) >> L, ge = ((j + 1) * n) >> L;
+      const uint64_t c = (gs >> 3) + lt % HALF_LANES;
+      load_block(c, gs, ge, dr, dt);
+      load_block(c + HALF_LANES, gs, ge, dr + 8, dt + 8);
     }
   };
   // first pass: labels of the loaded reals (word x mod 8 of Philox block x/8)
   auto finish_load = [&](uint32_t item, uint32_t* dt) {
-    constexpr uint32_t QH = HALF_LANES / 2;  // lanes of a bucket that can hold reals
-    if constexpr (FIRST && QH >= 1 && QH < 64) {
-      // A group has at most Z/2 elements, so its reals sit in the first QH
-      // lanes of the bucket (16 slots each, two Philox blocks).  Every lane
-      // computes one block: lane q labels the block (q / QH) of lane q mod QH,
-      // and lane q < QH takes its second block from lane q + QH.
+    if constexpr (FIRST) {
       const uint64_t h = uint64_t(item) >> i0;
       const uint64_t j = h * NB + S_load;
-      const uint64_t gs = (j * n) >> L;
-      const uint32_t q = lt % HALF_LANES;
-      const uint64_t xo = gs + 16u * (q % QH);  // first element of the owning lane, a multiple of 8
-      const Philox4 ph = philox4x64_10((xo >> 3) + q / QH, a.attempt, a.seed, 0);
-      uint32_t w[8], wp[8];
-#pragma unroll
-      for (uint32_t e = 0; e < 8; ++e) {
-        w[e] = uint32_t(ph.v[e >> 1] >> (32u * (e & 1u)));
-        wp[e] = uint32_t(__shfl_xor(int(w[e]), int(QH), 64));
-      }
-      if (active) {
-#pragma unroll
-        for (uint32_t e = 0; e < 8; ++e) {
-          if (dt[e] != kDummyTag) dt[e] = L ? (w[e] >> (32u - L)) : 0u;
-          if (dt[8 + e] != kDummyTag) dt[8 + e] = L ? (wp[e] >> (32u - L)) : 0u;
-        }
-      }
-    } else if constexpr (FIRST) {
-      const uint64_t h = uint64_t(item) >> i0;
-      const uint64_t j = h * NB + S_load;
-      const uint64_t gs = (j * n) >> L;
-      const uint64_t x0 = gs + sb_load;  // multiple of 8
-      if (active && dt[0] != kDummyTag) {
-        const Philox4 p0 = philox4x64_10(x0 >> 3, a.attempt, a.seed, 0);
-#pragma unroll
-        for (uint32_t e = 0; e < 8; ++e) {
-          const uint32_t word = uint32_t(p0.v[e >> 1] >> (32u * (e & 1u)));
-          if (dt[e] != kDummyTag) dt[e] = L ? (word >> (32u - L)) : 0u;
-        }
-      }
-      if (active && dt[8] != kDummyTag) {
-        const Philox4 p1 = philox4x64_10((x0 >> 3) + 1, a.attempt, a.seed, 0);
-#pragma unroll
-        for (uint32_t e = 0; e < 8; ++e) {
-          const uint32_t word = uint32_t(p1.v[e >> 1] >> (32u * (e & 1u)));
-          if (dt[8 + e] != kDummyTag) dt[8 + e] = L ? (word >> (32u - L)) : 0u;
-        }
-      }
-    }
-  };
-  // first pass, groups not aligned to 8: stage the block through LDS and read
-  // layout A back (the generic placement of Algorithm 3.1)
-  auto staged_first_load = [&](uint32_t item) {
-    const uint64_t h = uint64_t(item) >> i0;
-    const uint64_t j_lo = h * NB;
-    const uint64_t x_lo = (j_lo * n) >> L, x_hi = ((j_lo + NB) * n) >> L;
-    const uint64_t c_lo = x_lo >> 3, c_hi = (x_hi + 7) >> 3;
-    // HALF: round 0 stages the first halves and the tags, round 1 the second
-    // halves; otherwise one round stages whole records
-    for (uint32_t round = 0; round < (HALF ? 2u : 1u); ++round) {
-      for (uint32_t t = tid; t < mp; t += nthr) {
-        BOS_TR(0, 4, t);
-        if constexpr (HALF) {
-          shalf[t] = HalfOf<T>::zero();
-        } else {
-          srec[t] = zero_rec<T>();
-        }
-        if (round == 0) {
-          BOS_TR(0, 5, t);
-          stag[t] = kDummyTag;
-        }
-      }
-      lds_barrier();
-      for (uint64_t c = c_lo + tid; c < c_hi; c += nthr) {
-        const Philox4 ph = philox4x64_10(c, a.attempt, a.seed, 0);
-#pragma unroll
-        for (uint32_t w = 0; w < 8; ++w) {
-          const uint64_t x = c * 8 + w;
-          if (x < x_lo || x >= x_hi) continue;
-          const uint32_t word = uint32_t(ph.v[w >> 1] >> (32u * (w & 1u)));
-          const uint64_t j = ((x + 1) * B - 1) / n;
-          const uint64_t gs = (j * n) >> L;
-          const uint32_t S = uint32_t(j - j_lo), s = uint32_t(x - gs);
-          const uint32_t pi = S * ZP + s + (s >> 4);
-          BOS_TR(0, 3, x);
-          BOS_TR(0, 4, pi);
-          if constexpr (HALF) {
-            shalf[pi] = round == 0 ? rec_lo(X[x - a.x_off]) : rec_hi(X[x - a.x_off]);
-          } else {
-            srec[pi] = X[x - a.x_off];
-          }
-          if (round == 0) {
-            BOS_TR(0, 5, pi);
-            stag[pi] = L ? (word >> (32u - L)) : 0u;
-          }
-        }
-      }
-      lds_barrier();
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        const uint32_t s = sb_load + e;
-        const uint32_t pi = S_load * ZP + s + (s >> 4);
-        if (active) BOS_TR(0, 4, pi);
-        if constexpr (HALF) {
-          if (round == 0) {
-            if (active) BOS_TR(0, 5, pi);
-            set_lo(rv[e], active ? shalf[pi] : HalfOf<T>::zero());
-            tv[e] = active ? stag[pi] : kDummyTag;
-          } else {
-            set_hi(rv[e], active ? shalf[pi] : HalfOf<T>::zero());
-          }
-        } else {
-          if (active) BOS_TR(0, 5, pi);
-          rv[e] = active ? srec[pi] : zero_rec<T>();
-          tv[e] = active ? stag[pi] : kDummyTag;
-        }
-      }
-      lds_barrier();
+      const uint64_t gs = (j * n) >> L, ge = ((j + 1) * n) >> L;
+      const uint64_t c = (gs >> 3) + lt % HALF_LANES;
+      label_block(c, dt);
+      if (8u * (c + HALF_LANES) < ge) label_block(c + HALF_LANES, dt + 8);
     }
   };
 
@@ -1260,6 +1222,91 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       set_hi(rv[e], active ? shalf[dst(e)] : HalfOf<T>::zero());
     }
   };
+  // WAVEX: this wave's words; slot q of the MergeSplit is at word q + q/32, so
+  // that the 32 lanes of a half wave touch 32 different banks in layout A
+  // (slots 16 l + e) and in layout B (64 e + l).  (With q + q/16 one lane of
+  // layout B's half wave wrapped onto another's bank, which doubles the time of
+  // the whole access: 4.1 instead of 2.1 cycles per b32 read.)
+  uint32_t* xw = reinterpret_cast<uint32_t*>(smem) + (tid >> 6) * kXWords;
+  const uint32_t slot_a = 16u * lt + (lt >> 1), slot_b = lt + (lt >> 5);
+  auto wave_exchange = [&](auto src, auto dst) {
+#pragma unroll
+    for (uint32_t w = 0; w <= R / 4u; ++w) {
+#pragma unroll
+      for (uint32_t e = 0; e < 16; ++e) {
+        BOS_TR(0, 4, (tid >> 6) * kXWords + src(e));
+        xw[src(e)] = w < R / 4u ? rec_word(rv[e], w) : tv[e];
+      }
+      lds_order();
+#pragma unroll
+      for (uint32_t e = 0; e < 16; ++e) {
+        BOS_TR(0, 4, (tid >> 6) * kXWords + dst(e));
+        const uint32_t x = xw[dst(e)];
+        if (w < R / 4u) set_word(rv[e], w, x);
+        else tv[e] = x;
+      }
+      lds_order();
+    }
+  };
+  // WAVEX, after level d: this wave holds buckets S0 (registers 0..7, layout
+  // B) and S1 (8..15); level d + 1 pairs S0 with the S0, and S1 with the S1, of
+  // wave w ^ 2^d.  The wave whose bit d is clear keeps S0 and takes the other
+  // S0 for its S1, the other wave the reverse.  kXWords words hold three words
+  // of eight slots; 16-byte records take two rounds.
+  auto swap_buckets = [&](uint32_t d) {
+    const uint32_t w = uint32_t(__builtin_amdgcn_readfirstlane(int(tid >> 6)));
+    const bool keep1 = ((w >> d) & 1u) != 0u;
+    const uint32_t pw = w ^ (1u << d);
+    const uint32_t* px = reinterpret_cast<const uint32_t*>(smem) + pw * kXWords;
+    auto put = [&](uint32_t e0, uint32_t w0, uint32_t w1) {
+#pragma unroll
+      for (uint32_t q = w0; q < w1; ++q)
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e) {
+          BOS_TR(0, 4, w * kXWords + ((q - w0) * 8u + e) * 64u + lt);
+          xw[((q - w0) * 8u + e) * 64u + lt] = q < R / 4u ? rec_word(rv[e0 + e], q) : tv[e0 + e];
+        }
+    };
+    auto get = [&](uint32_t e0, uint32_t w0, uint32_t w1) {
+#pragma unroll
+      for (uint32_t q = w0; q < w1; ++q)
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e) {
+          BOS_TR(0, 4, pw * kXWords + ((q - w0) * 8u + e) * 64u + lt);
+          const uint32_t x = px[((q - w0) * 8u + e) * 64u + lt];
+          if (q < R / 4u) set_word(rv[e0 + e], q, x);
+          else tv[e0 + e] = x;
+        }
+    };
+    constexpr uint32_t W = R / 4u + 1u;  // words per slot with the tag
+#pragma unroll
+    for (uint32_t w0 = 0; w0 < W; w0 += 3u) {
+      const uint32_t w1 = w0 + 3u < W ? w0 + 3u : W;
+      if (w0 > 0) {  // the first round is read
+        lds_barrier();
+        lds_order();
+      }
+      // (the empty asm statements keep the two sides of these wave-uniform
+      // branches apart: merged, every word would go through a v_cndmask)
+      if (keep1) {
+        put(0, w0, w1);
+        asm volatile("; keep S1" ::: "memory");
+      } else {
+        put(8, w0, w1);
+        asm volatile("; keep S0" ::: "memory");
+      }
+      lds_order();
+      lds_barrier();
+      lds_order();
+      if (keep1) {
+        asm volatile("; keep S1" ::: "memory");
+        get(0, w0, w1);
+      } else {
+        asm volatile("; keep S0" ::: "memory");
+        get(8, w0, w1);
+      }
+    }
+  };
   // where the previous level left this lane's slots (layout B), for HALF
   uint32_t pb0 = 0, pb1 = 0, pbB0 = 0, pbB1 = 0, plB = 0;
 
@@ -1272,7 +1319,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       // layout A: this lane's 16 slots are bucket (lt < TPM/2 ? S0 : S1),
       // slots 16*(lt mod TPM/2) + e
       const uint32_t baseA = (lt < HALF_LANES ? base0 : base1) + 17u * (lt % HALF_LANES);
-      if (d > 0) {
+      if (d > 0 && !WAVEX) {
         if constexpr (HALF) {
           half_finish([&](uint32_t e) { return b_index(e, pb0, pb1, pbB0, pbB1, plB); },
                       [&](uint32_t e) { return baseA + e; }, [] { lds_barrier(); });
@@ -1365,7 +1412,11 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       uint32_t baseB0 = 0, baseB1 = 0, lowB = 0;
       if constexpr (HAS_B) {
         // A -> LDS (HALF: the first halves)
-        if (active) {
+        if constexpr (WAVEX) {
+          lowB = lt;
+          // other waves have read what this one handed them after the last level
+          if (d > 0) lds_barrier();
+        } else if (active) {
 #pragma unroll
           for (uint32_t e = 0; e < 16; ++e) {
             BOS_TR(0, 4, baseA + e);
@@ -1377,7 +1428,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
             stag[baseA + e] = tv[e];
           }
         }
-        lds_group_sync<TPM>();  // layouts A and B of one MergeSplit share its lanes
+        if constexpr (!WAVEX) lds_group_sync<TPM>();  // layouts A and B of one MergeSplit share its lanes
         // Layout B pairs lanes through DPP only for Z >= 1024; below that the
         // lanes simply take consecutive slots (conflict-free LDS access).
         const uint32_t lb0 = lt & 1u, lb1 = (lt >> 1) & 1u, rest = lt >> 2;
@@ -1385,7 +1436,9 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         baseB0 = base0 + lowB + (lowB >> 4);
         baseB1 = base1 + lowB + (lowB >> 4);
         // HALF: the exchange first (its registers are free before the prefixes load)
-        if constexpr (HALF) {
+        if constexpr (WAVEX) {
+          wave_exchange([&](uint32_t e) { return slot_a + e; }, [&](uint32_t e) { return slot_b + 66u * e; });
+        } else if constexpr (HALF) {
           half_finish([&](uint32_t e) { return baseA + e; },
                       [&](uint32_t e) { return b_index(e, base0, base1, baseB0, baseB1, lowB); },
                       [] { lds_group_sync<TPM>(); });
@@ -1471,7 +1524,9 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         light_end();
       }
       // -- hand the level's output to LDS (next level or last-pass finish)
-      if (d + 1 < klev || LAST) {
+      if (WAVEX && (d + 1 < klev || LAST)) {
+        if (d + 1 < klev) swap_buckets(d);
+      } else if (d + 1 < klev || LAST) {
         if constexpr (HAS_B) {
           // every lane rewrites exactly the layout-B slots it read: no
           // barrier (HALF: the first halves; the next level's start, or the
@@ -1535,26 +1590,29 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   // split last pass: every bin's slots in layout P, then compaction and
   // the write of its reals
   auto finish_bins_split = [&](uint32_t blk) {
-    if constexpr (HALF) {
+    if constexpr (WAVEX) {
+      // layout A of the last level's MergeSplit is layout P of its two bins
+      wave_exchange([&](uint32_t e) { return slot_b + 66u * e; }, [&](uint32_t e) { return slot_a + e; });
+      lds_barrier();  // every bin's load is in sload, every prefix has been read
+      const uint32_t S = (tid >> 6) + (lt < HALF_LANES ? 0u : NB / 2u);
+      finish_split<R, LZ, SPLIT_FIN, FULL, true>(a, blk, klev, srec, stag, srhi, saux, sload, spfx, swave, rv, tv, S);
+    } else if constexpr (HALF) {
       const uint32_t HLn = Z >> 4;
       const uint32_t S = active ? tid / HLn : 0u, lq = active ? tid % HLn : 0u;
       const uint32_t pbase = S * ZP + 17u * lq;
       half_finish([&](uint32_t e) { return b_index(e, pb0, pb1, pbB0, pbB1, plB); },
                   [&](uint32_t e) { return pbase + e; }, [] { lds_barrier(); });
-      finish_split<R, LZ, SPLIT_FIN, FULL, true>(a, blk, klev, srec, stag, srhi, saux, sload, spfx, swave, rv, tv);
+      finish_split<R, LZ, SPLIT_FIN, FULL, true>(a, blk, klev, srec, stag, srhi, saux, sload, spfx, swave, rv, tv, S);
     } else {
-      finish_split<R, LZ, SPLIT_FIN, FULL, false>(a, blk, klev, srec, stag, srhi, saux, sload, spfx, swave, rv, tv);
+      finish_split<R, LZ, SPLIT_FIN, FULL, false>(a, blk, klev, srec, stag, srhi, saux, sload, spfx, swave, rv, tv,
+                                                  active ? tid / (Z >> 4) : 0u);
     }
   };
 
   if constexpr (BATCH && (!LAST || SPLIT)) {
     item0 += a.item_off;
-    if (FIRST && !aligned) {
-      staged_first_load(item0);
-    } else {
-      issue_load(item0, rv, tv);
-      finish_load(item0, tv);
-    }
+    issue_load(item0, rv, tv);
+    finish_load(item0, tv);
     process(item0);
     if constexpr (SPLIT) finish_bins_split(item0);
   } else if constexpr (!LAST || SPLIT) {
@@ -1568,12 +1626,8 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
     const uint32_t ioff = a.item_off, iend = ioff + nitems;
     uint32_t item = item0 + ioff;
     if (item >= iend) return;
-    if (FIRST && !aligned) {
-      staged_first_load(item);
-    } else {
-      issue_load(item, rv, tv);
-      finish_load(item, tv);
-    }
+    issue_load(item, rv, tv);
+    finish_load(item, tv);
     for (;;) {
       const uint32_t next = item + gridDim.x;
       const bool has_next = next < iend;
@@ -1582,12 +1636,8 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       if (!has_next) break;
       item = next;
       lds_barrier();  // LDS of the previous block is no longer read
-      if (FIRST && !aligned) {
-        staged_first_load(item);
-      } else {
-        issue_load(item, rv, tv);
-        finish_load(item, tv);
-      }
+      issue_load(item, rv, tv);
+      finish_load(item, tv);
     }
   } else {
     // Last pass: one block per launch block; the block index is a ticket so
@@ -1596,12 +1646,8 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
     if (tid == 0) smisc[0] = atomicAdd(a.ticket, 1u);
     lds_barrier();
     const uint32_t blk = smisc[0];
-    if (FIRST && !aligned) {
-      staged_first_load(blk);
-    } else {
-      issue_load(blk, rv, tv);
-      finish_load(blk, tv);
-    }
+    issue_load(blk, rv, tv);
+    finish_load(blk, tv);
     process(blk);
     // every final bin (LDS bucket S) now sits in LDS with padded slots
     finish_bins<R, LZ, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, soff);
@@ -1614,19 +1660,20 @@ __global__ __launch_bounds__(kMaxThreads) void route_kernel(PassArgs a, uint32_t
   route_run<R, LZ, MODE, false>(a, nitems, blockIdx.x);
 }
 
-// The passes after the first whose LDS exchanges go in two halves (kW3
-// below) are compiled for a register budget that lets as many workgroups
-// share a CU as their LDS allows: three waves per SIMD (at most 168 VGPRs)
-// for 16-byte records, four (at most 128) for 8-byte ones.  The first pass,
-// which also computes the labels, keeps the default allocation (it would
-// spill).
+// The passes whose LDS exchanges go in two halves (64 <= Z < 512, passes after
+// the first) or wave by wave (Z = 512) are compiled for a register budget that
+// lets as many workgroups share a CU as their LDS allows: 8-byte records four
+// waves per SIMD (at most 128 VGPRs), 16-byte ones two (at three, 168 VGPRs,
+// the Z = 512 passes spill 36 registers and take 0.355 ms instead of 0.303 at
+// n = 2^24, k = 3; two waves also pair up for light instructions).
 template <int R, int LZ, int MODE>
-constexpr bool kW3 = lds_rec_bytes(R, 1u << LZ, (MODE & 2) && !(MODE & 4)) < uint32_t(R) && LZ >= 6 && !(MODE & 1);
-template <int R>
-constexpr int kWavesPerSimd = R == 16 ? 3 : 4;
+constexpr bool kW3 = lds_rec_bytes(R, 1u << LZ, (MODE & 2) && !(MODE & 4)) < uint32_t(R) && LZ >= 6 &&
+                     (LZ == 9 || !(MODE & 1));
+template <int R, int LZ>
+constexpr int kWavesPerSimd = R == 8 ? 4 : LZ == 9 ? 2 : 3;
 
 template <int R, int LZ, int MODE>
-__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<R>, 8))) void
+__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<R, LZ>, 8))) void
 route_kernel_w3(PassArgs a, uint32_t nitems) {
   route_run<R, LZ, MODE, false>(a, nitems, blockIdx.x);
 }
@@ -1652,7 +1699,7 @@ __global__ __launch_bounds__(kMaxThreads) void route_kernel_b(const PassArgs* se
   route_b_body<R, LZ, MODE, false>(segs, blk_start, nsegs);
 }
 template <int R, int LZ, int MODE>
-__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<R>, 8))) void
+__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<R, LZ>, 8))) void
 route_kernel_b_w3(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs) {
   route_b_body<R, LZ, MODE, true>(segs, blk_start, nsegs);
 }
