@@ -65,7 +65,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_blocks_kernel(unsigned long
 // First level of the block-count scan: workgroup c turns v[c*1024 ..
 // c*1024 + 1023] into its exclusive scan in place (coalesced, one count per
 // thread) and writes the chunk's total to tot[c]; a second, one-workgroup
-// scan of tot gives every chunk's offset.
+// scan of tot gives every chunk's offset.  One chunk (at most 1024 blocks) has
+// offset 0 and writes it itself: no second launch (4.6 us of a small sort).
 __global__ __launch_bounds__(kScanThreads) void scan_chunks_kernel(unsigned long long* v, uint32_t count,
                                                                    unsigned long long* tot) {
   __shared__ unsigned long long wsum[kScanThreads / 64];
@@ -98,12 +99,15 @@ __global__ __launch_bounds__(kScanThreads) void scan_chunks_kernel(unsigned long
   }
   if (tid == 0) {
     BOS_TR(0, 32, blockIdx.x);
-    tot[blockIdx.x] = total;
+    tot[blockIdx.x] = gridDim.x == 1 ? 0ull : total;
   }
 }
 
 // Bitonic sort of sb[0..P2) by (key, payload) (P2 a power of two), by the
-// whole workgroup.
+// whole workgroup.  A wave's 64 pairs of a stage of stride <= 64 lie in 128
+// slots that only this wave touches, whatever the stride, so such stages follow
+// each other without a barrier (the LDS unit runs a wave's accesses in order);
+// only strides above 64 need one on either side.
 template <typename T>
 __device__ __forceinline__ void lds_bitonic(T* sb, uint32_t P2) {
   for (uint32_t size = 2; size <= P2; size <<= 1) {
@@ -118,9 +122,17 @@ __device__ __forceinline__ void lds_bitonic(T* sb, uint32_t P2) {
         sb[i] = sel(swap, y, x);
         sb[k] = sel(swap, x, y);
       }
-      __syncthreads();
+      // the next stage's stride: half of this one, or the next size's first
+      const uint32_t next = stride > 1 ? stride >> 1 : size;
+      if (stride > 64 || next > 64) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
     }
   }
+  __syncthreads();
 }
 
 // One routing block's bins (NB = 2^klev of them) to out[boff[blk] + coff[blk /
@@ -137,44 +149,56 @@ __device__ __forceinline__ void strip_block(const void* binned_, const uint32_t*
   using T = typename RecOf<R>::T;
   __shared__ uint32_t pre[513];  // NB <= 512: a block has at most 8192 slots, Z >= 16
   __shared__ uint16_t strad[512];
+  __shared__ uint8_t sorted[512];  // bin straddles a tile: written sorted
   __shared__ uint32_t nstrad;
   __shared__ __align__(16) unsigned char sbin_raw[2048 * R];  // one bin of at most Z <= 2048 reals
   const T* binned = static_cast<const T*>(binned_);
   T* out = static_cast<T*>(out_);
   const uint32_t tid = threadIdx.x, NB = 1u << klev;
   const uint64_t bin0 = blk << klev;
-  for (uint32_t j = tid; j < NB; j += kStripThreads) {
-    BOS_TR(0, 34, bin0 + j);
-    BOS_TR(0, 35, j + 1);
-    pre[j + 1] = loads[bin0 + j];
-  }
-  __syncthreads();
-  if (tid == 0) {
-    pre[0] = 0;
-    for (uint32_t j = 1; j <= NB; ++j) BOS_TR(0, 35, j);
-    for (uint32_t j = 1; j <= NB; ++j) pre[j] += pre[j - 1];
-    nstrad = 0;
+  BOS_TR(0, 36, blk);
+  const uint64_t base = boff[blk] + (coff ? coff[blk / kScanThreads] : 0ull);
+  // wave 0, 64 bins at a time: prefix sums of the loads and the list, in bin
+  // order, of the bins that straddle a tile (tile is a power of two)
+  if (tid < 64) {
+    const uint32_t tl = tile ? uint32_t(__builtin_ctz(tile)) : 0u;
+    uint32_t run = 0, ns = 0;
+    for (uint32_t j0 = 0; j0 < NB; j0 += 64) {
+      const uint32_t j = j0 + tid;
+      if (j < NB) BOS_TR(0, 34, bin0 + j);
+      const uint32_t ld = j < NB ? loads[bin0 + j] : 0u;
+      uint32_t incl = ld;
+#pragma unroll
+      for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (tid >= o) incl += y;
+      }
+      const uint64_t b1 = base + run + incl, b0 = b1 - ld;
+      const bool st = tile && ld >= 2 && (b0 >> tl) != ((b1 - 1) >> tl);
+      const unsigned long long m = __ballot(st);
+      if (j < NB) {
+        BOS_TR(0, 35, j);
+        pre[j] = run + incl - ld;
+        sorted[j] = st;
+        if (st) {
+          const uint32_t c = ns + uint32_t(__popcll(m & ((1ull << tid) - 1ull)));
+          BOS_TR(0, 37, c);
+          strad[c] = uint16_t(j);
+        }
+      }
+      run += uint32_t(__shfl(int(incl), 63, 64));
+      ns += uint32_t(__popcll(m));
+    }
+    if (tid == 0) {
+      BOS_TR(0, 35, NB);
+      pre[NB] = run;
+      nstrad = ns;
+    }
   }
   __syncthreads();
   BOS_TR(0, 35, NB);
   const uint32_t total = pre[NB];
-  BOS_TR(0, 36, blk);
-  const uint64_t base = boff[blk] + (coff ? coff[blk / kScanThreads] : 0ull);
   if (tile) {
-    // the straddling bins, in bin order (tile is a power of two)
-    if (tid == 0) {
-      const uint32_t tl = uint32_t(__builtin_ctz(tile));
-      uint32_t c = 0;
-      for (uint32_t j = 0; j < NB; ++j) {
-        const uint64_t b0 = base + pre[j], b1 = base + pre[j + 1];
-        if (b1 - b0 >= 2 && (b0 >> tl) != ((b1 - 1) >> tl)) {
-          BOS_TR(0, 37, c);
-          strad[c++] = uint16_t(j);
-        }
-      }
-      nstrad = c;
-    }
-    __syncthreads();
     T* sb = reinterpret_cast<T*>(sbin_raw);
     const uint32_t ns = nstrad;
     for (uint32_t k = 0; k < ns; ++k) {
@@ -199,7 +223,6 @@ __device__ __forceinline__ void strip_block(const void* binned_, const uint32_t*
       __syncthreads();
     }
   }
-  const uint32_t ns = tile ? nstrad : 0u;
   using V = typename NativeOf<T>::V;  // native vectors stay in registers
   const V* bv = reinterpret_cast<const V*>(binned);
   V* ov = reinterpret_cast<V*>(out);
@@ -222,11 +245,8 @@ __device__ __forceinline__ void strip_block(const void* binned_, const uint32_t*
           hi = mid;
       }
       // a straddling bin was written sorted above
-      bool done = false;
-      for (uint32_t m = 0; m < ns; ++m) {
-        BOS_TR(0, 37, m);
-        done |= strad[m] == lo;
-      }
+      BOS_TR(0, 37, lo);
+      const bool done = sorted[lo] != 0;
       BOS_TR(0, 35, lo);
       BOS_TR(0, 38, ((bin0 + lo) << lz) + (qq - pre[lo]));
       v[k] = bv[((bin0 + lo) << lz) + (qq - pre[lo]) - bin_slot0];
@@ -305,7 +325,7 @@ hipError_t launch_block_scan(unsigned long long* bsum, unsigned long long* coff,
   const uint32_t nchunks = (nblocks + kScanThreads - 1) / kScanThreads;
   hipLaunchKernelGGL(scan_chunks_kernel, dim3(nchunks), dim3(kScanThreads), 0, s, bsum, nblocks, coff);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || nchunks == 1) return e;
   hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(kScanThreads), 0, s, coff, nchunks);
   return hipGetLastError();
 }
@@ -318,12 +338,7 @@ hipError_t launch_strip(int rec, const void* binned, const uint32_t* loads, unsi
                         uint32_t tile, hipStream_t s) {
   BOS_TRACE_BIND();
   if (klev > 9 || lz > 11 || nblocks == 0 || (tile & (tile - 1u)) || !coff) return hipErrorInvalidValue;
-  const uint32_t nchunks = (nblocks + kScanThreads - 1) / kScanThreads;
-  hipLaunchKernelGGL(scan_chunks_kernel, dim3(nchunks), dim3(kScanThreads), 0, s, bsum, nblocks, coff);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(kScanThreads), 0, s, coff, nchunks);
-  e = hipGetLastError();
+  const hipError_t e = launch_block_scan(bsum, coff, nblocks, s);
   if (e != hipSuccess) return e;
   if (rec == 8)
     hipLaunchKernelGGL(strip_kernel<8>, dim3(nblocks), dim3(kStripThreads), 0, s, binned, loads, bsum, coff, out, n,
