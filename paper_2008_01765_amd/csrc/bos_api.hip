@@ -26,6 +26,8 @@
 
 namespace bos {
 hipError_t launch_fill_u64(unsigned long long* p, uint64_t count, unsigned long long v, hipStream_t s);
+hipError_t launch_attempt_init(unsigned long long* status, uint64_t count, unsigned long long* err, hipStream_t s);
+hipError_t launch_outcome(unsigned long long* status, const unsigned long long* err, hipStream_t s);
 hipError_t launch_labels(uint32_t* out, uint64_t n, uint32_t L, uint64_t seed, uint32_t attempt, hipStream_t s);
 hipError_t launch_pass(int rec, const PassArgs& a, bool first, bool last, uint32_t nblocks, hipStream_t s);
 hipError_t launch_route(int rec, const PassArgs& a, bool first, bool last, uint32_t nitems, uint32_t grid,
@@ -35,7 +37,7 @@ hipError_t launch_strip(int rec, const void* binned, const uint32_t* loads, unsi
                         uint32_t tile, hipStream_t s);
 constexpr uint32_t kScanChunk = 1024;  // block counts per workgroup of the strip's first scan
 hipError_t launch_comparison_sort(int rec, void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                  hipStream_t s, void** result, bool multiway);
+                                  hipStream_t s, void** result, bool multiway, bool err_clear = false);
 uint32_t comparison_sort_hbm_passes(int rec, uint64_t n, uint32_t ts, bool multiway);
 size_t comparison_sort_split_bytes(uint64_t n, int rec);
 unsigned long long* comparison_sort_err_word(uint64_t* split, uint64_t n, int rec);
@@ -443,11 +445,9 @@ StripSeg strip_seg(const Plan& pl, char* ws, void* out, uint32_t first) {
 // slot array (P + 1) & 1, which holds the bins until the strip).
 hipError_t enqueue_routing(const Plan& pl, const void* in, void* out, uint64_t seed, uint32_t attempt,
                            uint32_t fin, char* ws, hipStream_t s, int stop_after = -1, bool split = false,
-                           uint32_t flags = 0) {
+                           uint32_t flags = 0, unsigned long long* err = nullptr) {
   unsigned long long* status = reinterpret_cast<unsigned long long*>(ws + pl.off_status);
-  hipError_t e = launch_fill_u64(status, 2 + pl.nblocks_last, 0, s);
-  if (e != hipSuccess) return e;
-  e = launch_fill_u64(status, 1, kNoOverflow, s);
+  hipError_t e = launch_attempt_init(status, 2 + pl.nblocks_last, err, s);
   if (e != hipSuccess) return e;
   for (uint32_t t = 0; t < pl.P; ++t) {
     if (stop_after >= 0 && int(t) > stop_after) break;
@@ -1159,31 +1159,47 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
   void* tmp = sort_tmp(pl, w);
   void* start = (passes % 2 == 0) ? out : tmp;
   void* other = (passes % 2 == 0) ? tmp : out;
-  uint32_t attempts = 0;
+  // With BOS_SYNC: attempts q.attempt .. max_retries (at least one), each with
+  // its comparison sort enqueued behind it; the overflow word and the
+  // comparison sort's error word are then read together, so a sort waits for
+  // the device once (waiting for the overflow word before the comparison sort
+  // left the device idle for 45 us of every sort).  An overflowed attempt
+  // leaves some of `start` unwritten: the comparison sort orders whatever is
+  // there, in bounds, and the next attempt starts over.  Without BOS_SYNC:
+  // q.attempt alone, its words left on the device.
+  unsigned long long* status = reinterpret_cast<unsigned long long*>(w + pl.off_status);
+  uint64_t* csplit = reinterpret_cast<uint64_t*>(w + pl.off_split);
+  unsigned long long* err = comparison_sort_err_word(csplit, n, pl.rec);
+  const bool sync = (q.flags & BOS_SYNC) != 0;
+  const uint32_t last = sync ? std::max(q.max_retries, q.attempt) : q.attempt;
   uint64_t ovf = kNoOverflow;
-  st = run_routing(pl, q, in, start, 1, w, s, &attempts, &ovf, q.attempt, kNoOverflow, split);
-  if (st != BOS_OK) {
-    fill_report(rep, pl, attempts, ovf, 0);
-    return st;
-  }
-  void* result = nullptr;
-  hipError_t e = launch_comparison_sort(pl.rec, start, other, n, pl.tile,
-                                        reinterpret_cast<uint64_t*>(w + pl.off_split), s, &result, true);
-  if (e != hipSuccess) return BOS_ERR_HIP;
-  if (result != out) {
-    e = hipMemcpyAsync(out, result, n * pl.rec, hipMemcpyDeviceToDevice, s);
+  for (uint32_t att = q.attempt; att <= last; ++att) {
+    hipError_t e = enqueue_routing(pl, in, start, q.seed, att, 1, w, s, -1, split, q.flags, err);
     if (e != hipSuccess) return BOS_ERR_HIP;
+    void* result = nullptr;
+    e = launch_comparison_sort(pl.rec, start, other, n, pl.tile, csplit, s, &result, true, true);
+    if (e != hipSuccess) return BOS_ERR_HIP;
+    if (result != out) {
+      e = hipMemcpyAsync(out, result, n * pl.rec, hipMemcpyDeviceToDevice, s);
+      if (e != hipSuccess) return BOS_ERR_HIP;
+    }
+    if (sync) {
+      uint64_t words[2] = {0, 0};
+      if (launch_outcome(status, err, s) != hipSuccess ||
+          hipMemcpyAsync(words, status, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
+          hipStreamSynchronize(s) != hipSuccess)
+        return BOS_ERR_HIP;
+      if (words[0] != kNoOverflow) {
+        ovf = words[0];
+        continue;
+      }
+      if (words[1]) return BOS_ERR_INTERNAL;
+    }
+    fill_report(rep, pl, att + 1, ovf, uint64_t(2 + 2 * passes) * n * pl.rec);
+    return BOS_OK;
   }
-  if (q.flags & BOS_SYNC) {
-    unsigned long long err = 0;
-    if (hipMemcpyAsync(&err, comparison_sort_err_word(reinterpret_cast<uint64_t*>(w + pl.off_split), n, pl.rec), 8,
-                       hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return BOS_ERR_HIP;
-    if (err) return BOS_ERR_INTERNAL;
-  }
-  fill_report(rep, pl, attempts, ovf, uint64_t(2 + 2 * passes) * n * pl.rec);
-  return BOS_OK;
+  fill_report(rep, pl, last + 1, ovf, 0);
+  return BOS_ERR_OVERFLOW;
 }
 
 // ---- workspace held by the library, for callers that cannot allocate ------

@@ -428,6 +428,31 @@ hipError_t launch_fill_u64(unsigned long long* p, uint64_t count, unsigned long 
   return hipGetLastError();
 }
 
+// Start of an attempt: the status word says no overflow, the ticket and the
+// block words behind it (count words in all) and the comparison sort's error
+// word (null: none) are zero.
+__global__ void attempt_init_kernel(unsigned long long* status, uint64_t count, unsigned long long* err) {
+  const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const uint64_t step = uint64_t(gridDim.x) * blockDim.x;
+  for (uint64_t t = i; t < count; t += step) status[t] = t == 0 ? kNoOverflow : 0ull;
+  if (i == 0 && err) *err = 0ull;
+}
+hipError_t launch_attempt_init(unsigned long long* status, uint64_t count, unsigned long long* err, hipStream_t s) {
+  const uint32_t threads = 256;
+  uint64_t blocks = (count + threads - 1) / threads;
+  if (blocks > 1024) blocks = 1024;
+  hipLaunchKernelGGL(attempt_init_kernel, dim3(uint32_t(blocks)), dim3(threads), 0, s, status, count, err);
+  return hipGetLastError();
+}
+
+// End of a sort: the comparison sort's error word next to the overflow word
+// (in the ticket's place), so that one copy reads both.
+__global__ void outcome_kernel(unsigned long long* status, const unsigned long long* err) { status[1] = *err; }
+hipError_t launch_outcome(unsigned long long* status, const unsigned long long* err, hipStream_t s) {
+  hipLaunchKernelGGL(outcome_kernel, dim3(1), dim3(1), 0, s, status, err);
+  return hipGetLastError();
+}
+
 hipError_t launch_labels(uint32_t* out, uint64_t n, uint32_t L, uint64_t seed, uint32_t attempt,
                          hipStream_t s) {
   if (n == 0) return hipSuccess;

@@ -1313,7 +1313,7 @@ unsigned long long* comparison_sort_err_word(uint64_t* split, uint64_t n, int re
 
 template <int R>
 static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                    hipStream_t s, void** result, bool multiway) {
+                                    hipStream_t s, void** result, bool multiway, bool err_clear) {
   BOS_TRACE_BIND();
   static bool attr = false;
   if (!attr) {
@@ -1324,9 +1324,10 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
   }
   if (!sort_tile_ok(R, ts)) return hipErrorInvalidValue;
   *result = buf0;
-  // the error word is cleared on every call, before anything can return
+  // the error word is zero before anything can return: the caller has cleared
+  // it on this stream (err_clear) or it is cleared here
   unsigned long long* err = comparison_sort_err_word(split, n, R);
-  {
+  if (!err_clear) {
     const hipError_t e0 = launch_fill_u64(err, 1, 0ull, s);
     if (e0 != hipSuccess) return e0;
   }
@@ -1514,9 +1515,9 @@ hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, con
 // multiway: four-way passes where they apply (split must then hold
 // comparison_sort_split_bytes(n, rec)); else two-way passes only.
 hipError_t launch_comparison_sort(int rec, void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                  hipStream_t s, void** result, bool multiway) {
-  return rec == 8 ? comparison_sort_t<8>(buf0, buf1, n, ts, split, s, result, multiway)
-                  : comparison_sort_t<16>(buf0, buf1, n, ts, split, s, result, multiway);
+                                  hipStream_t s, void** result, bool multiway, bool err_clear) {
+  return rec == 8 ? comparison_sort_t<8>(buf0, buf1, n, ts, split, s, result, multiway, err_clear)
+                  : comparison_sort_t<16>(buf0, buf1, n, ts, split, s, result, multiway, err_clear);
 }
 
 // Tile of the bitonic baseline: 8192 records of 8 bytes or 4096 of 16, 70 KB
