@@ -36,8 +36,10 @@ hipError_t launch_strip(int rec, const void* binned, const uint32_t* loads, unsi
                         unsigned long long* coff, void* out, uint64_t n, uint32_t nblocks, uint32_t klev, uint32_t lz,
                         uint32_t tile, hipStream_t s);
 constexpr uint32_t kScanChunk = 1024;  // block counts per workgroup of the strip's first scan
+bool one_pass_merge(uint64_t n, uint32_t ts);
 hipError_t launch_comparison_sort(int rec, void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                  hipStream_t s, void** result, bool multiway, bool err_clear = false);
+                                  hipStream_t s, void** result, bool multiway, bool err_clear = false,
+                                  bool one_pass = false);
 uint32_t comparison_sort_hbm_passes(int rec, uint64_t n, uint32_t ts, bool multiway);
 size_t comparison_sort_split_bytes(uint64_t n, int rec);
 unsigned long long* comparison_sort_err_word(uint64_t* split, uint64_t n, int rec);
@@ -1154,7 +1156,20 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
   // The comparison sort ping-pongs between `out` and a free region of the
   // workspace (sort_tmp); the routing output goes where the sort must start
   // so that the result lands in `out`.
-  const uint32_t passes = comparison_sort_hbm_passes(pl.rec, n, pl.tile, true);
+  // A sort of at most 16 tiles merges them in one launch: the smallest tile
+  // from 4096 records up that makes it so, even where the table has another one
+  // (its small classes are timed in batches, whose tiles fill the chip).  2^16
+  // records of 8 bytes: tile sort 62 us on four workgroups of 16384 records, 23
+  // on sixteen of 4096.  2^17: 170 us in all with 8192, 191 with 16384 and 227
+  // with 4096 (32 tiles, merge passes).
+  if (q.tile == 0)
+    for (uint32_t t = 4096; sort_tile_ok(pl.rec, t); t *= 2)
+      if (n <= 16ull * t) {
+        if (pl.tile > t || n > 16ull * pl.tile) pl.tile = t;
+        break;
+      }
+  const uint32_t passes =
+      one_pass_merge(n, pl.tile) ? 1u : comparison_sort_hbm_passes(pl.rec, n, pl.tile, true);
   const bool split = split_last(pl);
   void* tmp = sort_tmp(pl, w);
   void* start = (passes % 2 == 0) ? out : tmp;
@@ -1177,7 +1192,7 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
     hipError_t e = enqueue_routing(pl, in, start, q.seed, att, 1, w, s, -1, split, q.flags, err);
     if (e != hipSuccess) return BOS_ERR_HIP;
     void* result = nullptr;
-    e = launch_comparison_sort(pl.rec, start, other, n, pl.tile, csplit, s, &result, true, true);
+    e = launch_comparison_sort(pl.rec, start, other, n, pl.tile, csplit, s, &result, true, true, true);
     if (e != hipSuccess) return BOS_ERR_HIP;
     if (result != out) {
       e = hipMemcpyAsync(out, result, n * pl.rec, hipMemcpyDeviceToDevice, s);

@@ -556,6 +556,146 @@ __device__ __forceinline__ bool precedes(T x, uint32_t kx, T e, uint32_t ke) {
   return kx < ke ? !rec_less(e, x) : rec_less(x, e);
 }
 
+// ---- one-pass merge of a small sort ------------------------------------------
+//
+// A sort of at most kRankRuns tiles is finished by one launch: every record's
+// place in the output is its index in its run plus, for every other run, the
+// number of records before it (in the order (record, run)).  A workgroup takes
+// 256 consecutive records of one run; its waves bound the matching windows of
+// the other runs with 64-ary searches, the windows go to LDS (or are searched in
+// global memory when they hold more than kRankCap records, as repeated records
+// can make them), and each thread searches there.  Four-way passes over the
+// same runs take four launches each of which fills a few CUs: 2^16 records of 8
+// bytes in tiles of 4096 took 2 x 38 us, this launch takes 27.
+constexpr uint32_t kRankRuns = 16;
+template <int R>
+constexpr uint32_t kRankCap = R == 8 ? 6144u : 5120u;
+
+template <int R>
+__global__ __launch_bounds__(256) void merge_rank_kernel(const void* src_, void* dst_, uint64_t n, uint32_t lw) {
+  using T = typename RecOf<R>::T;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* win = reinterpret_cast<T*>(smem);
+  __shared__ uint32_t wlo[kRankRuns], wlen[kRankRuns], woff[kRankRuns];
+  __shared__ uint32_t wtotal;
+  const T* src = static_cast<const T*>(src_);
+  T* dst = static_cast<T*>(dst_);
+  const uint64_t base = uint64_t(blockIdx.x) * 256u;  // runs are multiples of 256 long
+  const uint32_t j = uint32_t(base >> lw), runs = uint32_t((n + (1ull << lw) - 1) >> lw);
+  const uint64_t last = (base + 256u < n ? base + 256u : n) - 1;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  if (tid < kRankRuns) wlo[tid] = wlen[tid] = 0;
+  __syncthreads();
+  {
+    BOS_TR(1, 40, base);
+    BOS_TR(1, 40, last);
+    const T ef = src[base], el = src[last];
+    constexpr uint32_t KW = kRankRuns / 4;  // runs per wave
+    uint32_t lo[KW][2], hi[KW][2];
+    bool more = false;
+#pragma unroll
+    for (uint32_t q = 0; q < KW; ++q) {
+      const uint32_t k = wave * KW + q;
+      const uint64_t st = uint64_t(k) << lw;
+      const uint32_t len = k < runs && k != j ? uint32_t(n - st < (1ull << lw) ? n - st : (1ull << lw)) : 0u;
+      lo[q][0] = lo[q][1] = 0;
+      hi[q][0] = hi[q][1] = len;
+      more = more || len > 0;
+    }
+    while (more) {
+      more = false;
+      // a round: every open search's probes, then the ballots
+      T x[KW][2];
+#pragma unroll
+      for (uint32_t q = 0; q < KW; ++q)
+#pragma unroll
+        for (uint32_t b = 0; b < 2; ++b) {
+          const uint32_t l = lo[q][b], h = hi[q][b], sp = (h - l + 63) / 64, at = l + lane * sp;
+          const uint64_t i = l < h ? (uint64_t(wave * KW + q) << lw) + (at < h ? at : l) : base;
+          BOS_TR(1, 40, i);
+          x[q][b] = src[i];  // (a closed search rereads a valid record)
+        }
+#pragma unroll
+      for (uint32_t q = 0; q < KW; ++q)
+#pragma unroll
+        for (uint32_t b = 0; b < 2; ++b) {
+          if (lo[q][b] >= hi[q][b]) continue;  // uniform over the wave
+          const uint32_t l = lo[q][b], h = hi[q][b], sp = (h - l + 63) / 64, at = l + lane * sp;
+          const bool pr = at < h && precedes(x[q][b], wave * KW + q, sel(b != 0, el, ef), j);
+          const uint32_t f = uint32_t(__popcll(__ballot(pr)));
+          if (f == 0) {
+            hi[q][b] = l;
+          } else {
+            lo[q][b] = l + (f - 1) * sp + 1;
+            hi[q][b] = l + f * sp < h ? l + f * sp : h;
+          }
+          more = more || lo[q][b] < hi[q][b];
+        }
+    }
+    if (lane == 0)
+#pragma unroll
+      for (uint32_t q = 0; q < KW; ++q) {
+        BOS_TR(1, 51, wave * KW + q);
+        wlo[wave * KW + q] = lo[q][0];
+        wlen[wave * KW + q] = lo[q][1] - lo[q][0];
+      }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t t = 0;
+    for (uint32_t k = 0; k < kRankRuns; ++k) {
+      woff[k] = t;
+      t += wlen[k];
+    }
+    wtotal = t;
+  }
+  __syncthreads();
+  const bool inl = wtotal <= kRankCap<R>;
+  if (inl) {
+    for (uint32_t k = 0; k < runs; ++k)
+      for (uint32_t t = tid; t < wlen[k]; t += 256) {
+        BOS_TR(1, 40, (uint64_t(k) << lw) + wlo[k] + t);
+        BOS_TR(1, 46, woff[k] + t);
+        win[woff[k] + t] = src[(uint64_t(k) << lw) + wlo[k] + t];
+      }
+  }
+  __syncthreads();
+  const uint64_t i = base + tid;
+  if (i > last) return;
+  BOS_TR(1, 40, i);
+  const T e = src[i];
+  uint32_t c[kRankRuns], len[kRankRuns], any = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kRankRuns; ++k) {
+    c[k] = 0;
+    len[k] = wlen[k];
+    any |= len[k];
+  }
+  while (any) {
+    any = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kRankRuns; ++k) {
+      if (len[k] == 0) continue;
+      const uint32_t half = len[k] >> 1, at = c[k] + half;
+      if (inl) BOS_TR(1, 46, woff[k] + at);
+      else BOS_TR(1, 40, (uint64_t(k) << lw) + wlo[k] + at);
+      const T x = inl ? win[woff[k] + at] : src[(uint64_t(k) << lw) + wlo[k] + at];
+      if (precedes(x, k, e, j)) {
+        c[k] = at + 1;
+        len[k] -= half + 1;
+      } else {
+        len[k] = half;
+      }
+      any |= len[k];
+    }
+  }
+  uint64_t pos = i - (uint64_t(j) << lw);
+#pragma unroll
+  for (uint32_t k = 0; k < kRankRuns; ++k) pos += wlo[k] + c[k];
+  BOS_TR(1, 49, pos);
+  dst[pos] = e;
+}
+
 // Samples of a four-way pass's input, smp[i] = src[i*G], when a two-way pass
 // produced it (the tile sort and the four-way tile kernel write their own).
 template <int R>
@@ -1308,12 +1448,15 @@ static bool four_way_next(int rec, uint64_t n, uint64_t w) {
   return w >= merge_tile_records(rec) && l >= 2 && l % 2 == 0;
 }
 
+// Does one rank launch finish the sort after its tiles of ts records?
+bool one_pass_merge(uint64_t n, uint32_t ts) { return n > ts && n <= uint64_t(kRankRuns) * ts; }
+
 hipError_t launch_fill_u64(unsigned long long* p, uint64_t count, unsigned long long v, hipStream_t s);
 unsigned long long* comparison_sort_err_word(uint64_t* split, uint64_t n, int rec);
 
 template <int R>
 static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                    hipStream_t s, void** result, bool multiway, bool err_clear) {
+                                    hipStream_t s, void** result, bool multiway, bool err_clear, bool one_pass) {
   BOS_TRACE_BIND();
   static bool attr = false;
   if (!attr) {
@@ -1336,11 +1479,15 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
   void* smp = region + align256(split2_bytes(n));
   uint64_t* spl = reinterpret_cast<uint64_t*>(region + align256(split2_bytes(n)) + align256(sample_bytes(R, n)));
   // the tile sort writes the first merge pass's samples when that pass is four-way
-  bool have_sample = multiway && ts < n && four_way_next(R, n, ts);
+  bool have_sample = multiway && ts < n && four_way_next(R, n, ts) && !(one_pass && one_pass_merge(n, ts));
   void* tsmp = have_sample ? smp : nullptr;
   prof_begin(BOS_K_SORT_TILE, 0, 2 * n * R, s);
   hipError_t e = hipErrorInvalidValue;
-  switch (ts) {
+  // one tile: the smallest network that holds the n records (1000 records of 8
+  // bytes: 23.5 us with the 4096-record network, 16.5 with the 1024-record one)
+  uint32_t tn = ts;
+  while (n <= ts && tn > 1024 && n <= tn / 2) tn /= 2;
+  switch (tn) {
     case 1024: e = launch_tile_sort_t<R, 10>(buf0, n, s, tsmp); break;
     case 2048: e = launch_tile_sort_t<R, 11>(buf0, n, s, tsmp); break;
     case 4096: e = launch_tile_sort_t<R, 12>(buf0, n, s, tsmp); break;
@@ -1353,6 +1500,23 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
   if (e != hipSuccess) return e;
   void* src = buf0;
   void* dst = buf1;
+  if (one_pass && one_pass_merge(n, ts)) {
+    static bool rattr = false;
+    if (!rattr) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_rank_kernel<R>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, int(kRankCap<R> * uint32_t(R)));
+      if (e != hipSuccess) return e;
+      rattr = true;
+    }
+    uint32_t lw = 0;
+    while ((1u << lw) < ts) ++lw;
+    prof_begin(BOS_K_SORT_MERGE, 0, 2 * n * R, s);
+    hipLaunchKernelGGL(merge_rank_kernel<R>, dim3(uint32_t((n + 255) / 256)), dim3(256), kRankCap<R> * uint32_t(R), s,
+                       src, dst, n, lw);
+    prof_end(s);
+    *result = dst;
+    return hipGetLastError();
+  }
   uint32_t pass = 0;
   const uint64_t mtiles = (n + kMTile<R> - 1) / kMTile<R>;
   const uint32_t merge_lds = (kMTile<R> + (kMTile<R> >> 4)) * uint32_t(R);
@@ -1513,11 +1677,13 @@ hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, con
 }
 
 // multiway: four-way passes where they apply (split must then hold
-// comparison_sort_split_bytes(n, rec)); else two-way passes only.
+// comparison_sort_split_bytes(n, rec)); else two-way passes only.  one_pass:
+// where one_pass_merge(n, ts) holds, one rank launch in place of the merge
+// passes (the result is then in buf1).
 hipError_t launch_comparison_sort(int rec, void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                  hipStream_t s, void** result, bool multiway, bool err_clear) {
-  return rec == 8 ? comparison_sort_t<8>(buf0, buf1, n, ts, split, s, result, multiway, err_clear)
-                  : comparison_sort_t<16>(buf0, buf1, n, ts, split, s, result, multiway, err_clear);
+                                  hipStream_t s, void** result, bool multiway, bool err_clear, bool one_pass) {
+  return rec == 8 ? comparison_sort_t<8>(buf0, buf1, n, ts, split, s, result, multiway, err_clear, one_pass)
+                  : comparison_sort_t<16>(buf0, buf1, n, ts, split, s, result, multiway, err_clear, one_pass);
 }
 
 // Tile of the bitonic baseline: 8192 records of 8 bytes or 4096 of 16, 70 KB
