@@ -1156,16 +1156,16 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
   // The comparison sort ping-pongs between `out` and a free region of the
   // workspace (sort_tmp); the routing output goes where the sort must start
   // so that the result lands in `out`.
-  // A sort of at most 16 tiles merges them in one launch: the smallest tile
-  // from 4096 records up that makes it so, even where the table has another one
-  // (its small classes are timed in batches, whose tiles fill the chip).  2^16
-  // records of 8 bytes: tile sort 62 us on four workgroups of 16384 records, 23
-  // on sixteen of 4096.  2^17: 170 us in all with 8192, 191 with 16384 and 227
-  // with 4096 (32 tiles, merge passes).
+  // A sort of at most 16 tiles merges them in one launch, and a table's tile
+  // above 4096 is for the many tiles of a batch: a lone sort takes the smallest
+  // tile from 4096 records up that keeps it within 16.  2^16 records of 8 bytes:
+  // tile sort 62 us on four workgroups of 16384 records, 23 on sixteen of 4096;
+  // 2^17: 170 us in all with 8192, 191 with 16384 and 227 with 4096 (32 tiles,
+  // merge passes).
   if (q.tile == 0)
-    for (uint32_t t = 4096; sort_tile_ok(pl.rec, t); t *= 2)
+    for (uint32_t t = 4096; t < pl.tile; t *= 2)
       if (n <= 16ull * t) {
-        if (pl.tile > t || n > 16ull * pl.tile) pl.tile = t;
+        pl.tile = t;
         break;
       }
   const uint32_t passes =
