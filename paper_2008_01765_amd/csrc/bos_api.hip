@@ -48,10 +48,8 @@ hipError_t launch_route_batched(int rec, uint32_t lz, bool first, bool last, con
                                 uint32_t lds, hipStream_t s, bool split);
 hipError_t launch_strip_batched(int rec, const StripSeg* segs, uint32_t nsegs, uint32_t blocks, hipStream_t s);
 hipError_t launch_block_scan(unsigned long long* bsum, unsigned long long* coff, uint32_t nblocks, hipStream_t s);
-hipError_t launch_strip_staged(int rec, const void* binned, const uint32_t* loads, const unsigned long long* bsum,
-                               const unsigned long long* coff, void* out, uint64_t n, uint32_t klev, uint32_t lz,
-                               uint32_t tile, uint64_t blk0, uint32_t nblk, uint64_t bin_slot0, uint64_t out0,
-                               hipStream_t s);
+hipError_t launch_chunk_words(const unsigned long long* status, const unsigned long long* counts, uint32_t nb,
+                              unsigned long long* words, hipStream_t s);
 hipError_t launch_or_u64(unsigned long long* dst, const unsigned long long* src, hipStream_t s);
 hipError_t launch_orp_finish(int rec, uint32_t lz, const FinishArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_sort_batched(int rec, int kind, uint32_t tile, const SortSeg* segs, uint32_t nsegs, uint32_t total,
@@ -1996,19 +1994,19 @@ bos_status sort_batched_sequential(const bos_instance* inst, uint32_t count, bos
 //
 // The records, the output and the two slot arrays of Algorithm 3.1 stay in host
 // memory; the device holds the small per-run arrays (overflow word, bin loads,
-// block counts) and staging buffers.  Every routing pass streams the slot
-// arrays through the device once: a chunk of the pass's blocks is a range of
-// consecutive block indices, whose input is one contiguous range of buckets
-// when the chunk covers whole groups of 2^(i+k) buckets and 2^k contiguous
-// segments otherwise, and whose output is one contiguous range of buckets
-// (the consecutive-bucket structure of Section 4.3).  Chunks alternate between
-// two staging sets and run as a pipeline over three streams (input copies,
-// kernels, output copies; OocPipe), so that the next chunk's input copy runs
-// while this chunk's output copy does: the host link carries both directions
-// at once.  The per-bin finish (bos_orp) or strip (bos_sort) streams the bins
-// the same way; the sort's comparison phase is a two-pass external sort: runs
-// sorted on the device, then output segments cut by sample splitters, each
-// gathered from the runs, sorted on the device and written once.
+// block counts) and staging buffers.  The slot arrays make as few trips through
+// the device as the staging buffers allow (OocTrip): a chunk runs every pass of
+// its trip before it leaves.  A chunk is a range of consecutive block indices,
+// whose input is a range of the records in the first trip and 2^K contiguous
+// segments of buckets in the later ones, and whose output is one contiguous range
+// of buckets (the consecutive-bucket structure of Section 4.3).  Chunks
+// alternate between two staging sets and run as a pipeline over three streams
+// (input copies, kernels, output copies; OocPipe), so that the next chunk's input
+// copy runs while this chunk's output copy does: the host link carries both
+// directions at once.  bos_orp's per-bin finish streams the bins the same way.
+// bos_sort strips and sorts each chunk of the last trip on the device, so that it
+// leaves as a sorted run; the runs are then merged: output segments cut by sample
+// splitters, each gathered from the runs, sorted on the device and written once.
 namespace {
 
 constexpr uint64_t kMaxNHost = 1ull << 36;
@@ -2022,8 +2020,9 @@ struct OocStreams {
 std::mutex g_ooc_mu;
 OocStreams g_ooc[kOocDevices];
 
-// Host workspace: slot arrays 0 and 1 (records, then the two tag arrays side
-// by side: after routing they hold the sort's runs, 2 B Z 4 >= n R bytes).
+// Host workspace: slot arrays 0 and 1 (records, then the two tag arrays; the
+// last trip of a sort leaves its runs in the records of slot array (trips - 1) &
+// 1).
 struct HostLayout {
   size_t off_rec[2], off_tag[2], total;
 };
@@ -2125,102 +2124,197 @@ struct OocPipe {
   hipError_t done() { return hipEventRecord(o->ev_out[b], o->st[2]); }
 };
 
-// One attempt's routing passes, chunk by chunk (the last in split form: bins
-// compacted into host slot array (P - 1) & 1, loads and block counts on the
-// device).
+// One trip of the slot arrays over the host link: routing passes [t0, t1), the
+// levels [i0, i0 + K), chunk by chunk.  A block of the trip is what a single pass
+// of K levels would work on, 2^K buckets; a chunk is cb of them.
+struct OocTrip {
+  uint32_t t0, t1, i0, K;
+  uint64_t cb;
+};
+
+// The trips of a plan whose staging buffers hold `cap` slots.  A chunk's passes
+// run back to back on the device, so a trip takes as many passes as 2^K buckets
+// fit the buffers: the link bounds a trip.  A sort of 2^24 records of 8 bytes
+// with 256 MB of staging took 51 ms with its four passes as four trips and 25 ms
+// with two.  After the first trip a chunk is read in
+// 2^K segments; they stay at 512 KB of records or more (9 us of the link, what a
+// copy costs to start), except that a trip has at least one pass.
+std::vector<OocTrip> ooc_trips(const Plan& pl, uint64_t cap) {
+  std::vector<OocTrip> trips;
+  for (uint32_t t = 0; t < pl.P;) {
+    OocTrip o{t, t + 1, pl.lev0[t], pl.klev[t], 0};
+    auto fits = [&](uint32_t K) {
+      const uint64_t cb = cap >> (K + pl.lz);  // blocks per chunk
+      return cb > 0 && (o.i0 == 0 || (cap >> K) * uint64_t(pl.rec) >= (512u << 10));
+    };
+    while (o.t1 < pl.P && fits(o.K + pl.klev[o.t1])) o.K += pl.klev[o.t1++];
+    o.cb = std::min<uint64_t>(pl.B >> o.K, cap >> (o.K + pl.lz));
+    trips.push_back(o);
+    t = o.t1;
+  }
+  return trips;
+}
+
+// Input copies of the trip's chunk of blocks [it0, it0 + cb) into the staging
+// buffer (rec, tag).
+hipError_t ooc_copy_in(const Plan& pl, const OocTrip& o, uint64_t it0, const char* in, const char* hin_rec,
+                       const char* hin_tag, char* rec, char* tag, hipStream_t s) {
+  const size_t R = pl.rec;
+  if (o.t0 == 0) {
+    // groups [it0 2^K, (it0 + cb) 2^K) hold X[x_lo, x_hi)
+    const uint64_t x_lo = ((it0 << o.K) * pl.n) >> pl.L, x_hi = (((it0 + o.cb) << o.K) * pl.n) >> pl.L;
+    return h2d(rec, in + x_lo * R, (x_hi - x_lo) * R, s);
+  }
+  // inside one group (the trip before took every pass that left whole groups
+  // in a chunk): 2^K segments of cb buckets
+  const uint64_t h0 = it0 >> o.i0, r0 = it0 & ((1ull << o.i0) - 1), seg = o.cb << pl.lz;
+  hipError_t e = hipSuccess;
+  for (uint64_t m = 0; m < (1ull << o.K) && e == hipSuccess; ++m) {
+    const uint64_t slot0 = ((h0 << (o.i0 + o.K)) + (m << o.i0) + r0) << pl.lz;
+    e = h2d(rec + m * seg * R, hin_rec + slot0 * R, seg * R, s);
+    if (e == hipSuccess) e = h2d(tag + m * seg * 4, hin_tag + slot0 * 4, seg * 4, s);
+  }
+  return e;
+}
+
+// The sorted runs that an attempt's last trip left in host memory (bos_sort),
+// run r at base + r * stride records.
+struct OocRuns {
+  char* base = nullptr;
+  uint64_t stride = 0;
+  std::vector<uint64_t> len;
+};
+
+// One attempt's routing.  bos_orp (runs null): the last pass in split form, bins
+// compacted into host slot array (trips - 1) & 1, loads and block counts on the
+// device.  bos_sort: the last trip's chunks are whole bins, so their reals are
+// stripped and sorted where they are and leave the device as one sorted run per
+// chunk (the lone run of a one-chunk trip goes to `out`); the chunk's real count,
+// which the run's length is, is read after its routing.  An overflowed attempt's
+// runs are not formed.
 hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, const char* in, char* hws,
-                     const HostLayout& hl, char* dws, const DevLayout& dl, OocStreams* o) {
-  const int R = pl.rec;
+                     const HostLayout& hl, char* dws, const DevLayout& dl, OocStreams* o,
+                     const std::vector<OocTrip>& trips, uint64_t cap, char* out, OocRuns* runs) {
+  const size_t R = pl.rec;
   unsigned long long* status = reinterpret_cast<unsigned long long*>(dws + dl.off_status);
-  hipError_t e = launch_fill_u64(status, 2 + pl.nblocks_last, 0, o->st[0]);
-  if (e == hipSuccess) e = launch_fill_u64(status, 1, kNoOverflow, o->st[0]);
+  unsigned long long* scan = status + 2;
+  unsigned long long* coff = reinterpret_cast<unsigned long long*>(dws + dl.off_coff);
+  unsigned long long* err = reinterpret_cast<unsigned long long*>(dws + dl.off_err);
+  uint32_t* loads = reinterpret_cast<uint32_t*>(dws + dl.off_loads);
+  hipError_t e = launch_attempt_init(status, 2 + pl.nblocks_last, err, o->st[0]);
   if (e == hipSuccess) e = hipStreamSynchronize(o->st[0]);
   if (e != hipSuccess) return e;
-  // staging: two sets of input records, input tags, output records, output tags
-  const uint64_t cap = pow2_floor(dl.stage / (4 * size_t(R + 4)));  // slots per buffer
-  for (uint32_t t = 0; t < pl.P; ++t) {
-    const uint32_t i0 = pl.lev0[t], k = pl.klev[t];
-    const bool first = t == 0, last = t + 1 == pl.P;
-    const uint64_t items = pl.B >> k, blk_slots = uint64_t(pl.Z) << k;
-    const uint64_t cb = std::min<uint64_t>(items, cap / blk_slots);
-    const char* hin_rec = hws + hl.off_rec[(t + 1) & 1];
-    const char* hin_tag = hws + hl.off_tag[(t + 1) & 1];
-    char* hout_rec = hws + hl.off_rec[t & 1];
-    char* hout_tag = hws + hl.off_tag[t & 1];
-    uint32_t c = 0;
+  for (size_t g = 0; g < trips.size(); ++g) {
+    const OocTrip& tr = trips[g];
+    const bool fuse = runs && g + 1 == trips.size();
+    const uint64_t items = pl.B >> tr.K, nchunks = items / tr.cb, cslots = (tr.cb << tr.K) << pl.lz;
+    const char* hin_rec = hws + hl.off_rec[(g + 1) & 1];
+    const char* hin_tag = hws + hl.off_tag[(g + 1) & 1];
+    char* hout_rec = hws + hl.off_rec[g & 1];
+    char* hout_tag = hws + hl.off_tag[g & 1];
+    if (fuse) {
+      runs->base = nchunks == 1 ? out : hout_rec;
+      runs->stride = cslots;
+      runs->len.assign(nchunks, 0);
+    }
+    // staging set b: two buffers of `cap` slots, records then tags; a chunk's
+    // passes go back and forth between them
+    auto buf = [&](int b, uint32_t x) { return dws + dl.off_stage + (size_t(b) * 2 + (x & 1u)) * cap * (R + 4); };
     OocPipe pipe{o};
-    for (uint64_t it0 = 0; it0 < items; it0 += cb, ++c) {
-      const int b = int(c & 1u);
+    auto copy_in = [&](uint64_t c) {
       hipStream_t s = nullptr;
-      e = pipe.start(c, &s);
-      if (e != hipSuccess) return e;
-      char* set = dws + dl.off_stage + size_t(b) * 2 * cap * (R + 4);
-      char* d_in_rec = set;
-      uint32_t* d_in_tag = reinterpret_cast<uint32_t*>(set + cap * R);
-      char* d_out_rec = set + cap * (R + 4);
-      uint32_t* d_out_tag = reinterpret_cast<uint32_t*>(set + cap * (R + 4) + cap * R);
-      PassArgs a;
-      std::memset(&a, 0, sizeof(a));
-      if (first) {
-        // groups [it0 2^k, (it0 + cb) 2^k) hold X[x_lo, x_hi)
-        const uint64_t j_lo = it0 << k, j_hi = (it0 + cb) << k;
-        const uint64_t x_lo = (j_lo * pl.n) >> pl.L, x_hi = (j_hi * pl.n) >> pl.L;
-        e = h2d(d_in_rec, in + x_lo * R, (x_hi - x_lo) * R, s);
-        a.x_in = d_in_rec;
-        a.x_off = x_lo;
-      } else {
-        const uint64_t g = 1ull << i0, h0 = it0 >> i0;
-        a.staged = 1;
-        a.in_h0 = h0;
-        if (cb >= g) {  // whole groups: one contiguous range of buckets
-          const uint64_t slot0 = (h0 << (i0 + k)) << pl.lz, ns = cb * blk_slots;
-          e = h2d(d_in_rec, hin_rec + slot0 * R, ns * R, s);
-          if (e == hipSuccess) e = h2d(d_in_tag, hin_tag + slot0 * 4, ns * 4, s);
-          a.in_r0 = 0;
-          a.in_lseg = i0;
-        } else {  // inside one group: 2^k segments of cb buckets
-          const uint64_t r0 = it0 & (g - 1), seg = cb << pl.lz;
-          for (uint64_t m = 0; m < (1ull << k) && e == hipSuccess; ++m) {
-            const uint64_t slot0 = ((h0 << (i0 + k)) + (m << i0) + r0) << pl.lz;
-            e = h2d(d_in_rec + m * seg * R, hin_rec + slot0 * R, seg * R, s);
-            if (e == hipSuccess) e = h2d(d_in_tag + m * seg, hin_tag + slot0 * 4, seg * 4, s);
-          }
-          a.in_r0 = r0;
-          a.in_lseg = log2u(cb);
-        }
-        a.rec_in = d_in_rec;
-        a.tag_in = d_in_tag;
-      }
-      if (e != hipSuccess) return e;
-      const uint64_t out_slot0 = (it0 << k) << pl.lz, ns_out = cb * blk_slots;
-      a.rec_out = d_out_rec;
-      a.tag_out = d_out_tag;
-      a.out_slot0 = out_slot0;
-      a.status = status;
-      a.ticket = reinterpret_cast<uint32_t*>(status + 1);
-      a.scan = status + 2;
-      a.n = pl.n;
-      a.buckets = pl.B;
-      a.seed = q.seed;
-      a.z = pl.Z;
-      a.lz = pl.lz;
-      a.levels = pl.L;
-      a.level0 = i0;
-      a.klev = k;
-      a.attempt = attempt;
-      a.fin = 1;
-      a.item_off = uint32_t(it0);
-      if (last) a.loads = reinterpret_cast<uint32_t*>(dws + dl.off_loads);
-      const uint32_t kind = first ? BOS_K_ROUTE_FIRST : last ? BOS_K_ROUTE_LAST : BOS_K_ROUTE_MID;
-      const uint64_t slot_bytes = ns_out * (uint64_t(R) + 4);
+      hipError_t x = pipe.start(c, &s);
+      char* d = buf(pipe.b, 0);
+      return x == hipSuccess ? ooc_copy_in(pl, tr, c * tr.cb, in, hin_rec, hin_tag, d, d + cap * R, s) : x;
+    };
+    bool overflowed = false;
+    e = copy_in(0);
+    if (e != hipSuccess) return e;
+    for (uint64_t c = 0; c < nchunks; ++c) {
+      const uint64_t it0 = c * tr.cb, out_slot0 = (it0 << tr.K) << pl.lz;
+      // the chunk's r of each group, and its first group and r
+      const uint32_t lc = tr.i0 ? log2u(tr.cb) : 0u;
+      const uint64_t h0 = it0 >> tr.i0, r0 = it0 & ((1ull << tr.i0) - 1);
+      hipStream_t s = nullptr;
+      pipe.b = int(c & 1u);
+      const int b = pipe.b;
       e = pipe.kernels(&s);
-      if (e != hipSuccess) return e;
-      prof_begin(kind, t, slot_bytes * 2, s);
-      e = launch_route(R, a, first, last, uint32_t(cb), num_cus(), s, last);
-      prof_end(s);
+      uint32_t x = 0;  // the buffer that holds the chunk
+      for (uint32_t t = tr.t0; t < tr.t1 && e == hipSuccess; ++t, ++x) {
+        const bool first = t == 0, last = t + 1 == pl.P;
+        const uint32_t k = pl.klev[t], dl0 = pl.lev0[t] - tr.i0;
+        PassArgs a;
+        std::memset(&a, 0, sizeof(a));
+        if (first) {
+          a.x_in = buf(b, x);
+          a.x_off = ((it0 << tr.K) * pl.n) >> pl.L;
+        } else {
+          a.rec_in = buf(b, x);
+          a.tag_in = reinterpret_cast<const uint32_t*>(buf(b, x) + cap * R);
+        }
+        a.staged = 1;
+        a.in_lseg = lc + dl0;
+        a.in_h0 = h0 << (tr.K - dl0 - k);
+        a.in_r0 = r0 << dl0;
+        a.rec_out = buf(b, x + 1);
+        a.tag_out = reinterpret_cast<uint32_t*>(buf(b, x + 1) + cap * R);
+        a.out_slot0 = out_slot0;
+        a.status = status;
+        a.ticket = reinterpret_cast<uint32_t*>(status + 1);
+        a.scan = scan;
+        a.n = pl.n;
+        a.buckets = pl.B;
+        a.seed = q.seed;
+        a.z = pl.Z;
+        a.lz = pl.lz;
+        a.levels = pl.L;
+        a.level0 = pl.lev0[t];
+        a.klev = k;
+        a.attempt = attempt;
+        a.fin = 1;
+        if (last) a.loads = loads;
+        const uint32_t kind = first ? BOS_K_ROUTE_FIRST : last ? BOS_K_ROUTE_LAST : BOS_K_ROUTE_MID;
+        prof_begin(kind, t, cslots * (R + 4) * 2, s);
+        e = launch_route(int(R), a, first, last, uint32_t(tr.cb << (tr.K - k)), num_cus(), s, last);
+        prof_end(s);
+      }
+      const char* res = buf(b, x);
+      uint64_t len = cslots;
+      const uint32_t klast = pl.klev[pl.P - 1], nblk = uint32_t(tr.cb << (tr.K - klast));
+      unsigned long long* bsum = scan + (it0 << (tr.K - klast));
+      if (fuse && e == hipSuccess) e = launch_chunk_words(status, bsum, nblk, err + 1, s);
+      // the next chunk's input copies run while this chunk is worked on
+      if (e == hipSuccess && c + 1 < nchunks) e = copy_in(c + 1);
+      pipe.b = b;
+      if (fuse && e == hipSuccess) {
+        uint64_t words[2] = {0, 0};  // overflow word, reals of the chunk
+        e = d2h(words, err + 1, 16, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        overflowed = overflowed || words[0] != kNoOverflow;
+        len = overflowed ? 0 : words[1];
+        if (len > cslots) return hipErrorUnknown;  // (a bin holds at most Z)
+        runs->len[c] = len;
+        if (e == hipSuccess && len) {
+          // strip into the other buffer, sort there and in this one; the merge
+          // splits go where the other buffer's tags were
+          char* to = buf(b, x + 1);
+          uint64_t* split = reinterpret_cast<uint64_t*>(to + cap * R);
+          if (comparison_sort_split_bytes(len, int(R)) > cap * 4) return hipErrorInvalidValue;
+          prof_begin(BOS_K_STRIP, uint32_t(c), 2 * len * R, s);
+          e = launch_strip(int(R), res, loads + (it0 << tr.K), bsum, coff, to, len, nblk, klast, pl.lz, pl.tile, s);
+          prof_end(s);
+          void* r = to;
+          if (e == hipSuccess && len > 1) {
+            e = launch_comparison_sort(int(R), to, buf(b, x), len, pl.tile, split, s, &r, true, false, true);
+            if (e == hipSuccess) e = launch_or_u64(err, comparison_sort_err_word(split, len, int(R)), s);
+          }
+          res = static_cast<const char*>(r);
+        }
+      }
       if (e == hipSuccess) e = pipe.out(&s);
-      if (e == hipSuccess) e = d2h(hout_rec + out_slot0 * R, d_out_rec, ns_out * R, s);
-      if (e == hipSuccess && !last) e = d2h(hout_tag + out_slot0 * 4, d_out_tag, ns_out * 4, s);
+      char* dst = fuse ? runs->base + c * cslots * R : hout_rec + out_slot0 * R;
+      if (e == hipSuccess) e = d2h(dst, res, len * R, s);
+      if (e == hipSuccess && tr.t1 < pl.P) e = d2h(hout_tag + out_slot0 * 4, res + cap * R, len * 4, s);
       if (e == hipSuccess) e = pipe.done();
       if (e != hipSuccess) return e;
     }
@@ -2249,24 +2343,20 @@ hipError_t ooc_block_offsets(const Plan& pl, char* dws, const DevLayout& dl, hip
   return hipSuccess;
 }
 
-// bos_orp's per-bin finish, or bos_sort's strip (into `dst`, host), over
-// chunks of whole routing blocks.
-hipError_t ooc_finish(const Plan& pl, const bos_params& q, uint32_t attempt, bool sort, char* dst, char* hws,
-                      const HostLayout& hl, char* dws, const DevLayout& dl, OocStreams* o,
-                      const std::vector<uint64_t>& boff) {
+// bos_orp's per-bin finish (into `dst`, host) of the bins in host slot array
+// `binned`, over chunks of whole routing blocks.
+hipError_t ooc_finish(const Plan& pl, const bos_params& q, uint32_t attempt, char* dst, const char* binned, char* dws,
+                      const DevLayout& dl, OocStreams* o, const std::vector<uint64_t>& boff) {
   const int R = pl.rec;
   const uint32_t klast = pl.klev[pl.P - 1];
-  const char* binned = hws + hl.off_rec[(pl.P - 1) & 1];
   unsigned long long* scan = reinterpret_cast<unsigned long long*>(dws + dl.off_status) + 2;
   unsigned long long* coff = reinterpret_cast<unsigned long long*>(dws + dl.off_coff);
   unsigned long long* tie = coff + pl.nblocks_last / kScanChunk + 1;
   const uint32_t* loads = reinterpret_cast<const uint32_t*>(dws + dl.off_loads);
   hipError_t e = hipSuccess;
-  if (!sort) {
-    e = launch_fill_u64(tie, 1, (q.flags & BOS_EXACT_FINISH) ? 1ull : 0ull, o->st[0]);
-    if (e == hipSuccess) e = hipStreamSynchronize(o->st[0]);
-    if (e != hipSuccess) return e;
-  }
+  e = launch_fill_u64(tie, 1, (q.flags & BOS_EXACT_FINISH) ? 1ull : 0ull, o->st[0]);
+  if (e == hipSuccess) e = hipStreamSynchronize(o->st[0]);
+  if (e != hipSuccess) return e;
   // two sets of (bin slots, output records)
   const uint64_t cap = pow2_floor(dl.stage / (4 * size_t(R)));
   const uint64_t bslots = uint64_t(pl.Z) << klast;  // slots per routing block
@@ -2285,31 +2375,25 @@ hipError_t ooc_finish(const Plan& pl, const bos_params& q, uint32_t attempt, boo
     e = h2d(d_bin, binned + slot0 * R, (b1 - b0) * bslots * R, s);
     if (e == hipSuccess) e = pipe.kernels(&s);
     if (e != hipSuccess) return e;
-    if (sort) {
-      prof_begin(BOS_K_STRIP, c, 2 * (out1 - out0) * R, s);
-      e = launch_strip_staged(R, d_bin, loads, scan, coff, d_out, pl.n, klast, pl.lz, pl.tile, b0, uint32_t(b1 - b0),
-                              slot0, out0, s);
-    } else {
-      FinishArgs f;
-      std::memset(&f, 0, sizeof(f));
-      f.binned = d_bin;
-      f.loads = loads;
-      f.boff = scan;
-      f.coff = coff;
-      f.out = d_out;
-      f.n = pl.n;
-      f.nbins = pl.B;
-      f.seed = q.seed;
-      f.klev = klast;
-      f.attempt = attempt;
-      f.tie = tie;
-      f.gb_lo = b0 << klast;
-      f.gb_hi = b1 << klast;
-      f.bin_slot0 = slot0;
-      f.out0 = out0;
-      prof_begin(BOS_K_ORP_FINISH, c, 2 * (out1 - out0) * R, s);
-      e = launch_orp_finish(R, pl.lz, f, num_cus(), s);
-    }
+    FinishArgs f;
+    std::memset(&f, 0, sizeof(f));
+    f.binned = d_bin;
+    f.loads = loads;
+    f.boff = scan;
+    f.coff = coff;
+    f.out = d_out;
+    f.n = pl.n;
+    f.nbins = pl.B;
+    f.seed = q.seed;
+    f.klev = klast;
+    f.attempt = attempt;
+    f.tie = tie;
+    f.gb_lo = b0 << klast;
+    f.gb_hi = b1 << klast;
+    f.bin_slot0 = slot0;
+    f.out0 = out0;
+    prof_begin(BOS_K_ORP_FINISH, c, 2 * (out1 - out0) * R, s);
+    e = launch_orp_finish(R, pl.lz, f, num_cus(), s);
     prof_end(s);
     if (e == hipSuccess) e = pipe.out(&s);
     if (e == hipSuccess) e = d2h(dst + out0 * R, d_out, (out1 - out0) * R, s);
@@ -2339,18 +2423,15 @@ bool host_rec_less(const char* a, const char* b, int R) {
   return pa < pb;
 }
 
-// Comparison phase of the out-of-core sort (Section 3.3 applied to host
-// arrays): the permuted records in `a` (host, n records) are sorted into
-// `out` (host).  Runs of rl records (a multiple of the tile, so their tile
-// sorts cover the tiles the strip prepared) are sorted on the device in
-// place; then every q-th record of each run is a sample, the samples are
-// ordered by (record, run, position), every t-th opens an output segment, and
-// each run is cut at each splitter by binary search (a total order, so equal
-// records split consistently).  A segment holds at most t q + m (q - 1) <= rl
-// records; its run slices are gathered, sorted on the device and written to
-// their place in `out`.  Every access depends on comparisons of the permuted
-// records only.
-bos_status ooc_comparison_sort(const Plan& pl, char* a, char* out, char* dws, const DevLayout& dl, OocStreams* o) {
+// Merge of the out-of-core sort's runs (Section 3.3 applied to host arrays):
+// every q-th record of each run is a sample, the samples are ordered by (record,
+// run, position), every t-th opens an output segment, and each run is cut at each
+// splitter by binary search (a total order, so equal records split consistently).
+// A segment holds at most t q + m (q - 1) <= rl records; its run slices are
+// gathered, sorted on the device and written to their place in `out`.  Every
+// access depends on comparisons of the permuted records only.
+bos_status ooc_merge_runs(const Plan& pl, const OocRuns& runs, char* out, char* dws, const DevLayout& dl,
+                          OocStreams* o) {
   const int R = pl.rec;
   const uint64_t n = pl.n;
   // two sets of (buffer, buffer, merge splits) of rl records
@@ -2369,61 +2450,40 @@ bos_status ooc_comparison_sort(const Plan& pl, char* a, char* out, char* dws, co
     if (e == hipSuccess) e = launch_or_u64(err, comparison_sort_err_word(split, len, R), s);
     return e;
   };
-  hipError_t e = launch_fill_u64(err, 1, 0ull, o->st[0]);
-  if (e == hipSuccess) e = hipStreamSynchronize(o->st[0]);
-  if (e != hipSuccess) return BOS_ERR_HIP;
-  const uint64_t m = (n + rl - 1) / rl;
-  char* dst_runs = m == 1 ? out : a;  // a single run goes straight to out
-  OocPipe pipe{o};
-  for (uint64_t r = 0; r < m; ++r) {
-    const int sb = int(r & 1u);
-    hipStream_t s = nullptr;
-    const uint64_t len = std::min(rl, n - r * rl);
-    char* set = dws + dl.off_stage + size_t(sb) * set_bytes;
-    void* result = nullptr;
-    e = pipe.start(r, &s);
-    if (e == hipSuccess) e = h2d(set, a + r * rl * R, len * R, s);
-    if (e == hipSuccess) e = pipe.kernels(&s);
-    if (e == hipSuccess) e = sort_on_device(sb, len, s, &result);
-    if (e == hipSuccess) e = pipe.out(&s);
-    if (e == hipSuccess) e = d2h(dst_runs + r * rl * R, result, len * R, s);
-    if (e == hipSuccess) e = pipe.done();
-    if (e != hipSuccess) return BOS_ERR_HIP;
-  }
-  if (sync3(o) != hipSuccess) return BOS_ERR_HIP;
+  hipError_t e = hipSuccess;
+  const uint64_t m = runs.len.size();
+  auto run_at = [&](uint64_t r) { return static_cast<const char*>(runs.base) + r * runs.stride * R; };
   if (m > 1) {
-    // samples every q records of every run, q the largest power of two with m q <= rl / 2
-    uint64_t q = pow2_floor(rl / (2 * m));
-    if (q == 0) return BOS_ERR_WORKSPACE;
+    // samples every q records of every run, q the largest power of two with m q
+    // <= rl / 2 (or 1: every record a sample, and segments of exactly t)
+    const uint64_t q = std::max<uint64_t>(1, pow2_floor(rl / (2 * m)));
     struct Smp {
       const char* p;
       uint64_t run, pos;
     };
     std::vector<Smp> smp;
     for (uint64_t r = 0; r < m; ++r) {
-      const uint64_t len = std::min(rl, n - r * rl);
-      for (uint64_t i = 0; i < len; i += q) smp.push_back(Smp{a + (r * rl + i) * R, r, i});
+      for (uint64_t i = 0; i < runs.len[r]; i += q) smp.push_back(Smp{run_at(r) + i * R, r, i});
     }
     std::sort(smp.begin(), smp.end(), [&](const Smp& x, const Smp& y) {
       if (host_rec_less(x.p, y.p, R)) return true;
       if (host_rec_less(y.p, x.p, R)) return false;
       return x.run != y.run ? x.run < y.run : x.pos < y.pos;
     });
-    const uint64_t t = (rl - m * q) / q;
+    const uint64_t t = q > 1 ? (rl - m * q) / q : rl;
     // cut[j * m + r]: first position of run r in segment j
     std::vector<uint64_t> cut;
     for (uint64_t r = 0; r < m; ++r) cut.push_back(0);
     for (uint64_t si = t; si < smp.size(); si += t) {
       const Smp& sp = smp[si];
       for (uint64_t r = 0; r < m; ++r) {
-        const char* run = a + r * rl * R;
-        const uint64_t len = std::min(rl, n - r * rl);
+        const char* run = run_at(r);
         uint64_t pos;
         if (r == sp.run) {
           pos = sp.pos;
         } else {
           // records before (sp, run, pos) in the order (record, run, position)
-          uint64_t lo = 0, hi = len;
+          uint64_t lo = 0, hi = runs.len[r];
           while (lo < hi) {
             const uint64_t mid = (lo + hi) / 2;
             const char* x = run + mid * R;
@@ -2438,7 +2498,7 @@ bos_status ooc_comparison_sort(const Plan& pl, char* a, char* out, char* dws, co
         cut.push_back(pos);
       }
     }
-    for (uint64_t r = 0; r < m; ++r) cut.push_back(std::min(rl, n - r * rl));
+    for (uint64_t r = 0; r < m; ++r) cut.push_back(runs.len[r]);
     const uint64_t nseg = cut.size() / m - 1;
     uint64_t base = 0;
     OocPipe spipe{o};
@@ -2451,7 +2511,7 @@ bos_status ooc_comparison_sort(const Plan& pl, char* a, char* out, char* dws, co
       for (uint64_t r = 0; r < m && e == hipSuccess; ++r) {
         const uint64_t c0 = cut[j * m + r], c1 = cut[(j + 1) * m + r];
         if (c1 < c0 || len + (c1 - c0) > rl) return BOS_ERR_INTERNAL;  // the segment bound above
-        e = h2d(set + len * R, a + (r * rl + c0) * R, (c1 - c0) * R, s);
+        e = h2d(set + len * R, run_at(r) + c0 * R, (c1 - c0) * R, s);
         len += c1 - c0;
       }
       void* result = nullptr;
@@ -2502,12 +2562,18 @@ bos_status ooc_impl(const void* in, void* out, uint64_t n, bos_rec rec, const bo
     return BOS_ERR_HIP;
   char* h = static_cast<char*>(hws);
   char* d = static_cast<char*>(dws);
+  // two staging sets of two buffers of cap slots
+  const uint64_t cap = pow2_floor(dl.stage / (4 * size_t(pl.rec + 4)));
+  const std::vector<OocTrip> trips = ooc_trips(pl, cap);
+  OocRuns runs;
   uint32_t attempts = 0;
   uint64_t ovf = kNoOverflow, last_ovf = kNoOverflow;
   bool ok = false;
   uint32_t att = q.attempt;
   for (; att <= std::max(q.max_retries, q.attempt); ++att) {
-    if (ooc_route(pl, q, att, static_cast<const char*>(in), h, hl, d, dl, o) != hipSuccess) return BOS_ERR_HIP;
+    if (ooc_route(pl, q, att, static_cast<const char*>(in), h, hl, d, dl, o, trips, cap, static_cast<char*>(out),
+                  sort ? &runs : nullptr) != hipSuccess)
+      return BOS_ERR_HIP;
     attempts = att + 1;
     uint64_t sw = 0;
     if (d2h(&sw, d + dl.off_status, 8, o->st[0]) != hipSuccess || hipStreamSynchronize(o->st[0]) != hipSuccess)
@@ -2523,20 +2589,18 @@ bos_status ooc_impl(const void* in, void* out, uint64_t n, bos_rec rec, const bo
     fill_report(rep, pl, attempts, last_ovf, 0);
     return BOS_ERR_OVERFLOW;
   }
-  std::vector<uint64_t> boff;
-  if (ooc_block_offsets(pl, d, dl, o->st[0], &boff) != hipSuccess) return BOS_ERR_HIP;
-  if (!sort) {
-    if (ooc_finish(pl, q, att, false, static_cast<char*>(out), h, hl, d, dl, o, boff) != hipSuccess)
-      return BOS_ERR_HIP;
-    fill_report(rep, pl, attempts, ovf, 0);
-    return BOS_OK;
+  if (sort) {
+    st = ooc_merge_runs(pl, runs, static_cast<char*>(out), d, dl, o);
+    fill_report(rep, pl, attempts, ovf, 6 * n * uint64_t(pl.rec));
+    return st;
   }
-  // strip into the tag arrays (dead after routing), then the comparison phase
-  char* a = h + hl.off_tag[0];
-  if (ooc_finish(pl, q, att, true, a, h, hl, d, dl, o, boff) != hipSuccess) return BOS_ERR_HIP;
-  st = ooc_comparison_sort(pl, a, static_cast<char*>(out), d, dl, o);
-  fill_report(rep, pl, attempts, ovf, 6 * n * uint64_t(pl.rec));
-  return st;
+  std::vector<uint64_t> boff;
+  if (ooc_block_offsets(pl, d, dl, o->st[0], &boff) != hipSuccess ||
+      ooc_finish(pl, q, att, static_cast<char*>(out), h + hl.off_rec[(trips.size() - 1) & 1], d, dl, o, boff) !=
+          hipSuccess)
+    return BOS_ERR_HIP;
+  fill_report(rep, pl, attempts, ovf, 0);
+  return BOS_OK;
 }
 
 }  // namespace

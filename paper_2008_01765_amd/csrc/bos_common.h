@@ -121,14 +121,14 @@ struct PassArgs {
   uint32_t pad;
   uint32_t* loads;            // split last pass: real count of every final bin
   // Staged (out-of-core) launches run a chunk of the pass's blocks on copies
-  // of its slots; all zero otherwise.  Blocks keep their global index
-  // (item_off + launch index) for labels, overflow pairs and bins.
-  uint32_t item_off;          // global index of the launch's first block
-  uint32_t staged;            // 1: rec_in/tag_in hold the chunk's input segments (in_h0, in_r0, in_lseg)
-  uint64_t in_h0, in_r0;      // the chunk's first group h and (for a chunk inside one group) first r
-  uint32_t in_lseg, pad2;     // log2 of the buckets per staged input segment
+  // of its slots; all zero otherwise.  The chunk's blocks are those with r in
+  // [in_r0, in_r0 + 2^in_lseg) of the groups h from in_h0 on.  Blocks keep their
+  // global index for labels, overflow pairs and bins.
+  uint32_t staged;            // 1: a staged launch
+  uint32_t in_lseg;           // log2 of the chunk's r per group = of the buckets per staged input segment
+  uint64_t in_h0, in_r0;      // the chunk's first group h and first r
   uint64_t x_off;             // first pass: global index of the first staged input record
-  uint64_t out_slot0;         // global index of the first staged output slot (rec_out, tag_out)
+  uint64_t out_slot0;         // last pass: global index of the first staged output slot (rec_out)
 };
 
 // One instance of a batched comparison-sort launch (tile sort or merge pass).

@@ -1062,8 +1062,8 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   uint16_t* saux = reinterpret_cast<uint16_t*>(srhi + mp);
 
   __builtin_amdgcn_s_setprio(1);  // light_begin / light_end lower it inside the networks
-  const uint32_t tid = threadIdx.x, nthr = blockDim.x;
-  const uint64_t n = a.n, B = a.buckets;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t n = a.n;
   const uint32_t L = a.levels, i0 = a.level0;
   const bool active = FULL || tid < (m >> 4);
   const uint32_t ms = active ? tid / TPM : 0u, lt = active ? tid % TPM : 0u;
@@ -1128,7 +1128,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       const uint64_t bucket = (h << (i0 + klev)) + (uint64_t(S_load) << i0) + r;
       const uint64_t gi = bucket << LZ;
       // staged chunk: input segment S_load holds buckets (S_load, r in0 ..)
-      const uint64_t si = a.staged ? ((((h - a.in_h0) << (i0 + klev)) + (uint64_t(S_load) << a.in_lseg) +
+      const uint64_t si = a.staged ? ((((h - a.in_h0) << (a.in_lseg + klev)) + (uint64_t(S_load) << a.in_lseg) +
                                        (r - a.in_r0)) << LZ)
                                    : gi;
       // A bucket is a set, so its slots take the network's positions in the
@@ -1565,8 +1565,11 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         // last level of a non-last pass: write the 2^klev output buckets
         // (LDS bucket S is output digit bitrev(S)) straight from registers
         T* RO = static_cast<T*>(a.rec_out);
-        const uint64_t ob0 = (h << (i0 + klev)) + (r << klev) + brev_k(S0, klev);
-        const uint64_t ob1 = (h << (i0 + klev)) + (r << klev) + brev_k(S1, klev);
+        const uint64_t og = (h << (i0 + klev)) + (r << klev);
+        const uint64_t ob0 = og + brev_k(S0, klev), ob1 = og + brev_k(S1, klev);
+        // staged chunk: its groups' buckets follow each other
+        const uint64_t so =
+            a.staged ? (og - ((h - a.in_h0) << (a.in_lseg + klev)) - ((r - a.in_r0) << klev)) << LZ : 0ull;
         if (active) {
 #pragma unroll
           for (uint32_t e = 0; e < 16; ++e) {
@@ -1579,8 +1582,8 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
             }
             BOS_TR(0, 10, gi);
             BOS_TR(0, 11, gi);
-            RO[gi - a.out_slot0] = rv[e];
-            a.tag_out[gi - a.out_slot0] = tv[e];
+            RO[gi - so] = rv[e];
+            a.tag_out[gi - so] = tv[e];
           }
         }
       }
@@ -1610,7 +1613,6 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   };
 
   if constexpr (BATCH && (!LAST || SPLIT)) {
-    item0 += a.item_off;
     issue_load(item0, rv, tv);
     finish_load(item0, tv);
     process(item0);
@@ -1621,20 +1623,25 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
     // prefetch registers a pass runs three workgroups per CU at 2^3 Z slots
     // per block, and their interleaving hides the loads better than a
     // register prefetch with fewer workgroups did.
-    // items are global block indices: a staged launch runs blocks
-    // item_off .. item_off + nitems - 1
-    const uint32_t ioff = a.item_off, iend = ioff + nitems;
-    uint32_t item = item0 + ioff;
-    if (item >= iend) return;
+    // global index of the launch's block t: in a staged launch, block t mod
+    // 2^in_lseg of the chunk's group t >> in_lseg
+    auto block_index = [&](uint32_t t) -> uint32_t {
+      if (!a.staged) return t;
+      return uint32_t(((a.in_h0 + (t >> a.in_lseg)) << i0) + a.in_r0 + (t & ((1u << a.in_lseg) - 1u)));
+    };
+    uint32_t t = item0;
+    if (t >= nitems) return;
+    uint32_t item = block_index(t);
     issue_load(item, rv, tv);
     finish_load(item, tv);
     for (;;) {
-      const uint32_t next = item + gridDim.x;
-      const bool has_next = next < iend;
+      const uint32_t next = t + gridDim.x;
+      const bool has_next = next < nitems;
       process(item);
       if constexpr (SPLIT) finish_bins_split(item);
       if (!has_next) break;
-      item = next;
+      t = next;
+      item = block_index(t);
       lds_barrier();  // LDS of the previous block is no longer read
       issue_load(item, rv, tv);
       finish_load(item, tv);
