@@ -48,6 +48,11 @@ hipError_t launch_route_batched(int rec, uint32_t lz, bool first, bool last, con
                                 uint32_t lds, hipStream_t s, bool split);
 hipError_t launch_strip_batched(int rec, const StripSeg* segs, uint32_t nsegs, uint32_t blocks, hipStream_t s);
 hipError_t launch_block_scan(unsigned long long* bsum, unsigned long long* coff, uint32_t nblocks, hipStream_t s);
+uint32_t packed_tag_bytes(uint32_t bits);
+hipError_t launch_pack_slots(int rec, const void* recs, const void* tags, void* out, uint64_t slots, uint32_t lu,
+                             uint32_t bits, hipStream_t s);
+hipError_t launch_unpack_slots(int rec, const void* in, void* recs, void* tags, uint64_t slots, uint32_t lu,
+                               uint32_t bits, hipStream_t s);
 hipError_t launch_chunk_words(const unsigned long long* status, const unsigned long long* counts, uint32_t nb,
                               unsigned long long* words, hipStream_t s);
 hipError_t launch_or_u64(unsigned long long* dst, const unsigned long long* src, hipStream_t s);
@@ -2020,20 +2025,18 @@ struct OocStreams {
 std::mutex g_ooc_mu;
 OocStreams g_ooc[kOocDevices];
 
-// Host workspace: slot arrays 0 and 1 (records, then the two tag arrays; the
-// last trip of a sort leaves its runs in the records of slot array (trips - 1) &
-// 1).
+// Host workspace: slot arrays 0 and 1, of records with packed tags (the last trip
+// leaves bos_orp's bins or bos_sort's runs, records alone, in slot array
+// (trips - 1) & 1).
 struct HostLayout {
-  size_t off_rec[2], off_tag[2], total;
+  size_t off[2], total;
 };
 HostLayout host_layout(const Plan& pl) {
   HostLayout h;
   const size_t slots = size_t(pl.B) * pl.Z;
-  h.off_rec[0] = 0;
-  h.off_rec[1] = align_up(slots * pl.rec);
-  h.off_tag[0] = h.off_rec[1] + align_up(slots * pl.rec);
-  h.off_tag[1] = h.off_tag[0] + align_up(slots * 4);
-  h.total = h.off_tag[1] + align_up(slots * 4);
+  h.off[0] = 0;
+  h.off[1] = align_up(slots * (size_t(pl.rec) + 4));
+  h.total = 2 * h.off[1];
   return h;
 }
 
@@ -2135,8 +2138,8 @@ struct OocTrip {
 // The trips of a plan whose staging buffers hold `cap` slots.  A chunk's passes
 // run back to back on the device, so a trip takes as many passes as 2^K buckets
 // fit the buffers: the link bounds a trip.  A sort of 2^24 records of 8 bytes
-// with 256 MB of staging took 51 ms with its four passes as four trips and 25 ms
-// with two.  After the first trip a chunk is read in
+// with 256 MB of staging took 51 ms with its four passes as four trips, 25 ms with
+// two and 18.5 ms with two of packed slots (launch_pack_slots).  After the first trip a chunk is read in
 // 2^K segments; they stay at 512 KB of records or more (9 us of the link, what a
 // copy costs to start), except that a trip has at least one pass.
 std::vector<OocTrip> ooc_trips(const Plan& pl, uint64_t cap) {
@@ -2155,24 +2158,24 @@ std::vector<OocTrip> ooc_trips(const Plan& pl, uint64_t cap) {
   return trips;
 }
 
-// Input copies of the trip's chunk of blocks [it0, it0 + cb) into the staging
-// buffer (rec, tag).
-hipError_t ooc_copy_in(const Plan& pl, const OocTrip& o, uint64_t it0, const char* in, const char* hin_rec,
-                       const char* hin_tag, char* rec, char* tag, hipStream_t s) {
+// Input copies of the trip's chunk of blocks [it0, it0 + cb) into a staging
+// buffer.
+hipError_t ooc_copy_in(const Plan& pl, const OocTrip& o, uint64_t it0, const char* in, const char* slots, char* d,
+                       hipStream_t s) {
   const size_t R = pl.rec;
   if (o.t0 == 0) {
     // groups [it0 2^K, (it0 + cb) 2^K) hold X[x_lo, x_hi)
     const uint64_t x_lo = ((it0 << o.K) * pl.n) >> pl.L, x_hi = (((it0 + o.cb) << o.K) * pl.n) >> pl.L;
-    return h2d(rec, in + x_lo * R, (x_hi - x_lo) * R, s);
+    return h2d(d, in + x_lo * R, (x_hi - x_lo) * R, s);
   }
   // inside one group (the trip before took every pass that left whole groups
   // in a chunk): 2^K segments of cb buckets
   const uint64_t h0 = it0 >> o.i0, r0 = it0 & ((1ull << o.i0) - 1), seg = o.cb << pl.lz;
+  const size_t sb = R + packed_tag_bytes(pl.L - o.i0);  // bytes of a slot
   hipError_t e = hipSuccess;
   for (uint64_t m = 0; m < (1ull << o.K) && e == hipSuccess; ++m) {
     const uint64_t slot0 = ((h0 << (o.i0 + o.K)) + (m << o.i0) + r0) << pl.lz;
-    e = h2d(rec + m * seg * R, hin_rec + slot0 * R, seg * R, s);
-    if (e == hipSuccess) e = h2d(tag + m * seg * 4, hin_tag + slot0 * 4, seg * 4, s);
+    e = h2d(d + m * seg * sb, slots + slot0 * sb, seg * sb, s);
   }
   return e;
 }
@@ -2208,12 +2211,13 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
     const OocTrip& tr = trips[g];
     const bool fuse = runs && g + 1 == trips.size();
     const uint64_t items = pl.B >> tr.K, nchunks = items / tr.cb, cslots = (tr.cb << tr.K) << pl.lz;
-    const char* hin_rec = hws + hl.off_rec[(g + 1) & 1];
-    const char* hin_tag = hws + hl.off_tag[(g + 1) & 1];
-    char* hout_rec = hws + hl.off_rec[g & 1];
-    char* hout_tag = hws + hl.off_tag[g & 1];
+    const char* hin = hws + hl.off[(g + 1) & 1];
+    char* hout = hws + hl.off[g & 1];
+    // label bits that the next trip's slots keep, bytes of an outgoing slot
+    const uint32_t bits = pl.L - tr.i0 - tr.K;
+    const size_t osb = bits ? R + packed_tag_bytes(bits) : R;
     if (fuse) {
-      runs->base = nchunks == 1 ? out : hout_rec;
+      runs->base = nchunks == 1 ? out : hout;
       runs->stride = cslots;
       runs->len.assign(nchunks, 0);
     }
@@ -2224,8 +2228,7 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
     auto copy_in = [&](uint64_t c) {
       hipStream_t s = nullptr;
       hipError_t x = pipe.start(c, &s);
-      char* d = buf(pipe.b, 0);
-      return x == hipSuccess ? ooc_copy_in(pl, tr, c * tr.cb, in, hin_rec, hin_tag, d, d + cap * R, s) : x;
+      return x == hipSuccess ? ooc_copy_in(pl, tr, c * tr.cb, in, hin, buf(pipe.b, 0), s) : x;
     };
     bool overflowed = false;
     e = copy_in(0);
@@ -2240,6 +2243,11 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
       const int b = pipe.b;
       e = pipe.kernels(&s);
       uint32_t x = 0;  // the buffer that holds the chunk
+      if (g > 0 && e == hipSuccess) {
+        e = launch_unpack_slots(int(R), buf(b, 0), buf(b, 1), buf(b, 1) + cap * R, cslots, lc + pl.lz,
+                                pl.L - tr.i0, s);
+        x = 1;
+      }
       for (uint32_t t = tr.t0; t < tr.t1 && e == hipSuccess; ++t, ++x) {
         const bool first = t == 0, last = t + 1 == pl.P;
         const uint32_t k = pl.klev[t], dl0 = pl.lev0[t] - tr.i0;
@@ -2278,6 +2286,11 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
         e = launch_route(int(R), a, first, last, uint32_t(tr.cb << (tr.K - k)), num_cus(), s, last);
         prof_end(s);
       }
+      if (bits && e == hipSuccess) {
+        e = launch_pack_slots(int(R), buf(b, x), buf(b, x) + cap * R, buf(b, x + 1), cslots,
+                              log2u(trips[g + 1].cb) + pl.lz, bits, s);
+        ++x;
+      }
       const char* res = buf(b, x);
       uint64_t len = cslots;
       const uint32_t klast = pl.klev[pl.P - 1], nblk = uint32_t(tr.cb << (tr.K - klast));
@@ -2312,9 +2325,7 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
         }
       }
       if (e == hipSuccess) e = pipe.out(&s);
-      char* dst = fuse ? runs->base + c * cslots * R : hout_rec + out_slot0 * R;
-      if (e == hipSuccess) e = d2h(dst, res, len * R, s);
-      if (e == hipSuccess && tr.t1 < pl.P) e = d2h(hout_tag + out_slot0 * 4, res + cap * R, len * 4, s);
+      if (e == hipSuccess) e = d2h(fuse ? runs->base + c * cslots * R : hout + out_slot0 * osb, res, len * osb, s);
       if (e == hipSuccess) e = pipe.done();
       if (e != hipSuccess) return e;
     }
@@ -2596,7 +2607,7 @@ bos_status ooc_impl(const void* in, void* out, uint64_t n, bos_rec rec, const bo
   }
   std::vector<uint64_t> boff;
   if (ooc_block_offsets(pl, d, dl, o->st[0], &boff) != hipSuccess ||
-      ooc_finish(pl, q, att, static_cast<char*>(out), h + hl.off_rec[(trips.size() - 1) & 1], d, dl, o, boff) !=
+      ooc_finish(pl, q, att, static_cast<char*>(out), h + hl.off[(trips.size() - 1) & 1], d, dl, o, boff) !=
           hipSuccess)
     return BOS_ERR_HIP;
   fill_report(rep, pl, attempts, ovf, 0);

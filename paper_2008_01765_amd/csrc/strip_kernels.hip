@@ -362,4 +362,78 @@ hipError_t launch_chunk_words(const unsigned long long* status, const unsigned l
   return hipGetLastError();
 }
 
+// Slots of an out-of-core trip as they cross the host link: units of 2^lu slots
+// (a segment of the next trip), each its records followed by its tags, so that a
+// segment is one copy.  A tag keeps the label bits that the next levels read, in
+// TB = 1, 2 or 4 bytes, all ones for a dummy: 9 to 12 bytes a slot of 8-byte
+// records over the link that bounds a trip (2^25 slots with 4 bits left: 302
+// MB in place of 403).  A thread moves four slots; device copies of a chunk, far
+// above the link's rate.
+uint32_t packed_tag_bytes(uint32_t bits) { return bits < 8 ? 1u : bits < 16 ? 2u : 4u; }
+template <typename TB>
+__device__ __forceinline__ uint32_t widen_tag(TB v) {
+  return v == TB(~TB(0)) ? kDummyTag : uint32_t(v);
+}
+template <int R, typename TB, bool PACK>
+__global__ __launch_bounds__(256) void pack_slots_kernel(const char* rec_in, const char* tag_in, char* rec_out,
+                                                         char* tag_out, uint64_t slots, uint32_t lu, uint32_t mask) {
+  using T = typename RecOf<R>::T;
+  typedef TB V __attribute__((ext_vector_type(4)));
+  const uint64_t q = (uint64_t(blockIdx.x) * 256u + threadIdx.x) * 4u;
+  if (q >= slots) return;
+  const uint64_t unit = q >> lu, at = q & ((1ull << lu) - 1ull);
+  const uint64_t r = (unit << lu) * (R + sizeof(TB)) + at * R;
+  const uint64_t t = (unit << lu) * (R + sizeof(TB)) + (uint64_t(R) << lu) + at * sizeof(TB);
+  if constexpr (PACK) {
+    const uint4 w = *reinterpret_cast<const uint4*>(tag_in + q * 4);
+    const T* ri = reinterpret_cast<const T*>(rec_in) + q;
+    T* ro = reinterpret_cast<T*>(rec_out + r);
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) ro[i] = ri[i];
+    // (a dummy's tag is all ones, a label is below 2^31)
+    auto narrow = [&](uint32_t v) { return TB((v & mask) | uint32_t(int32_t(v) >> 31)); };
+    *reinterpret_cast<V*>(rec_out + t) = V{narrow(w.x), narrow(w.y), narrow(w.z), narrow(w.w)};
+  } else {
+    const T* ri = reinterpret_cast<const T*>(rec_in + r);
+    const V ti = *reinterpret_cast<const V*>(rec_in + t);
+    T* ro = reinterpret_cast<T*>(rec_out) + q;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) ro[i] = ri[i];
+    *reinterpret_cast<uint4*>(tag_out + q * 4) =
+        make_uint4(widen_tag(ti[0]), widen_tag(ti[1]), widen_tag(ti[2]), widen_tag(ti[3]));
+  }
+}
+
+template <int R, bool PACK>
+static hipError_t launch_slots(const void* rec_in, const void* tag_in, void* rec_out, void* tag_out, uint64_t slots,
+                               uint32_t lu, uint32_t bits, hipStream_t s) {
+  const uint32_t tb = packed_tag_bytes(bits), mask = (1u << bits) - 1u;
+  const dim3 grid(uint32_t((slots / 4 + 255) / 256)), block(256);
+  const char *ri = static_cast<const char*>(rec_in), *ti = static_cast<const char*>(tag_in);
+  char *ro = static_cast<char*>(rec_out), *to = static_cast<char*>(tag_out);
+  if (tb == 1)
+    hipLaunchKernelGGL((pack_slots_kernel<R, uint8_t, PACK>), grid, block, 0, s, ri, ti, ro, to, slots, lu,
+                       mask);
+  else if (tb == 2)
+    hipLaunchKernelGGL((pack_slots_kernel<R, uint16_t, PACK>), grid, block, 0, s, ri, ti, ro, to, slots, lu,
+                       mask);
+  else
+    hipLaunchKernelGGL((pack_slots_kernel<R, uint32_t, PACK>), grid, block, 0, s, ri, ti, ro, to, slots, lu,
+                       mask);
+  return hipGetLastError();
+}
+
+// slots and 2^lu: multiples of 16 (a bucket holds at least 16 slots), slots a
+// multiple of 2^lu; bits < 32 label bits left.
+hipError_t launch_pack_slots(int rec, const void* recs, const void* tags, void* out, uint64_t slots, uint32_t lu,
+                             uint32_t bits, hipStream_t s) {
+  return rec == 8 ? launch_slots<8, true>(recs, tags, out, nullptr, slots, lu, bits, s)
+                  : launch_slots<16, true>(recs, tags, out, nullptr, slots, lu, bits, s);
+}
+hipError_t launch_unpack_slots(int rec, const void* in, void* recs, void* tags, uint64_t slots, uint32_t lu,
+                               uint32_t bits, hipStream_t s) {
+  return rec == 8 ? launch_slots<8, false>(in, nullptr, recs, tags, slots, lu, bits, s)
+                  : launch_slots<16, false>(in, nullptr, recs, tags, slots, lu, bits, s);
+}
+
 }  // namespace bos

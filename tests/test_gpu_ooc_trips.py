@@ -52,6 +52,17 @@ def test_trips(rec, z, k, times):
     np.testing.assert_array_equal(got, cf.sorted_records(a))
 
 
+def test_tags_of_two_bytes():
+    # 17 levels at the smallest workspace: trips of 8, 3, 3 and 3 levels, so the
+    # slots cross the link with 9, 6 and 3 label bits left (tags of 2, 1 and 1 bytes)
+    n = (1 << 24) + 1
+    a = inputs.records(n, 8, 73)
+    got = _np(bos.orp_host(_host(a), seed=6, z=512, k=3), 8)
+    np.testing.assert_array_equal(got, bos.to_numpy(bos.orp(bos.from_numpy(a), seed=6, z=512)))
+    got = _np(bos.sort_host(_host(a), seed=6, z=512, k=3), 8)
+    np.testing.assert_array_equal(got, cf.sorted_records(a))
+
+
 def test_sort_overflow_retries():
     # Z = 32 overflows often at this size: the overflowed attempts form no runs
     n = 1 << 14
