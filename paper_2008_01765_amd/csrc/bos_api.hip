@@ -66,8 +66,8 @@ hipError_t launch_batch_status(unsigned long long* const* status, unsigned long 
 bool merge_pass_at(int rec, uint64_t n, uint32_t ts, uint32_t p, uint64_t* w_out, bool* four, bool* next_four);
 void* first_pass_samples(int rec, uint64_t n, uint32_t ts, uint64_t* split);
 void merge4_seg(int rec, const void* src, void* dst, uint64_t n, uint64_t* split, uint64_t w, bool gather,
-                bool next_four, M4Seg* sg, uint32_t counts[5]);
-hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, const uint32_t totals[5],
+                bool next_four, M4Seg* sg, uint32_t counts[4]);
+hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, const uint32_t totals[4],
                                  hipStream_t s);
 uint32_t bitonic_tile(int rec);
 hipError_t launch_bitonic(int rec, const void* in, void* out, uint64_t n, void* ws, uint64_t N,
@@ -611,7 +611,7 @@ void* split_smp(const Plan& pl, char* w, uint64_t n) {
 struct MergeRound {
   std::vector<SortSeg> two;
   std::vector<M4Seg> four;
-  uint32_t two_tiles = 0, m4[5] = {0, 0, 0, 0, 0};
+  uint32_t two_tiles = 0, m4[4] = {0, 0, 0, 0};
   void add(int rec, void* src, void* dst, uint64_t n, uint32_t tile, uint32_t pass, uint64_t* split) {
     uint64_t w = 0;
     bool f = false, nf = false;
@@ -628,9 +628,9 @@ struct MergeRound {
     bool pf = true, pnf = false;
     const bool gather = pass > 0 && merge_pass_at(rec, n, tile, pass - 1, &pw, &pf, &pnf) && !pf;
     M4Seg sg;
-    uint32_t c[5];
+    uint32_t c[4];
     merge4_seg(rec, src, dst, n, split, w, gather, nf, &sg, c);
-    for (int k = 0; k < 5; ++k) {
+    for (int k = 0; k < 4; ++k) {
       sg.first[k] = m4[k];
       m4[k] += c[k];
     }
@@ -658,7 +658,7 @@ struct BLaunch {
   uint32_t lz = 0;    // route: log2 Z of the launch
   uint32_t tile = 0;  // tile sort: records per tile
   uint32_t nsegs = 0, blocks = 0, threads = 0, lds = 0, total = 0, job = 0;
-  uint32_t m4[5] = {0, 0, 0, 0, 0};  // four-way pass: blocks of each of its launches
+  uint32_t m4[4] = {0, 0, 0, 0};  // four-way pass: blocks of each of its launches
   size_t tab = 0, aux = 0;
 };
 
@@ -1518,7 +1518,7 @@ bos_status step_impl(bos_job* jobs, uint32_t count, bos_rec rec, const bos_param
   struct Round {
     size_t o_fill = 0, o_strip = 0, o_tile[5] = {0, 0, 0, 0, 0}, o_merge = 0, o_m4 = 0;
     uint32_t nfill = 0, nstrip = 0, ntile[5] = {0, 0, 0, 0, 0}, nmerge = 0, nm4 = 0;
-    uint32_t sblocks = 0, tiles[5] = {0, 0, 0, 0, 0}, mtiles = 0, m4[5] = {0, 0, 0, 0, 0};
+    uint32_t sblocks = 0, tiles[5] = {0, 0, 0, 0, 0}, mtiles = 0, m4[4] = {0, 0, 0, 0};
     std::map<uint32_t, RouteGroup> route;  // key: (mode * 16 + lz) * 16 + levels of the pass
     std::vector<uint32_t> whole;  // jobs routed by the per-job path in this round
   };

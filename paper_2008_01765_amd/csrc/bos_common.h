@@ -144,19 +144,18 @@ struct SortSeg {
 
 // One instance of a batched four-way merge pass (two merge levels in one HBM
 // pass).  Launch k of the pass (0 sample gather, 1 per-sample ranks,
-// 2 workgroup-wide ranks, 3 tile starts, 4 tile merges) gives the instance
+// 2 workgroup-wide ranks, 3 tile merges) gives the instance
 // its blocks first[k] .. first[k] + count - 1 (count 0: not in that launch).
 struct M4Seg {
   const void* src;            // runs of width 2^lw
   void* dst;
   void* smp;                  // samples of src (every 2^kSmpLog-th record)
   void* next_smp;             // the next pass's samples, written by the tiles (null: none)
-  uint64_t* spl;              // sample ranks, then tile starts
+  uint64_t* spl;              // tile starts
   unsigned long long* err;    // the instance's comparison-sort error word
-  uint64_t n, ntf, ng, ntl, total;  // records; tiles per full group, groups, tiles of the last group, all tiles
+  uint64_t n, ntf, ng, ntl;   // records; tiles per full group, groups, tiles of the last group
   uint32_t lw, pad;
-  uint32_t first[5];
-  uint32_t pad2;
+  uint32_t first[4];
 };
 
 // One instance of a batched scan + strip after a split last pass.

@@ -712,30 +712,100 @@ __global__ void sample_gather_kernel(const void* src_, void* smp_, uint64_t n) {
   sample_gather_one<R>(src_, smp_, n, blockIdx.x);
 }
 
-// Ranks of the samples in their group, kSplS<R> samples per thread with all
-// their searches advancing together (one round of loads per halving).  A
-// sample whose rank is a multiple of kSplM opens tile rank/kSplM of its group;
-// for it, spl[4*tile + k] receives the count of run k's samples before it
-// (k != its run j) and spl[4*tile + j] = kSplOwn | its sample index.
+// A sample whose rank in its group is a multiple of kSplM opens tile
+// rank/kSplM of the group.  The rank kernels collect such samples per wave: the
+// sample's index and, for every other run k, the count of run k's samples before
+// it.
+constexpr uint32_t kOpenCap = 128;
+using OpenList = uint32_t[5][kOpenCap];  // counts in runs 0..3 (own: 0), index
+
+// Exact starts spl[4*tile + k] of the tiles that the wave's collected samples
+// open, four lanes a tile.  Samples c-1 and c of run k bracket the opening
+// sample e, so the search covers the records between them.  (As a launch of its
+// own, one thread per tile, this took 9 us of every pass of a small sort.)
+template <int R>
+__device__ __forceinline__ void merge4_starts(const void* src_, const void* smp_, uint64_t n, uint32_t lw,
+                                              uint64_t ntf, uint64_t* spl, const OpenList& open, uint32_t cnt) {
+  using T = typename RecOf<R>::T;
+  constexpr uint32_t LG = kSmpLog<R>;
+  constexpr uint64_t G = 1ull << LG;
+  const T* src = static_cast<const T*>(src_);
+  const uint32_t lane = threadIdx.x & 63u, k = lane & 3u;
+  const uint64_t w = 1ull << lw;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (uint32_t x = lane >> 2; x < cnt; x += 16) {
+    BOS_TR(1, 52, x);
+    const uint32_t i = open[4][x], ck = open[k][x];
+    const uint64_t p = uint64_t(i) << LG, g = p >> (lw + 2), gs = g << (lw + 2);
+    const uint32_t j = uint32_t(p >> lw) & 3u;
+    const uint32_t rank =
+        uint32_t((p - (gs + j * w)) >> LG) + open[0][x] + open[1][x] + open[2][x] + open[3][x];
+    const uint64_t st = gs + k * w < n ? gs + k * w : n, len = n - st < w ? n - st : w;
+    uint64_t lb = k == j ? p - st : ck > 0 ? (ck - 1) * G + 1 : 0;
+    const uint64_t hi = ck * G < len ? ck * G : len;
+    uint32_t cl = k == j || ck == 0 ? 0u : uint32_t(hi - lb);
+    BOS_TR(1, 41, i);
+    const T e = static_cast<const T*>(smp_)[i];
+    while (cl > 0) {
+      const uint32_t half = cl >> 1;
+      BOS_TR(1, 48, st + lb + half);
+      if (precedes(src[st + lb + half], k, e, j)) {
+        lb += half + 1;
+        cl -= half + 1;
+      } else {
+        cl = half;
+      }
+    }
+    BOS_TR(1, 50, 4 * (g * ntf + rank / kSplM) + k);
+    spl[4 * (g * ntf + rank / kSplM) + k] = st + lb;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Adds this lane's sample i (counts c) to the wave's list if it opens a tile;
+// full waves only.  Empties the list first when 64 more might not fit.
+template <int R>
+__device__ __forceinline__ void merge4_open(bool opens, uint32_t i, const uint32_t (&c)[4], const void* src,
+                                            const void* smp, uint64_t n, uint32_t lw, uint64_t ntf, uint64_t* spl,
+                                            OpenList& open, uint32_t& cnt) {
+  if (cnt > kOpenCap - 64u) {
+    merge4_starts<R>(src, smp, n, lw, ntf, spl, open, cnt);
+    cnt = 0;
+  }
+  const unsigned long long m = __ballot(opens);
+  if (opens) {
+    const uint32_t x = cnt + uint32_t(__popcll(m & ((1ull << (threadIdx.x & 63u)) - 1ull)));
+    BOS_TR(1, 52, x);
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) open[k][x] = c[k];
+    open[4][x] = i;
+  }
+  cnt += uint32_t(__popcll(m));
+}
+
+// Ranks of the samples in their group and the starts of the tiles they open,
+// kSplS<R> samples per thread with all their searches advancing together (one
+// round of loads per halving).
 template <int R>
 constexpr uint32_t kSplS = R == 8 ? 4u : 2u;  // (more would spill registers)
-constexpr uint64_t kSplOwn = 1ull << 63;
 template <int R>
-__device__ __forceinline__ void merge4_rank_one(const void* smp_, uint64_t n, uint32_t lw, uint64_t ntf,
-                                                uint64_t* spl, uint64_t blk) {
+__device__ __forceinline__ void merge4_rank_one(const void* src, const void* smp_, uint64_t n, uint32_t lw,
+                                                uint64_t ntf, uint64_t* spl, uint64_t blk) {
   using T = typename RecOf<R>::T;
+  __shared__ OpenList open[4];  // 256 threads
   constexpr uint32_t LG = kSmpLog<R>;
   constexpr uint64_t G = 1ull << LG;
   const T* smp = static_cast<const T*>(smp_);
   const uint64_t ns = (n + G - 1) >> LG, w = 1ull << lw;
-  const uint64_t i0 = (blk * blockDim.x + threadIdx.x) * kSplS<R>;
-  if (i0 >= ns) return;
+  const uint64_t i0 = (blk * 256u + threadIdx.x) * kSplS<R>;
   T e[kSplS<R>];
   uint32_t j[kSplS<R>], own[kSplS<R>], c[kSplS<R>][4], cl[kSplS<R>][4], rb[kSplS<R>][4];
   uint32_t maxl = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kSplS<R>; ++q) {
-    const uint64_t i = i0 + q < ns ? i0 + q : i0;  // past the end: repeat the first (not stored)
+    const uint64_t i = i0 + q < ns ? i0 + q : 0;  // past the end: the first sample (opens nothing)
     const uint64_t p = i << LG, gs = (p >> (lw + 2)) << (lw + 2);
     j[q] = uint32_t(p >> lw) & 3u;
     BOS_TR(1, 41, i);
@@ -769,23 +839,21 @@ __device__ __forceinline__ void merge4_rank_one(const void* smp_, uint64_t n, ui
       }
     }
   }
+  uint32_t cnt = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kSplS<R>; ++q) {
     const uint64_t i = i0 + q;
-    if (i >= ns) continue;
-    const uint64_t p = i << LG, g = p >> (lw + 2);
     const uint32_t r = uint32_t(i - own[q]) + c[q][0] + c[q][1] + c[q][2] + c[q][3];
-    if (r % kSplM != 0) continue;
-    uint64_t* out = spl + 4 * (g * ntf + r / kSplM);
-    BOS_TR(1, 50, 4 * (g * ntf + r / kSplM));
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) out[k] = k == j[q] ? (kSplOwn | i) : uint64_t(c[q][k]);
+    merge4_open<R>(i < ns && r % kSplM == 0, uint32_t(i), c[q], src, smp_, n, lw, ntf, spl, open[threadIdx.x >> 6],
+                   cnt);
   }
+  merge4_starts<R>(src, smp_, n, lw, ntf, spl, open[threadIdx.x >> 6], cnt);
 }
 
 template <int R>
-__global__ void merge4_rank_kernel(const void* smp_, uint64_t n, uint32_t lw, uint64_t ntf, uint64_t* spl) {
-  merge4_rank_one<R>(smp_, n, lw, ntf, spl, blockIdx.x);
+__global__ __launch_bounds__(256) void merge4_rank_kernel(const void* src, const void* smp, uint64_t n, uint32_t lw,
+                                                          uint64_t ntf, uint64_t* spl) {
+  merge4_rank_one<R>(src, smp, n, lw, ntf, spl, blockIdx.x);
 }
 
 // The same ranks when a workgroup's kSplW<R> samples lie in one run (the
@@ -793,18 +861,19 @@ __global__ void merge4_rank_kernel(const void* smp_, uint64_t n, uint32_t lw, ui
 // run k, how many of its samples precede the workgroup's first and last sample
 // (64-ary searches: a round of 64 probes and a ballot narrows the range 64-fold);
 // the samples between those two counts are copied to LDS, where each thread
-// searches for its own samples (in global memory if the window exceeds kSplCap).
+// searches for its own samples, all searches together (in global memory if the
+// window exceeds kSplCap).
 template <int R>
 constexpr uint32_t kSplW = 256u * kSplS<R>;
 template <int R>
 constexpr uint32_t kSplCap = R == 8 ? 2048u : 1024u;
 template <int R>
-__device__ __forceinline__ void merge4_rank_wide_one(const void* smp_, uint64_t n, uint32_t lw, uint64_t ntf,
-                                                     uint64_t* spl, uint64_t blk) {
+__device__ __forceinline__ void merge4_rank_wide_one(const void* src, const void* smp_, uint64_t n, uint32_t lw,
+                                                     uint64_t ntf, uint64_t* spl, uint64_t blk) {
   using T = typename RecOf<R>::T;
   constexpr uint32_t LG = kSmpLog<R>, CAP = kSplCap<R>;
   constexpr uint64_t G = 1ull << LG;
-  __shared__ T win[3 * CAP];
+  __shared__ __align__(16) T win[3 * CAP];
   __shared__ uint32_t wlo[4], wlen[4];
   const T* smp = static_cast<const T*>(smp_);
   const uint64_t ns = (n + G - 1) >> LG, w = 1ull << lw;
@@ -882,122 +951,69 @@ __device__ __forceinline__ void merge4_rank_wide_one(const void* smp_, uint64_t 
     }
   }
   __syncthreads();
+  T e[kSplS<R>];
+  uint32_t c[kSplS<R>][4], len[kSplS<R>][4], any = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kSplS<R>; ++q) {
     const uint64_t i = base + q * 256u + threadIdx.x;
-    if (i > last) continue;
-    BOS_TR(1, 41, i);
-    const T e = smp[i];
-    uint32_t c[4];
-    uint32_t r = uint32_t(i - rb[j]);
+    BOS_TR(1, 41, i <= last ? i : last);
+    e[q] = smp[i <= last ? i : last];
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
-      c[k] = 0;
+      c[q][k] = 0;
+      len[q][k] = k == j ? 0u : wlen[k];
+      any |= len[q][k];
+    }
+  }
+  while (any) {
+    any = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
       if (k == j) continue;
       const uint32_t slot = k < j ? k : k - 1;
       const bool inl = wlen[k] <= CAP;
-      uint32_t l = 0, len = wlen[k];
-      while (len > 0) {
-        const uint32_t half = len >> 1;
-        if (inl) BOS_TR(1, 51, slot * CAP + l + half);
-        else BOS_TR(1, 41, rb[k] + wlo[k] + l + half);
-        const T x = inl ? win[slot * CAP + l + half] : smp[rb[k] + wlo[k] + l + half];
-        if (precedes(x, k, e, j)) {
-          l += half + 1;
-          len -= half + 1;
+#pragma unroll
+      for (uint32_t q = 0; q < kSplS<R>; ++q) {
+        if (len[q][k] == 0) continue;
+        const uint32_t half = len[q][k] >> 1, at = c[q][k] + half;
+        if (inl) BOS_TR(1, 51, slot * CAP + at);
+        else BOS_TR(1, 41, rb[k] + wlo[k] + at);
+        const T x = inl ? win[slot * CAP + at] : smp[rb[k] + wlo[k] + at];
+        if (precedes(x, k, e[q], j)) {
+          c[q][k] = at + 1;
+          len[q][k] -= half + 1;
         } else {
-          len = half;
+          len[q][k] = half;
         }
+        any |= len[q][k];
       }
-      c[k] = wlo[k] + l;
-      r += c[k];
     }
-    if (r % kSplM != 0) continue;
-    uint64_t* out = spl + 4 * (g * ntf + r / kSplM);
-    BOS_TR(1, 50, 4 * (g * ntf + r / kSplM));
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) out[k] = k == j ? (kSplOwn | i) : uint64_t(c[k]);
   }
-}
-
-template <int R>
-__global__ __launch_bounds__(256) void merge4_rank_wide_kernel(const void* smp_, uint64_t n, uint32_t lw,
-                                                               uint64_t ntf, uint64_t* spl) {
-  merge4_rank_wide_one<R>(smp_, n, lw, ntf, spl, blockIdx.x);
-}
-
-// One thread per tile: the tile's exact start in each run.  Samples c-1 and
-// c of run k bracket the opening sample e, so the search covers the records
-// between them; the three searches advance together.
-template <int R>
-__device__ __forceinline__ void merge4_bound_one(const void* src_, const void* smp_, uint64_t n, uint32_t lw,
-                                                 uint64_t total, uint64_t* spl, uint64_t blk) {
-  using T = typename RecOf<R>::T;
-  constexpr uint32_t LG = kSmpLog<R>;
-  constexpr uint64_t G = 1ull << LG;
-  const T* src = static_cast<const T*>(src_);
-  const uint64_t t = blk * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  uint64_t wd[4];
-  uint32_t j = 0, owners = 0;
-  BOS_TR(1, 50, 4 * t);
+  // the lists lie where the windows were (with 10 KB of their own a CU held two
+  // workgroups instead of three)
+  __syncthreads();
+  static_assert(sizeof(win) >= 4 * sizeof(OpenList), "a list per wave");
+  OpenList& open = reinterpret_cast<OpenList*>(win)[threadIdx.x >> 6];
+  uint32_t cnt = 0;
 #pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) {
-    wd[k] = spl[4 * t + k];
-    j = (wd[k] & kSplOwn) ? k : j;
-    owners += (wd[k] & kSplOwn) ? 1u : 0u;
-  }
-  const uint64_t i = wd[j] & ~kSplOwn, p = i << LG, w = 1ull << lw, gs = (p >> (lw + 2)) << (lw + 2);
-  // entries not of the form the rank kernel writes: mark the tile invalid
-  // (the merge kernel skips it) rather than search out of bounds
-  bool ok = owners == 1 && i < ((n + G - 1) >> LG);
-  uint64_t st[4], lb[4], cl[4], maxl = 0;
-#pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) {
-    st[k] = gs + k * w < n ? gs + k * w : n;
-    const uint64_t len = n - st[k] < w ? n - st[k] : w;
-    ok = ok && (k == j || wd[k] <= (len + G - 1) >> LG);
-  }
-  if (!ok) {
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) spl[4 * t + k] = ~0ull;
-    return;
-  }
-  BOS_TR(1, 41, i);
-  const T e = static_cast<const T*>(smp_)[i];
-#pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) {
-    const uint64_t len = n - st[k] < w ? n - st[k] : w, ck = wd[k];
-    lb[k] = k == j ? p - st[k] : ck > 0 ? (ck - 1) * G + 1 : 0;
-    const uint64_t hi = ck * G < len ? ck * G : len;
-    cl[k] = k == j || ck == 0 ? 0 : hi - lb[k];
-    maxl = cl[k] > maxl ? cl[k] : maxl;
-  }
-  while (maxl > 0) {
-    maxl = 0;
+  for (uint32_t q = 0; q < kSplS<R>; ++q) {
+    const uint64_t i = base + q * 256u + threadIdx.x;
+    uint32_t r = uint32_t(i - rb[j]);
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
-      if (cl[k] == 0) continue;
-      const uint64_t half = cl[k] >> 1;
-      BOS_TR(1, 48, st[k] + lb[k] + half);
-      if (precedes(src[st[k] + lb[k] + half], k, e, j)) {
-        lb[k] += half + 1;
-        cl[k] -= half + 1;
-      } else {
-        cl[k] = half;
-      }
-      maxl = cl[k] > maxl ? cl[k] : maxl;
+      c[q][k] += k == j ? 0u : wlo[k];
+      r += c[q][k];
     }
+    merge4_open<R>(i <= last && r % kSplM == 0, uint32_t(i), c[q], src, smp_, n, lw, ntf, spl,
+                   open, cnt);
   }
-  BOS_TR(1, 50, 4 * t);
-#pragma unroll
-  for (uint32_t k = 0; k < 4; ++k) spl[4 * t + k] = st[k] + lb[k];
+  merge4_starts<R>(src, smp_, n, lw, ntf, spl, open, cnt);
 }
 
 template <int R>
-__global__ void merge4_bound_kernel(const void* src_, const void* smp_, uint64_t n, uint32_t lw, uint64_t total,
-                                    uint64_t* spl) {
-  merge4_bound_one<R>(src_, smp_, n, lw, total, spl, blockIdx.x);
+__global__ __launch_bounds__(256) void merge4_rank_wide_kernel(const void* src, const void* smp, uint64_t n,
+                                                               uint32_t lw, uint64_t ntf, uint64_t* spl) {
+  merge4_rank_wide_one<R>(src, smp, n, lw, ntf, spl, blockIdx.x);
 }
 
 // ITEMS outputs, from output dd on, of the merge of A (na records at slot
@@ -1069,6 +1085,11 @@ __device__ __forceinline__ void merge4_tile_one(const void* src_, void* dst_, ui
     ok = ok && st <= a[k] && a[k] <= e[k] && e[k] <= en;
     o0 += a[k] - st;
   }
+  // the opening sample has rank b kSplM: at most that many G-blocks lie before
+  // the tile, less what the three partial ones lack (a start left over from
+  // another pass fails this)
+  constexpr uint64_t G = 1ull << LG;
+  ok = ok && o0 - gs <= b * kSplM * G && o0 - gs + 3 * (G - 1) >= b * kSplM * G;
   // A tile whose bounds break what the splitters guarantee is skipped (no
   // access out of bounds) and reported in the error word, which the host
   // turns into a non-OK status.
@@ -1152,8 +1173,7 @@ __global__ __launch_bounds__(kM4Threads<R>) void merge4_tile_kernel(const void* 
 }
 
 // Batched four-way passes: one table entry (M4Seg) per instance; launch k
-// (0 gather, 1 per-sample ranks, 2 workgroup-wide ranks, 3 tile starts,
-// 4 tiles) gives the instance blocks first[k] .. first[k] + count[k] - 1.
+// (0 gather, 1 per-sample ranks, 2 workgroup-wide ranks, 3 tiles) gives the instance blocks first[k] .. first[k] + count[k] - 1.
 __device__ __forceinline__ uint32_t m4_find(const M4Seg* segs, uint32_t nsegs, uint32_t x, uint32_t k) {
   uint32_t lo = 0, hi = nsegs;
   while (hi - lo > 1) {
@@ -1172,25 +1192,20 @@ __global__ void sample_gather_kernel_b(const M4Seg* segs, uint32_t nsegs) {
   sample_gather_one<R>(sg.src, sg.smp, sg.n, blockIdx.x - sg.first[0]);
 }
 template <int R>
-__global__ void merge4_rank_kernel_b(const M4Seg* segs, uint32_t nsegs) {
+__global__ __launch_bounds__(256) void merge4_rank_kernel_b(const M4Seg* segs, uint32_t nsegs) {
   const M4Seg& sg = segs[m4_find(segs, nsegs, blockIdx.x, 1)];
-  merge4_rank_one<R>(sg.smp, sg.n, sg.lw, sg.ntf, sg.spl, blockIdx.x - sg.first[1]);
+  merge4_rank_one<R>(sg.src, sg.smp, sg.n, sg.lw, sg.ntf, sg.spl, blockIdx.x - sg.first[1]);
 }
 template <int R>
 __global__ __launch_bounds__(256) void merge4_rank_wide_kernel_b(const M4Seg* segs, uint32_t nsegs) {
   const M4Seg& sg = segs[m4_find(segs, nsegs, blockIdx.x, 2)];
-  merge4_rank_wide_one<R>(sg.smp, sg.n, sg.lw, sg.ntf, sg.spl, blockIdx.x - sg.first[2]);
-}
-template <int R>
-__global__ void merge4_bound_kernel_b(const M4Seg* segs, uint32_t nsegs) {
-  const M4Seg& sg = segs[m4_find(segs, nsegs, blockIdx.x, 3)];
-  merge4_bound_one<R>(sg.src, sg.smp, sg.n, sg.lw, sg.total, sg.spl, blockIdx.x - sg.first[3]);
+  merge4_rank_wide_one<R>(sg.src, sg.smp, sg.n, sg.lw, sg.ntf, sg.spl, blockIdx.x - sg.first[2]);
 }
 template <int R>
 __global__ __launch_bounds__(kM4Threads<R>) void merge4_tile_kernel_b(const M4Seg* segs, uint32_t nsegs) {
-  const M4Seg& sg = segs[m4_find(segs, nsegs, blockIdx.x, 4)];
+  const M4Seg& sg = segs[m4_find(segs, nsegs, blockIdx.x, 3)];
   merge4_tile_one<R>(sg.src, sg.dst, sg.n, sg.lw, sg.spl, sg.ntf, sg.ng, sg.ntl, sg.next_smp,
-                     blockIdx.x - sg.first[4], sg.err);
+                     blockIdx.x - sg.first[3], sg.err);
 }
 
 // Tiles of a four-way pass over runs of width 2^lw: per full group (ntf), in
@@ -1532,14 +1547,12 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
         hipLaunchKernelGGL(sample_gather_kernel<R>, dim3(uint32_t((nsmp + 255) / 256)), dim3(256), 0, s, src, smp, n);
       if ((w >> kSmpLog<R>) >= kSplW<R>) {
         hipLaunchKernelGGL(merge4_rank_wide_kernel<R>, dim3(uint32_t((nsmp + kSplW<R> - 1) / kSplW<R>)), dim3(256), 0,
-                           s, smp, n, lw, t.ntf, spl);
+                           s, src, smp, n, lw, t.ntf, spl);
       } else {
         const uint64_t rthreads = (nsmp + kSplS<R> - 1) / kSplS<R>;
-        hipLaunchKernelGGL(merge4_rank_kernel<R>, dim3(uint32_t((rthreads + 255) / 256)), dim3(256), 0, s, smp, n, lw,
-                           t.ntf, spl);
+        hipLaunchKernelGGL(merge4_rank_kernel<R>, dim3(uint32_t((rthreads + 255) / 256)), dim3(256), 0, s, src, smp, n,
+                           lw, t.ntf, spl);
       }
-      hipLaunchKernelGGL(merge4_bound_kernel<R>, dim3(uint32_t((t.total + 255) / 256)), dim3(256), 0, s, src, smp, n,
-                         lw, t.total, spl);
       hipLaunchKernelGGL(merge4_tile_kernel<R>, dim3(uint32_t(t.total)), dim3(kM4Threads<R>), merge_lds, s, src, dst, n,
                          lw, spl, t.ntf, t.ng, t.ntl, next4 ? smp : nullptr, err);
       prof_end(s);
@@ -1620,7 +1633,7 @@ void* first_pass_samples(int rec, uint64_t n, uint32_t ts, uint64_t* split) {
 // whose samples are already written (gather = false: by the tile sort or the
 // previous four-way pass) or not; counts[k] = its blocks in launch k.
 void merge4_seg(int rec, const void* src, void* dst, uint64_t n, uint64_t* split, uint64_t w, bool gather,
-                bool next_four, M4Seg* sg, uint32_t counts[5]) {
+                bool next_four, M4Seg* sg, uint32_t counts[4]) {
   char* region = reinterpret_cast<char*>(split);
   uint32_t lw = 0;
   while ((1ull << lw) < w) ++lw;
@@ -1639,18 +1652,16 @@ void merge4_seg(int rec, const void* src, void* dst, uint64_t n, uint64_t* split
   sg->ntf = t.ntf;
   sg->ng = t.ng;
   sg->ntl = t.ntl;
-  sg->total = t.total;
   sg->lw = lw;
   const bool wide = (w >> lg) >= sw;
   counts[0] = gather ? uint32_t((nsmp + 255) / 256) : 0u;
   counts[1] = wide ? 0u : uint32_t(((nsmp + ss - 1) / ss + 255) / 256);
   counts[2] = wide ? uint32_t((nsmp + sw - 1) / sw) : 0u;
-  counts[3] = uint32_t((t.total + 255) / 256);
-  counts[4] = uint32_t(t.total);
+  counts[3] = uint32_t(t.total);
 }
 
 template <int R>
-static hipError_t merge4_batched_t(const M4Seg* segs, uint32_t nsegs, const uint32_t totals[5], hipStream_t s) {
+static hipError_t merge4_batched_t(const M4Seg* segs, uint32_t nsegs, const uint32_t totals[4], hipStream_t s) {
   static bool attr = false;
   if (!attr) {
     const hipError_t e = allow_lds(merge4_tile_kernel_b<R>);
@@ -1661,16 +1672,15 @@ static hipError_t merge4_batched_t(const M4Seg* segs, uint32_t nsegs, const uint
   if (totals[0]) hipLaunchKernelGGL(sample_gather_kernel_b<R>, dim3(totals[0]), dim3(256), 0, s, segs, nsegs);
   if (totals[1]) hipLaunchKernelGGL(merge4_rank_kernel_b<R>, dim3(totals[1]), dim3(256), 0, s, segs, nsegs);
   if (totals[2]) hipLaunchKernelGGL(merge4_rank_wide_kernel_b<R>, dim3(totals[2]), dim3(256), 0, s, segs, nsegs);
-  if (totals[3]) hipLaunchKernelGGL(merge4_bound_kernel_b<R>, dim3(totals[3]), dim3(256), 0, s, segs, nsegs);
   const uint32_t lds = (kMTile<R> + (kMTile<R> >> 4)) * uint32_t(R);
-  if (totals[4])
-    hipLaunchKernelGGL(merge4_tile_kernel_b<R>, dim3(totals[4]), dim3(kM4Threads<R>), lds, s, segs, nsegs);
+  if (totals[3])
+    hipLaunchKernelGGL(merge4_tile_kernel_b<R>, dim3(totals[3]), dim3(kM4Threads<R>), lds, s, segs, nsegs);
   return hipGetLastError();
 }
 
 // One batched four-way pass over the instances of segs (totals[k]: blocks of
 // launch k summed over them).
-hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, const uint32_t totals[5],
+hipError_t launch_merge4_batched(int rec, const M4Seg* segs, uint32_t nsegs, const uint32_t totals[4],
                                  hipStream_t s) {
   BOS_TRACE_BIND();
   return rec == 8 ? merge4_batched_t<8>(segs, nsegs, totals, s) : merge4_batched_t<16>(segs, nsegs, totals, s);
