@@ -76,16 +76,29 @@ hipError_t launch_route_bt(const PassArgs* segs, const uint32_t* blk_start, uint
   return hipGetLastError();
 }
 
+// The segments of a batched launch have the same klev, so blocks of at least
+// 1024 slots fill their waves as in a single launch: the unguarded kernels (256
+// sorts of 2^10..2^18 records of 16 bytes: the largest middle launch 442 us with
+// lane guards, 304 without).  From Z = 512 up every block does.
+template <int R, int LZ, bool FULL>
+hipError_t launch_route_bf(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs, uint32_t blocks,
+                           uint32_t threads, uint32_t lds, int mode, hipStream_t s) {
+  constexpr int F = FULL ? 16 : 0;
+  switch (mode) {
+    case 0: return launch_route_bt<R, LZ, F | 0>(segs, blk_start, nsegs, blocks, threads, lds, s);
+    case 1: return launch_route_bt<R, LZ, F | 1>(segs, blk_start, nsegs, blocks, threads, lds, s);
+    case 2: return launch_route_bt<R, LZ, F | 2>(segs, blk_start, nsegs, blocks, threads, lds, s);
+    case 6: return launch_route_bt<R, LZ, F | 6>(segs, blk_start, nsegs, blocks, threads, lds, s);
+    default: return launch_route_bt<R, LZ, F | 3>(segs, blk_start, nsegs, blocks, threads, lds, s);
+  }
+}
 template <int R, int LZ>
 hipError_t launch_route_bm(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs, uint32_t blocks,
                            uint32_t threads, uint32_t lds, int mode, hipStream_t s) {
-  switch (mode) {
-    case 0: return launch_route_bt<R, LZ, 0>(segs, blk_start, nsegs, blocks, threads, lds, s);
-    case 1: return launch_route_bt<R, LZ, 1>(segs, blk_start, nsegs, blocks, threads, lds, s);
-    case 2: return launch_route_bt<R, LZ, 2>(segs, blk_start, nsegs, blocks, threads, lds, s);
-    case 6: return launch_route_bt<R, LZ, 6>(segs, blk_start, nsegs, blocks, threads, lds, s);
-    default: return launch_route_bt<R, LZ, 3>(segs, blk_start, nsegs, blocks, threads, lds, s);
-  }
+  if constexpr (LZ < 9)  // 64 lanes may be more than the block's slots fill
+    if (threads <= 64)
+      return launch_route_bf<R, LZ, false>(segs, blk_start, nsegs, blocks, threads, lds, mode, s);
+  return launch_route_bf<R, LZ, true>(segs, blk_start, nsegs, blocks, threads, lds, mode, s);
 }
 
 template <int R, int LZ>
