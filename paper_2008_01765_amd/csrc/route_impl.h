@@ -28,7 +28,9 @@
 // ms for a middle pass, 4.4 TB/s of the 4.9 a copy reaches; 3.91 ms with the
 // compare-and-select networks of v_cmp and v_cndmask); at k = 4 the networks and
 // their LDS exchanges (3.46 ms, 3.8 before the wave-local exchanges), which
-// still makes the fewer passes the faster sort.
+// still makes the fewer passes the faster sort.  The first pass of four levels
+// takes 2.82 ms (the labels, and networks for three levels), the last 4.2 (and a
+// compaction per bin).
 //
 // Obliviousness: every HBM and LDS address is a function of (n, Z, klev,
 // level, block, lane, register) only; labels and records steer register
@@ -91,6 +93,11 @@ __device__ __forceinline__ uint2 dpp(uint2 v) {
 template <uint32_t CTRL>
 __device__ __forceinline__ uint4 dpp(uint4 v) {
   return make_uint4(dpp<CTRL>(v.x), dpp<CTRL>(v.y), dpp<CTRL>(v.z), dpp<CTRL>(v.w));
+}
+
+__device__ __forceinline__ uint2 rec_and(uint2 v, uint32_t m) { return make_uint2(v.x & m, v.y & m); }
+__device__ __forceinline__ uint4 rec_and(uint4 v, uint32_t m) {
+  return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
 }
 
 __device__ __forceinline__ uint32_t brev_k(uint32_t x, uint32_t k) { return k ? (__brev(x) >> (32u - k)) : 0u; }
@@ -1016,8 +1023,7 @@ __device__ __forceinline__ void finish_bins(const PassArgs& a, uint32_t blk, uin
 // R: record bytes; LZ: log2 Z (4..11); MODE bit 0 = first pass, bit 1 = last,
 // bit 2 = split form of the last pass (bins compacted and written to rec_out,
 // then scan + strip; the sorts only), bit 4 = the launch has exactly Z 2^klev / 16 lanes
-// (all of them hold slots, so no lane needs a guard), bit 5 = a first pass whose
-// groups all start on a multiple of 8 elements (no staged loads).
+// (all of them hold slots, so no lane needs a guard).
 // Body of one routing launch.  BATCH = false: a persistent workgroup walks
 // over items blockIdx.x, + gridDim.x, ... (last pass: tickets).  BATCH = true:
 // the workgroup runs the single item `item0` of one instance of a batch.
@@ -1085,42 +1091,48 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
     else
       return e * HALF_LANES + lh;
   };
-  // first pass: elements 8c .. 8c + 7 that lie in [gs, ge), dummies elsewhere
-  // (tag 0 marks a real until label_block fills in its label)
-  auto load_block = [&](uint64_t c, uint64_t gs, uint64_t ge, T* dr, uint32_t* dt) {
+  // first pass: group [gs, ge), of at most Z/2 elements, in registers 0..7 of
+  // its bucket's lanes.  Lane q takes the Philox block c = gs/8 + q, element i of
+  // the block in register i; the elements of block gs/8 + Z/16 (of a group that
+  // starts inside a block) take lane 0's registers that lie before gs.  Other
+  // slots are dummies (tag 0 marks a real until finish_load puts its label there).
+  auto load_group = [&](uint64_t c, uint64_t gs, uint64_t ge, T* dr, uint32_t* dt) {
 #pragma unroll
     for (uint32_t i = 0; i < 8; i += 2) {
-      const uint64_t x = 8u * c + i;
-      const bool r0 = active && x >= gs && x < ge, r1 = active && x + 1 >= gs && x + 1 < ge;
-      if (r0) BOS_TR(0, 3, x);
-      if (r1) BOS_TR(0, 3, x + 1);
+      uint64_t x0 = 8u * c + i, x1 = x0 + 1;
+      x0 += x0 < gs ? 8u * HALF_LANES : 0u;
+      x1 += x1 < gs ? 8u * HALF_LANES : 0u;
+      const bool r0 = active && x0 < ge, r1 = active && x1 < ge;
+      if (r0) BOS_TR(0, 3, x0);
+      if (r1) BOS_TR(0, 3, x1);
       dr[i] = dr[i + 1] = zero_rec<T>();
       if constexpr (R == 8) {
-        if (r0 && r1) {  // one 16-byte load (8-byte aligned: x_off may be odd)
+        if (r0 && r1 && x1 == x0 + 1) {  // one 16-byte load (8-byte aligned: x_off may be odd)
           typedef v4u __attribute__((aligned(8))) v4u8;
-          const v4u t = *reinterpret_cast<const v4u8*>(X + (x - a.x_off));
+          const v4u t = *reinterpret_cast<const v4u8*>(X + (x0 - a.x_off));
           dr[i] = make_uint2(t.x, t.y);
           dr[i + 1] = make_uint2(t.z, t.w);
         } else {
-          if (r0) dr[i] = X[x - a.x_off];
-          if (r1) dr[i + 1] = X[x + 1 - a.x_off];
+          if (r0) dr[i] = X[x0 - a.x_off];
+          if (r1) dr[i + 1] = X[x1 - a.x_off];
         }
       } else {
-        if (r0) dr[i] = X[x - a.x_off];
-        if (r1) dr[i + 1] = X[x + 1 - a.x_off];
+        if (r0) dr[i] = X[x0 - a.x_off];
+        if (r1) dr[i + 1] = X[x1 - a.x_off];
       }
       dt[i] = r0 ? 0u : kDummyTag;
       dt[i + 1] = r1 ? 0u : kDummyTag;
     }
-  };
-  auto label_block = [&](uint64_t c, uint32_t* dt) {
-    const Philox4 ph = philox4x64_10(c, a.attempt, a.seed, 0);
 #pragma unroll
-    for (uint32_t i = 0; i < 8; ++i) {
-      const uint32_t w = uint32_t(ph.v[i >> 1] >> (32u * (i & 1u)));
-      // (a dummy's tag is all ones)
-      dt[i] |= L ? (w >> (32u - L)) : 0u;
+    for (uint32_t i = 8; i < 16; ++i) {
+      dr[i] = zero_rec<T>();
+      dt[i] = kDummyTag;
     }
+  };
+  // label of element i of the Philox block ph
+  auto label = [&](const Philox4& ph, uint32_t i) -> uint32_t {
+    const uint32_t w = uint32_t(ph.v[i >> 1] >> (32u * (i & 1u)));
+    return L ? (w >> (32u - L)) : 0u;
   };
   auto issue_load = [&](uint32_t item, T* dr, uint32_t* dt) {
     const uint64_t r = uint64_t(item) & ((1ull << i0) - 1ull), h = uint64_t(item) >> i0;
@@ -1149,18 +1161,10 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
         dt[e] = active ? a.tag_in[si + s] : kDummyTag;
       }
     } else {
-      // Group j = h*NB + S_load holds X[floor(jn/B), floor((j+1)n/B)), at most
-      // Z/2 elements.  Its slots take the network's positions in the order
-      // that labels best: registers 0..7 of the bucket's lane q hold the
-      // elements of the q-th Philox block of 8 that the group touches, and
-      // registers 8..15 those of block Z/16 + q (only a group of Z/2 elements
-      // that starts inside a block has one, in lane 0).  Other slots are
-      // dummies.
+      // Group j = h*NB + S_load holds X[floor(jn/B), floor((j+1)n/B))
       const uint64_t j = h * NB + S_load;
       const uint64_t gs = (j * n) >> L, ge = ((j + 1) * n) >> L;
-      const uint64_t c = (gs >> 3) + lt % HALF_LANES;
-      load_block(c, gs, ge, dr, dt);
-      load_block(c + HALF_LANES, gs, ge, dr + 8, dt + 8);
+      load_group((gs >> 3) + lt % HALF_LANES, gs, ge, dr, dt);
     }
   };
   // first pass: labels of the loaded reals (word x mod 8 of Philox block x/8)
@@ -1170,8 +1174,15 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
       const uint64_t j = h * NB + S_load;
       const uint64_t gs = (j * n) >> L, ge = ((j + 1) * n) >> L;
       const uint64_t c = (gs >> 3) + lt % HALF_LANES;
-      label_block(c, dt);
-      if (8u * (c + HALF_LANES) < ge) label_block(c + HALF_LANES, dt + 8);
+      const Philox4 ph = philox4x64_10(c, a.attempt, a.seed, 0);
+#pragma unroll
+      for (uint32_t i = 0; i < 8; ++i) dt[i] |= label(ph, i);  // (a dummy's tag is all ones)
+      if (8u * (c + HALF_LANES) < ge) {  // lane 0, a group that starts inside a block
+        const Philox4 p2 = philox4x64_10(c + HALF_LANES, a.attempt, a.seed, 0);
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+          if (8u * c + i < gs && 8u * (c + HALF_LANES) + i < ge) dt[i] = label(p2, i);
+      }
     }
   };
 
@@ -1310,6 +1321,25 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   // where the previous level left this lane's slots (layout B), for HALF
   uint32_t pb0 = 0, pb1 = 0, pbB0 = 0, pbB1 = 0, plB = 0;
 
+  // Level 0 of Algorithm 3.1 needs no network: a bucket starts with at most Z/2
+  // reals, which lie in registers 0..7 of its lanes, so the MergeSplit's lanes
+  // hold them all in Z slots.  Both outputs keep those slots, each with the other
+  // one's reals turned into dummies: registers 0..7 the lower bucket, 8..15 the
+  // upper one, as layout B has them.  It cannot overflow.  (First pass of four
+  // levels at n = 2^28 x 8 B: 3.41 ms with a network, 2.82 so.)
+  constexpr bool LEVEL0 = FIRST && !LAST && HAS_B;
+  auto level0 = [&](uint32_t shift) {
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+      // all ones: upper bucket (or dummy, whose record is zero)
+      const uint32_t up = 0u - (uint32_t(int32_t(tv[e]) >> shift) & 1u);
+      rv[8 + e] = rec_and(rv[e], up);
+      tv[8 + e] = tv[e] | ~up;
+      rv[e] = rec_and(rv[e], ~up);
+      tv[e] |= up;
+    }
+  };
+
   auto process = [&](uint32_t item) {
     const uint64_t r = uint64_t(item) & ((1ull << i0) - 1ull), h = uint64_t(item) >> i0;
     for (uint32_t d = 0; d < klev; ++d) {
@@ -1335,193 +1365,194 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
           }
         }
       }
-      // prefix counts of class-0 reals (bits 0 ..) and dummies (bits FB ..).
-      // tag >> shift (arithmetic) is all ones for a dummy and a real's label
-      // down to its routing bit, below 2^FB while L <= FB; longer labels
-      // (L > FB) are cut to their routing bit first.
-      constexpr uint32_t FB = 31u - LQ;
-      uint32_t pk[16];
-      uint32_t run = 0;
-      uint32_t kf = (1u << FB) | 1u;
-      asm("" : "+v"(kf));  // v_bitop3 takes no literal
-      light_begin();
-      if (L <= FB) {
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          pk[e] = run;
-          const uint32_t x = uint32_t(int32_t(tv[e]) >> shift);
-          run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);  // (x & kf) ^ 1
-        }
+      // lane lt in layout B: q = e << (LQ-4) | lb1 << (LQ-5) | lb0 << (LQ-6) | rest.
+      // Layout B pairs lanes through DPP only for Z >= 1024; below that the
+      // lanes simply take consecutive slots (conflict-free LDS access).
+      const uint32_t lb0 = lt & 1u, lb1 = (lt >> 1) & 1u, rest = lt >> 2;
+      const uint32_t lowB = (LQ >= 11) ? ((lb1 << (LQ - 5)) | (lb0 << (LQ - 6)) | rest) : lt;
+      const uint32_t baseB0 = base0 + lowB + (lowB >> 4), baseB1 = base1 + lowB + (lowB >> 4);
+      if (LEVEL0 && d == 0) {
+        level0(shift);
       } else {
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          pk[e] = run;
-          const uint32_t x = uint32_t(int32_t(tv[e]) >> shift) & (sign_mask(tv[e]) | 1u);
-          run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);
-        }
-      }
-      light_end();
-      uint32_t tot;
-      const uint32_t excl = seg_scan<TPM>(active ? run : 0u, swave, &tot);
-      const uint32_t x = tot & ((1u << FB) - 1u), nd = tot >> FB, y = 2u * Z - x - nd;
-      const uint32_t need = x <= Z ? Z - x : 0u;
-      // marks before slot e: class-0 reals + min(dummies, need); pm[e] is one
-      // less, modulo 2Z.  The count fields are biased (2Z - 1 + need below,
-      // -need above), so that min(dummies, need) = need + min(upper field, 0).
-      const uint32_t bias = excl + (2u * Z - 1u + need) - (need << FB);
-      uint32_t pm[16];
-      light_begin();
-#pragma unroll
-      for (uint32_t e = 0; e < 16; ++e) {
-        const uint32_t pe = bias + pk[e];
-        pm[e] = (pe & ((1u << FB) - 1u)) + (uint32_t(int32_t(pe) >> FB) & sign_mask(pe));
-      }
-      light_end();
-      const uint32_t qm = lane_prefix(pm[0], lt, TPM);
-      if (active) {
-        BOS_TR(0, 6, ms * TPM + lt);
-        spfx[ms * TPM + lt] = qm;
-        if (LAST && lt == 0 && d + 1 == klev) {
-          // bin loads of this block: S0 keeps min(x, Z) reals, S1 the rest of
-          // the pair's reals (exact even when the MergeSplit overflowed)
-          const uint32_t k0 = x < Z ? x : Z;
-          BOS_TR(0, 7, S0);
-          BOS_TR(0, 7, S1);
-          sload[S0] = k0;
-          sload[S1] = x + y - k0;
-        }
-        if (lt == 0 && (x > Z || y > Z)) {
-          const uint64_t G = S0 >> (d + 1);
-          const uint64_t v = brev_k(S0 & ((1u << d) - 1u), d);
-          const uint64_t j = (((h << (klev - d - 1)) + G) << lev) + (r << d) + v;
-          BOS_TR(0, 15, 0);
-          atomicMin(a.status, (unsigned long long)((uint64_t(lev) << 32) | j));
-        }
-      }
-      // -- layout A, q bits 0..3: register pairs
-      lane_stages(rv, tv, pm);
-      // -- layout A, q bit 4: lanes l and l^1 (node = 2 lanes, half = 16)
-      if constexpr (LQ >= 5) {
-        dpp_stage<kDppXor1>(rv, tv, dpp<kDppB1133>(qm), 1u << 27);
-      }
-      // -- layout A, q bit 5: lanes l and l^2 (node = 4 lanes, half = 32)
-      if constexpr (LQ >= 6) {
-        dpp_stage<kDppXor2>(rv, tv, dpp<kDppB2222>(qm) - ((lt & 1u) << 30), 1u << 26);
-      }
-      // lane lt in layout B: q = e << (LQ-4) | lb1 << (LQ-5) | lb0 << (LQ-6) | rest
-      uint32_t baseB0 = 0, baseB1 = 0, lowB = 0;
-      if constexpr (HAS_B) {
-        // A -> LDS (HALF: the first halves)
-        if constexpr (WAVEX) {
-          lowB = lt;
-          // other waves have read what this one handed them after the last level
-          if (d > 0) lds_barrier();
-        } else if (active) {
-#pragma unroll
-          for (uint32_t e = 0; e < 16; ++e) {
-            BOS_TR(0, 4, baseA + e);
-            BOS_TR(0, 5, baseA + e);
-            if constexpr (HALF)
-              shalf[baseA + e] = rec_lo(rv[e]);
-            else
-              srec[baseA + e] = rv[e];
-            stag[baseA + e] = tv[e];
-          }
-        }
-        if constexpr (!WAVEX) lds_group_sync<TPM>();  // layouts A and B of one MergeSplit share its lanes
-        // Layout B pairs lanes through DPP only for Z >= 1024; below that the
-        // lanes simply take consecutive slots (conflict-free LDS access).
-        const uint32_t lb0 = lt & 1u, lb1 = (lt >> 1) & 1u, rest = lt >> 2;
-        lowB = (LQ >= 11) ? ((lb1 << (LQ - 5)) | (lb0 << (LQ - 6)) | rest) : lt;
-        baseB0 = base0 + lowB + (lowB >> 4);
-        baseB1 = base1 + lowB + (lowB >> 4);
-        // HALF: the exchange first (its registers are free before the prefixes load)
-        if constexpr (WAVEX) {
-          wave_exchange([&](uint32_t e) { return slot_a + e; }, [&](uint32_t e) { return slot_b + 66u * e; });
-        } else if constexpr (HALF) {
-          half_finish([&](uint32_t e) { return baseA + e; },
-                      [&](uint32_t e) { return b_index(e, base0, base1, baseB0, baseB1, lowB); },
-                      [] { lds_group_sync<TPM>(); });
-        }
-        // scaled marks prefixes at the node middles (multiples of 16 slots)
-        uint32_t pv[16], pvh[16];
-#pragma unroll
-        for (uint32_t e = 0; e < 16; ++e) {
-          const uint32_t q = e << (LQ - 4);
-          pv[e] = 0;
-          // slot q is the middle of a node of half 2^(LQ-4+ctz(e)), at least 64
-          if (e != 0 && LQ - 4 + __builtin_ctz(e | 16u) >= 6) {
-            if (active) BOS_TR(0, 6, ms * TPM + (q >> 4));
-            pv[e] = active ? spfx[ms * TPM + (q >> 4)] : 0u;
-          }
-          if constexpr (LQ >= 11) {
-            const uint32_t qh = q | (1u << (LQ - 5));
-            if (active) BOS_TR(0, 6, ms * TPM + (qh >> 4));
-            pvh[e] = active ? spfx[ms * TPM + (qh >> 4)] : 0u;
-          } else {
-            pvh[e] = 0;
-          }
-        }
-        if constexpr (!HALF) {
-#pragma unroll
-          for (uint32_t e = 0; e < 16; ++e) {
-            const uint32_t pi = b_index(e, base0, base1, baseB0, baseB1, lowB);
-            if (active) {
-              BOS_TR(0, 4, pi);
-              BOS_TR(0, 5, pi);
-            }
-            rv[e] = active ? srec[pi] : zero_rec<T>();
-            tv[e] = active ? stag[pi] : kDummyTag;
-          }
-        }
-        // -- layout B, q bit LQ-6 (lane bit 0), only for Z = 2048
-        if constexpr (LQ - 6 >= 6) {
-          constexpr uint32_t LH = LQ - 6;
-#pragma unroll
-          for (uint32_t e = 0; e < 16; ++e) {
-            // node: q bits 0..LQ-6 cleared; its middle is 16-aligned
-            const uint32_t qn = (e << (LQ - 4)) | (lb1 << (LQ - 5)) | (1u << LH);
-            BOS_TR(0, 6, ms * TPM + (qn >> 4));
-            const uint32_t m = sign_mask(spfx[ms * TPM + (qn >> 4)] - (rest << (31u - LH)));
-            const T pr = dpp<kDppXor1>(rv[e]);
-            const uint32_t pt = dpp<kDppXor1>(tv[e]);
-            rv[e] = msel(m, pr, rv[e]);
-            tv[e] = msel(m, pt, tv[e]);
-          }
-        }
-        // -- layout B, q bit LQ-5 (lane bit 1), for Z >= 1024
-        if constexpr (LQ - 5 >= 6) {
-          constexpr uint32_t LH = LQ - 5;
-          const uint32_t il = ((lb0 << (LQ - 6)) | rest) << (31u - LH);
-#pragma unroll
-          for (uint32_t e = 0; e < 16; ++e) {
-            const uint32_t m = sign_mask(pvh[e] - il);
-            const T pr = dpp<kDppXor2>(rv[e]);
-            const uint32_t pt = dpp<kDppXor2>(tv[e]);
-            rv[e] = msel(m, pr, rv[e]);
-            tv[e] = msel(m, pt, tv[e]);
-          }
-        }
-        // -- layout B, q bits LQ-4 .. LQ-1: register pairs (those >= 6)
-        // the lane's part of the pair index, scaled for each of the four bits
-        const uint32_t ilB[4] = {lowB << (35u - LQ), lowB << (34u - LQ), lowB << (33u - LQ), lowB << (32u - LQ)};
+        // prefix counts of class-0 reals (bits 0 ..) and dummies (bits FB ..).
+        // tag >> shift (arithmetic) is all ones for a dummy and a real's label
+        // down to its routing bit, below 2^FB while L <= FB; longer labels
+        // (L > FB) are cut to their routing bit first.
+        constexpr uint32_t FB = 31u - LQ;
+        uint32_t pk[16];
+        uint32_t run = 0;
+        uint32_t kf = (1u << FB) | 1u;
+        asm("" : "+v"(kf));  // v_bitop3 takes no literal
         light_begin();
+        if (L <= FB) {
 #pragma unroll
-        for (uint32_t eb = 0; eb < 4; ++eb) {
-          if (LQ - 4 + eb < 6) continue;
-          const uint32_t hb = 1u << eb;
-          const uint32_t il = ilB[eb];
+          for (uint32_t e = 0; e < 16; ++e) {
+            pk[e] = run;
+            const uint32_t x = uint32_t(int32_t(tv[e]) >> shift);
+            run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);  // (x & kf) ^ 1
+          }
+        } else {
 #pragma unroll
-          for (uint32_t es = 0; es < 16; es += 2u * hb) {
-            const uint32_t q = pv[es | hb] - il;
-#pragma unroll
-            for (uint32_t i = 0; i < hb; ++i) {
-              const uint32_t m = sign_mask(q - (i << (31u - eb)));
-              mswap(m, rv[es + i], tv[es + i], rv[es + i + hb], tv[es + i + hb]);
-            }
+          for (uint32_t e = 0; e < 16; ++e) {
+            pk[e] = run;
+            const uint32_t x = uint32_t(int32_t(tv[e]) >> shift) & (sign_mask(tv[e]) | 1u);
+            run += __builtin_amdgcn_bitop3_b32(x, kf, 1u, 0x6A);
           }
         }
         light_end();
+        uint32_t tot;
+        const uint32_t excl = seg_scan<TPM>(active ? run : 0u, swave, &tot);
+        const uint32_t x = tot & ((1u << FB) - 1u), nd = tot >> FB, y = 2u * Z - x - nd;
+        const uint32_t need = x <= Z ? Z - x : 0u;
+        // marks before slot e: class-0 reals + min(dummies, need); pm[e] is one
+        // less, modulo 2Z.  The count fields are biased (2Z - 1 + need below,
+        // -need above), so that min(dummies, need) = need + min(upper field, 0).
+        const uint32_t bias = excl + (2u * Z - 1u + need) - (need << FB);
+        uint32_t pm[16];
+        light_begin();
+#pragma unroll
+        for (uint32_t e = 0; e < 16; ++e) {
+          const uint32_t pe = bias + pk[e];
+          pm[e] = (pe & ((1u << FB) - 1u)) + (uint32_t(int32_t(pe) >> FB) & sign_mask(pe));
+        }
+        light_end();
+        const uint32_t qm = lane_prefix(pm[0], lt, TPM);
+        if (active) {
+          BOS_TR(0, 6, ms * TPM + lt);
+          spfx[ms * TPM + lt] = qm;
+          if (LAST && lt == 0 && d + 1 == klev) {
+            // bin loads of this block: S0 keeps min(x, Z) reals, S1 the rest of
+            // the pair's reals (exact even when the MergeSplit overflowed)
+            const uint32_t k0 = x < Z ? x : Z;
+            BOS_TR(0, 7, S0);
+            BOS_TR(0, 7, S1);
+            sload[S0] = k0;
+            sload[S1] = x + y - k0;
+          }
+          if (lt == 0 && (x > Z || y > Z)) {
+            const uint64_t G = S0 >> (d + 1);
+            const uint64_t v = brev_k(S0 & ((1u << d) - 1u), d);
+            const uint64_t j = (((h << (klev - d - 1)) + G) << lev) + (r << d) + v;
+            BOS_TR(0, 15, 0);
+            atomicMin(a.status, (unsigned long long)((uint64_t(lev) << 32) | j));
+          }
+        }
+        // -- layout A, q bits 0..3: register pairs
+        lane_stages(rv, tv, pm);
+        // -- layout A, q bit 4: lanes l and l^1 (node = 2 lanes, half = 16)
+        if constexpr (LQ >= 5) {
+          dpp_stage<kDppXor1>(rv, tv, dpp<kDppB1133>(qm), 1u << 27);
+        }
+        // -- layout A, q bit 5: lanes l and l^2 (node = 4 lanes, half = 32)
+        if constexpr (LQ >= 6) {
+          dpp_stage<kDppXor2>(rv, tv, dpp<kDppB2222>(qm) - ((lt & 1u) << 30), 1u << 26);
+        }
+        if constexpr (HAS_B) {
+          // A -> LDS (HALF: the first halves)
+          if constexpr (WAVEX) {
+            // other waves have read what this one handed them after the last level
+            if (d > 0) lds_barrier();
+          } else if (active) {
+#pragma unroll
+            for (uint32_t e = 0; e < 16; ++e) {
+              BOS_TR(0, 4, baseA + e);
+              BOS_TR(0, 5, baseA + e);
+              if constexpr (HALF)
+                shalf[baseA + e] = rec_lo(rv[e]);
+              else
+                srec[baseA + e] = rv[e];
+              stag[baseA + e] = tv[e];
+            }
+          }
+          if constexpr (!WAVEX) lds_group_sync<TPM>();  // layouts A and B of one MergeSplit share its lanes
+          // HALF: the exchange first (its registers are free before the prefixes load)
+          if constexpr (WAVEX) {
+            wave_exchange([&](uint32_t e) { return slot_a + e; }, [&](uint32_t e) { return slot_b + 66u * e; });
+          } else if constexpr (HALF) {
+            half_finish([&](uint32_t e) { return baseA + e; },
+                        [&](uint32_t e) { return b_index(e, base0, base1, baseB0, baseB1, lowB); },
+                        [] { lds_group_sync<TPM>(); });
+          }
+          // scaled marks prefixes at the node middles (multiples of 16 slots)
+          uint32_t pv[16], pvh[16];
+#pragma unroll
+          for (uint32_t e = 0; e < 16; ++e) {
+            const uint32_t q = e << (LQ - 4);
+            pv[e] = 0;
+            // slot q is the middle of a node of half 2^(LQ-4+ctz(e)), at least 64
+            if (e != 0 && LQ - 4 + __builtin_ctz(e | 16u) >= 6) {
+              if (active) BOS_TR(0, 6, ms * TPM + (q >> 4));
+              pv[e] = active ? spfx[ms * TPM + (q >> 4)] : 0u;
+            }
+            if constexpr (LQ >= 11) {
+              const uint32_t qh = q | (1u << (LQ - 5));
+              if (active) BOS_TR(0, 6, ms * TPM + (qh >> 4));
+              pvh[e] = active ? spfx[ms * TPM + (qh >> 4)] : 0u;
+            } else {
+              pvh[e] = 0;
+            }
+          }
+          if constexpr (!HALF) {
+#pragma unroll
+            for (uint32_t e = 0; e < 16; ++e) {
+              const uint32_t pi = b_index(e, base0, base1, baseB0, baseB1, lowB);
+              if (active) {
+                BOS_TR(0, 4, pi);
+                BOS_TR(0, 5, pi);
+              }
+              rv[e] = active ? srec[pi] : zero_rec<T>();
+              tv[e] = active ? stag[pi] : kDummyTag;
+            }
+          }
+          // -- layout B, q bit LQ-6 (lane bit 0), only for Z = 2048
+          if constexpr (LQ - 6 >= 6) {
+            constexpr uint32_t LH = LQ - 6;
+#pragma unroll
+            for (uint32_t e = 0; e < 16; ++e) {
+              // node: q bits 0..LQ-6 cleared; its middle is 16-aligned
+              const uint32_t qn = (e << (LQ - 4)) | (lb1 << (LQ - 5)) | (1u << LH);
+              BOS_TR(0, 6, ms * TPM + (qn >> 4));
+              const uint32_t m = sign_mask(spfx[ms * TPM + (qn >> 4)] - (rest << (31u - LH)));
+              const T pr = dpp<kDppXor1>(rv[e]);
+              const uint32_t pt = dpp<kDppXor1>(tv[e]);
+              rv[e] = msel(m, pr, rv[e]);
+              tv[e] = msel(m, pt, tv[e]);
+            }
+          }
+          // -- layout B, q bit LQ-5 (lane bit 1), for Z >= 1024
+          if constexpr (LQ - 5 >= 6) {
+            constexpr uint32_t LH = LQ - 5;
+            const uint32_t il = ((lb0 << (LQ - 6)) | rest) << (31u - LH);
+#pragma unroll
+            for (uint32_t e = 0; e < 16; ++e) {
+              const uint32_t m = sign_mask(pvh[e] - il);
+              const T pr = dpp<kDppXor2>(rv[e]);
+              const uint32_t pt = dpp<kDppXor2>(tv[e]);
+              rv[e] = msel(m, pr, rv[e]);
+              tv[e] = msel(m, pt, tv[e]);
+            }
+          }
+          // -- layout B, q bits LQ-4 .. LQ-1: register pairs (those >= 6)
+          // the lane's part of the pair index, scaled for each of the four bits
+          const uint32_t ilB[4] = {lowB << (35u - LQ), lowB << (34u - LQ), lowB << (33u - LQ), lowB << (32u - LQ)};
+          light_begin();
+#pragma unroll
+          for (uint32_t eb = 0; eb < 4; ++eb) {
+            if (LQ - 4 + eb < 6) continue;
+            const uint32_t hb = 1u << eb;
+            const uint32_t il = ilB[eb];
+#pragma unroll
+            for (uint32_t es = 0; es < 16; es += 2u * hb) {
+              const uint32_t q = pv[es | hb] - il;
+#pragma unroll
+              for (uint32_t i = 0; i < hb; ++i) {
+                const uint32_t m = sign_mask(q - (i << (31u - eb)));
+                mswap(m, rv[es + i], tv[es + i], rv[es + i + hb], tv[es + i + hb]);
+              }
+            }
+          }
+          light_end();
+        }
       }
       // -- hand the level's output to LDS (next level or last-pass finish)
       if (WAVEX && (d + 1 < klev || LAST)) {
