@@ -274,8 +274,11 @@ bos_status make_plan(uint64_t n, int rec, const bos_params& q, bool shuffle_last
   // the last pass is sized as the fused form (whole records in LDS)
   const uint32_t kmid = max_klev(rec, Z, false, pl->generic), klast = max_klev(rec, Z, shuffle_last, true);
   if (kmid == 0 || klast == 0) return BOS_ERR_UNSUPPORTED;
-  // default: 3 levels per pass (a block of 2^3 Z slots leaves LDS for three
-  // workgroups per CU at Z = 512, which outruns fewer, larger passes)
+  // default: 3 levels per pass (a block of 2^3 Z slots leaves LDS for several
+  // workgroups per CU, which outruns fewer, larger passes); 4 for large arrays
+  // of 8-byte records at Z = 512, whose levels exchange within waves (sorts at 3
+  // and 4 levels: 2^16 156 and 167 us, 2^20 357 and 359, 2^24 1.97 and 1.84 ms,
+  // 2^28 33.2 and 31.0; 16-byte records: 2^26 13.5 and 14.0)
   // An explicit k must fit a block of 2^k buckets in LDS and in one
   // workgroup; the tuned or default k is capped at what fits.
   if (q.k > 12) return BOS_ERR_INVALID_ARG;
@@ -284,7 +287,7 @@ bos_status make_plan(uint64_t n, int rec, const bos_params& q, bool shuffle_last
   // so a workgroup holds one MergeSplit's 2Z slots and nothing across levels
   const bool strict = (q.flags & BOS_STRICT) != 0;
   if (strict && q.k > 1) return BOS_ERR_INVALID_ARG;
-  const uint32_t kreq = strict ? 1u : q.k ? q.k : (tuned && te.k && te.z == Z ? te.k : 3u);
+  const uint32_t kreq = strict ? 1u : q.k ? q.k : (tuned && te.k && te.z == Z ? te.k : (rec == 8 && Z == 512u && n >= (1ull << 20)) ? 4u : 3u);
   const uint32_t k = std::min(kreq, kmid);
   pl->k = k;
   pl->tile = q.tile ? q.tile : (tuned && te.tile ? te.tile : kDefaultTile);
