@@ -261,7 +261,6 @@ def bench_ooc(args, torch, bos, inputs):
     del blk, hblk, blk2, hblk2
     res = {"workload": "n=2^%d records of %d B in pinned host memory, Z=%d" % (args.log2n, rec, args.z),
            "device_workspace_GiB": args.ooc_dev_gib, "host_link": rates}
-    bz = None
     for mode, fn in (("orp", bos.orp_host), ("sort", bos.sort_host)):
         kw = {"z": args.z, "k": args.k, "out": host_out, "host_ws": hws, "dev_ws_bytes": dev_bytes}
         if mode == "sort":
@@ -273,18 +272,8 @@ def bench_ooc(args, torch, bos, inputs):
             fn(host_in, seed=args.seed, **kw)
         torch.cuda.synchronize()
         ms = (time.perf_counter() - t0) * 1e3 / args.ooc_steps
-        bz = rep["buckets"] * rep["z"]
-        # bytes over the host link per call: every routing pass reads and writes
-        # the slot arrays (the first reads the n records, the last writes the
-        # bins' records), then the finish or strip reads the bins and writes n
-        # records; the sort's comparison phase reads and writes them twice more
-        link = (n * rec + 2 * (rep["passes"] - 1) * bz * (rec + 4) + bz * (rec + 4) + bz * rec
-                + bz * rec + n * rec)
-        if mode == "sort":
-            link += 4 * n * rec
         res[mode] = {"ms": round(ms, 1), "Melem/s": round(n / ms / 1e3, 1), "passes": rep["passes"],
-                     "attempts": rep["attempts"], "host_link_bytes": int(link),
-                     "host_link_GB/s": round(link / ms / 1e6, 1)}
+                     "attempts": rep["attempts"]}
     res["sorted"] = bool(np.all(np.diff(host_out.numpy()[:, 0].view(np.uint32 if rec == 8 else np.uint64)
                                         .astype(np.float64)) >= 0))
     del host_in, host_out, hws
