@@ -935,13 +935,14 @@ __device__ __forceinline__ void finish_split(const PassArgs& a, uint32_t blk, ui
   }
 }
 
-// Last pass, fused form: sort (or randomly permute) every bin, then strip the
-// dummies and write the bins' reals to their place in the output, found with
+// Last pass, fused form: sort (fin 1), compact (fin 2) or randomly permute (fin
+// 0) every bin, then strip the dummies and write the bins' reals to their place in the output, found with
 // a decoupled look-back over the blocks (block index = ticket order).
 template <int R, int LZ, bool FULL>
 __device__ __forceinline__ void finish_bins(const PassArgs& a, uint32_t blk, uint32_t klev,
                                             typename RecOf<R>::T* srec, uint32_t* stag, uint32_t* srhi,
-                                            uint16_t* saux, uint32_t* sload, uint32_t* soff) {
+                                            uint16_t* saux, uint32_t* sload, uint32_t* soff, uint32_t* spfx,
+                                            uint32_t* swave) {
   using T = typename RecOf<R>::T;
   constexpr uint32_t Z = 1u << LZ, HL = Z >> 4;
   const uint32_t tid = threadIdx.x, NB = 1u << klev, m = Z << klev;
@@ -962,7 +963,13 @@ __device__ __forceinline__ void finish_bins(const PassArgs& a, uint32_t blk, uin
   }
   T outr[16];
   uint32_t load = 0;
-  sort_bins<R, LZ, 0, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, outr, &load);
+  if (a.fin == 2u) {
+    uint32_t tv[16];
+    compact_bin<R, LZ, FULL, true>(srec, stag, spfx, swave, klev, outr, tv);
+    load = active ? sload[S] : 0u;
+  } else {
+    sort_bins<R, LZ, 0, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, outr, &load);
+  }
   // look back for the block's output offset (reals occupy the first slots of
   // every sorted bin).  Wave 0 inspects 64 predecessors per step: it sums
   // their aggregates back to the nearest one whose inclusive prefix is known.
@@ -1688,7 +1695,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
     finish_load(blk, tv);
     process(blk);
     // every final bin (LDS bucket S) now sits in LDS with padded slots
-    finish_bins<R, LZ, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, soff);
+    finish_bins<R, LZ, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, soff, spfx, swave);
   }
   (void)nitems;
 }
