@@ -38,8 +38,8 @@ hipError_t launch_strip(int rec, const void* binned, const uint32_t* loads, unsi
 constexpr uint32_t kScanChunk = 1024;  // block counts per workgroup of the strip's first scan
 bool one_pass_merge(uint64_t n, uint32_t ts);
 hipError_t launch_comparison_sort(int rec, void* buf0, void* buf1, uint64_t n, uint32_t ts, uint64_t* split,
-                                  hipStream_t s, void** result, bool multiway, bool err_clear = false,
-                                  bool one_pass = false);
+                                  hipStream_t s, void** result, const unsigned long long* gate, bool multiway,
+                                  bool err_clear = false, bool one_pass = false);
 uint32_t comparison_sort_hbm_passes(int rec, uint64_t n, uint32_t ts, bool multiway);
 size_t comparison_sort_split_bytes(uint64_t n, int rec);
 unsigned long long* comparison_sort_err_word(uint64_t* split, uint64_t n, int rec);
@@ -1191,9 +1191,9 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
   // comparison sort's error word are then read together, so a sort waits for
   // the device once (waiting for the overflow word before the comparison sort
   // left the device idle for 45 us of every sort).  An overflowed attempt
-  // leaves some of `start` unwritten: the comparison sort orders whatever is
-  // there, in bounds, and the next attempt starts over.  Without BOS_SYNC:
-  // q.attempt alone, its words left on the device.
+  // leaves some of `start` unwritten, with records of earlier calls in it: the
+  // comparison sort's kernels read the overflow word themselves and do nothing.
+  // Without BOS_SYNC: q.attempt alone, its words left on the device.
   unsigned long long* status = reinterpret_cast<unsigned long long*>(w + pl.off_status);
   uint64_t* csplit = reinterpret_cast<uint64_t*>(w + pl.off_split);
   unsigned long long* err = comparison_sort_err_word(csplit, n, pl.rec);
@@ -1204,7 +1204,7 @@ bos_status sort_impl(const void* in, void* out, uint64_t n, bos_rec rec, const b
     hipError_t e = enqueue_routing(pl, in, start, q.seed, att, sort_fin(pl), w, s, -1, split, q.flags, err);
     if (e != hipSuccess) return BOS_ERR_HIP;
     void* result = nullptr;
-    e = launch_comparison_sort(pl.rec, start, other, n, pl.tile, csplit, s, &result, true, true, true);
+    e = launch_comparison_sort(pl.rec, start, other, n, pl.tile, csplit, s, &result, status, true, true, true);
     if (e != hipSuccess) return BOS_ERR_HIP;
     if (result != out) {
       e = hipMemcpyAsync(out, result, n * pl.rec, hipMemcpyDeviceToDevice, s);
@@ -1343,7 +1343,8 @@ bos_status bos_sort_batched(const bos_instance* inst, uint32_t count, bos_rec re
           void* result = nullptr;
           unsigned long long err = 0;
           uint64_t* split = reinterpret_cast<uint64_t*>(j.ws + j.pl.off_split);
-          if (launch_comparison_sort(j.pl.rec, j.start, j.other, j.n, j.pl.tile, split, s, &result, true) !=
+          if (launch_comparison_sort(j.pl.rec, j.start, j.other, j.n, j.pl.tile, split, s, &result,
+                                     reinterpret_cast<unsigned long long*>(j.ws + j.pl.off_status), true) !=
                   hipSuccess ||
               hipMemcpyAsync(&err, err_word(j.pl, j.ws, j.n), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
               hipStreamSynchronize(s) != hipSuccess)
@@ -2332,7 +2333,7 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
           prof_end(s);
           void* r = to;
           if (e == hipSuccess && len > 1) {
-            e = launch_comparison_sort(int(R), to, buf(b, x), len, pl.tile, split, s, &r, true, false, true);
+            e = launch_comparison_sort(int(R), to, buf(b, x), len, pl.tile, split, s, &r, status, true, false, true);
             if (e == hipSuccess) e = launch_or_u64(err, comparison_sort_err_word(split, len, int(R)), s);
           }
           res = static_cast<const char*>(r);
@@ -2465,13 +2466,14 @@ bos_status ooc_merge_runs(const Plan& pl, const OocRuns& runs, char* out, char* 
     rl /= 2;
   if (rl < pl.tile || rl < 2) return BOS_ERR_WORKSPACE;
   const size_t set_bytes = align_up(2 * rl * R) + align_up(comparison_sort_split_bytes(rl, R));
+  const unsigned long long* status = reinterpret_cast<const unsigned long long*>(dws + dl.off_status);
   unsigned long long* err = reinterpret_cast<unsigned long long*>(dws + dl.off_err);
   auto sort_on_device = [&](int sb, uint64_t len, hipStream_t s, void** result) -> hipError_t {
     char* set = dws + dl.off_stage + size_t(sb) * set_bytes;
     uint64_t* split = reinterpret_cast<uint64_t*>(set + align_up(2 * rl * R));
     *result = set;
     if (len <= 1) return hipSuccess;
-    hipError_t e = launch_comparison_sort(R, set, set + rl * R, len, pl.tile, split, s, result, true);
+    hipError_t e = launch_comparison_sort(R, set, set + rl * R, len, pl.tile, split, s, result, status, true);
     if (e == hipSuccess) e = launch_or_u64(err, comparison_sort_err_word(split, len, R), s);
     return e;
   };

@@ -1,0 +1,81 @@
+"""An attempt that overflows is abandoned before anything orders its records.
+
+The comparison sort's addresses depend on the order of the records it is given;
+Section 3.3 allows that for a permuted array, which an aborted attempt is not.
+With the digest build (see test_gpu_trace.py) a call whose only attempt overflows
+must leave equal digests for two different inputs, in the comparison sort's
+buffer too.
+"""
+import numpy as np
+import pytest
+
+import closed_forms as cf
+from paper_2008_01765_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2008_01765_amd import bos  # noqa: E402
+
+SLOTS = 1 << 21  # at least one per thread of the largest launch
+
+
+@pytest.fixture(scope="module")
+def digests():
+    """Calls fn with zeroed digest buffers; returns (status, routing digests,
+    comparison-sort digests)."""
+    with bos.using_library(bos.TRACE_LIB_PATH) as L:
+        bufs = [torch.zeros(SLOTS, dtype=torch.int64, device="cuda") for _ in range(2)]
+        assert L.bos_trace_bind(bufs[0].data_ptr(), bufs[1].data_ptr(), SLOTS) == bos.OK
+
+        def run(fn, *args, **kw):
+            for b in bufs:
+                b.zero_()
+            torch.cuda.synchronize()
+            st = bos.OK
+            try:
+                fn(*args, **kw)
+            except bos.BosError as e:
+                st = e.status
+            torch.cuda.synchronize()
+            return st, bufs[0].clone(), bufs[1].clone()
+
+        yield run
+        L.bos_trace_bind(None, None, 0)
+
+
+# one rank launch (16 tiles), two- and four-way passes from narrow and wide tiles
+@pytest.mark.parametrize("rec", [8, 16])
+@pytest.mark.parametrize("n,tile", [((1 << 14) - 5, 1024), (1 << 16, 1024), ((1 << 17) - 77, 4096),
+                                    ((1 << 19) - 1, 2048), ((1 << 19) - 1, 8192)])
+@pytest.mark.parametrize("sync", [True, False])
+def test_overflowed_sort_orders_nothing(digests, rec, n, tile, sync):
+    # attempt 0 of this seed overflows at Z = 32
+    kw = dict(seed=5, z=32, tile=tile, max_retries=0, min_security_bits=0)
+    got = []
+    for data_seed in (42, 43):
+        t = bos.from_numpy(inputs.records(n, rec, data_seed))
+        st, route, sort = digests(bos.sort, t, sync=sync, out=torch.empty_like(t), **kw)
+        if sync:
+            assert st == bos.OVERFLOW
+        else:
+            assert st == bos.OK and bos.status_word(t, z=32, tile=tile, min_security_bits=0) is not None
+        got.append((route, sort))
+    assert int(torch.count_nonzero(got[0][0])) > 0
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
+
+
+def test_retry_after_an_abandoned_attempt():
+    # the next attempt's comparison sort runs
+    a = inputs.records(1 << 14, 8, 42)
+    want = cf.sorted_records(a)
+    retried = 0
+    for seed in range(11, 17):
+        got, rep = bos.sort(bos.from_numpy(a), seed=seed, z=32, max_retries=30, min_security_bits=0, report=True)
+        retried += rep["attempts"] > 1
+        np.testing.assert_array_equal(bos.to_numpy(got), want)
+    assert retried > 0
