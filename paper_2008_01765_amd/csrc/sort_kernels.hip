@@ -39,15 +39,20 @@ __device__ __forceinline__ void write_sample(void* smp, uint64_t base, uint64_t 
 // The comparison sort of a routing attempt that overflowed does nothing: its
 // buffer holds whatever the attempt left there, records of earlier calls among
 // them, and Section 3.3's argument covers the addresses of a sort of permuted
-// records only.  gate: the attempt's status word, which every lone kernel reads
-// before the first address that depends on a record (next to its first loads,
-// so that the two are waited for together: the same times as without, 158 us for
-// 2^16 records of 8 bytes, 30.0 ms for 2^28); null in the batched and step engines,
-// whose passes run whatever the word says.
+// records only.  gate: the attempt's status word, which every lone kernel loads
+// with its first records and tests (gate_shut) before the first address that
+// depends on a record; null in the batched and step engines, whose passes run
+// whatever the word says.  A vector load, so that it is waited for together with
+// those records (by a scalar load, waited for first, a sort of 2^16 records of 8
+// bytes takes 162 us instead of 156).
 __device__ __forceinline__ unsigned long long gate_word(const unsigned long long* gate) {
   if (gate == nullptr) return kNoOverflow;
   BOS_TR(1, 53, 0);
-  return *gate;
+  return __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ bool gate_shut(unsigned long long gw) {
+  return (uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(gw)))) &
+          uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(gw >> 32))))) != ~0u;
 }
 
 __device__ __forceinline__ uint32_t lpad(uint32_t s) { return s + (s >> 5); }
@@ -220,7 +225,7 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
       if (gi < n) BOS_TR(1, 40, gi);
       v[e] = TileOf<R>::in(gi < n ? B[gi] : max_rec<T>());
     }
-    if (gw != kNoOverflow) return;
+    if (gate_shut(gw)) return;
     tile_to_lds<2>(v, lds, lq);
     __syncthreads();
     tile_from_lds<0>(v, lds, lq);
@@ -248,7 +253,7 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
     if (base + e < n) BOS_TR(1, 40, base + e);
     v[e] = TileOf<R>::in(base + e < n ? B[base + e] : max_rec<T>());
   }
-  if (gw != kNoOverflow) return;
+  if (gate_shut(gw)) return;
   bin_bitonic<TLOG>(v, lds, 0u, lq, true);
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e)
@@ -262,6 +267,7 @@ __device__ __forceinline__ void tile_sort_one(void* buf, uint64_t n, uint64_t ti
 template <int R, uint32_t TLOG>
 __global__ __launch_bounds__(tile_threads<TLOG>()) void tile_sort_reg_kernel(void* buf, uint64_t n, void* smp,
                                                                             const unsigned long long* gate) {
+  __builtin_assume(gate != nullptr);
   tile_sort_one<R, TLOG>(buf, n, blockIdx.x, smp, gate);
 }
 
@@ -315,7 +321,7 @@ __device__ __forceinline__ void merge_partition_one(const void* src_, uint64_t n
 template <int R>
 __global__ void merge_partition_kernel(const void* src, uint64_t n, uint64_t w, uint64_t* split, uint64_t ntiles,
                                        const unsigned long long* gate) {
-  if (gate_word(gate) != kNoOverflow) return;
+  if (gate_shut(gate_word(gate))) return;
   const uint64_t b = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (b < ntiles) merge_partition_one<R>(src, n, w, split, b);
 }
@@ -494,7 +500,7 @@ __device__ __forceinline__ void tile_sort_big_one(void* buf, uint64_t n, uint64_
     const uint64_t gi = t0 + (e << 8) + lq;
     v[e] = TileOf<R>::in(gi < n ? B[gi] : max_rec<T>());
   }
-  if (gw != kNoOverflow) return;
+  if (gate_shut(gw)) return;
   tile_to_lds<2>(v, lds, lq);
   __syncthreads();
   tile_from_lds<0>(v, lds, lq);
@@ -526,6 +532,7 @@ __device__ __forceinline__ void tile_sort_big_one(void* buf, uint64_t n, uint64_
 template <int R, uint32_t TLOG>
 __global__ __launch_bounds__(tile_threads<TLOG>()) void tile_sort_big_kernel(void* buf, uint64_t n, void* smp,
                                                                             const unsigned long long* gate) {
+  __builtin_assume(gate != nullptr);
   tile_sort_big_one<R, TLOG>(buf, n, blockIdx.x, smp, gate);
 }
 
@@ -540,7 +547,7 @@ template <int R>
 __global__ __launch_bounds__(kMThreads<R>) void merge_tile_kernel(const void* src, void* dst, uint64_t n, uint64_t w,
                                                                const uint64_t* split,
                                                                const unsigned long long* gate) {
-  if (gate_word(gate) != kNoOverflow) return;
+  if (gate_shut(gate_word(gate))) return;
   merge_tile_one<R>(src, dst, n, w, split, blockIdx.x);
 }
 
@@ -620,7 +627,7 @@ __global__ __launch_bounds__(256) void merge_rank_kernel(const void* src_, void*
     BOS_TR(1, 40, last);
     const unsigned long long gw = gate_word(gate);
     const T ef = src[base], el = src[last];
-    if (gw != kNoOverflow) return;
+    if (gate_shut(gw)) return;
     constexpr uint32_t KW = kRankRuns / 4;  // runs per wave
     uint32_t lo[KW][2], hi[KW][2];
     bool more = false;
@@ -853,7 +860,7 @@ __device__ __forceinline__ void merge4_rank_one(const void* src, const void* smp
       maxl = cl[q][k] > maxl ? cl[q][k] : maxl;
     }
   }
-  if (gw != kNoOverflow) return;
+  if (gate_shut(gw)) return;
   while (maxl > 0) {
     maxl = 0;
 #pragma unroll
@@ -908,6 +915,7 @@ __device__ __forceinline__ void merge4_rank_wide_one(const void* src, const void
                                                      uint64_t ntf, uint64_t* spl, uint64_t blk,
                                                      const unsigned long long* gate) {
   using T = typename RecOf<R>::T;
+  const unsigned long long gw = gate_word(gate);
   constexpr uint32_t LG = kSmpLog<R>, CAP = kSplCap<R>;
   constexpr uint64_t G = 1ull << LG;
   __shared__ __align__(16) T win[3 * CAP];
@@ -926,7 +934,7 @@ __device__ __forceinline__ void merge4_rank_wide_one(const void* src, const void
     rb[k] = st >> LG;
     sc[k] = uint32_t((len + G - 1) >> LG);
   }
-  if (gate_word(gate) != kNoOverflow) return;
+  if (gate_shut(gw)) return;
   if (threadIdx.x < 64) {
     const uint32_t lane = threadIdx.x;
     BOS_TR(1, 41, base);
@@ -1127,7 +1135,7 @@ __device__ __forceinline__ void merge4_tile_one(const void* src_, void* dst_, ui
     ok = ok && st <= a[k] && a[k] <= e[k] && e[k] <= en;
     o0 += a[k] - st;
   }
-  if (gw != kNoOverflow) return;
+  if (gate_shut(gw)) return;
   // the opening sample has rank b kSplM: at most that many G-blocks lie before
   // the tile, less what the three partial ones lack (a start left over from
   // another pass fails this)
@@ -1545,10 +1553,6 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
   // the tile sort writes the first merge pass's samples when that pass is four-way
   bool have_sample = multiway && ts < n && four_way_next(R, n, ts) && !(one_pass && one_pass_merge(n, ts));
   void* tsmp = have_sample ? smp : nullptr;
-  // (a tile's network is oblivious: its gate only saves an aborted attempt's time,
-  // and a lone tile goes without: 1000 records of 8 bytes 53.2 us with it, 52.6
-  // without)
-  const unsigned long long* tgate = n > ts ? gate : nullptr;
   prof_begin(BOS_K_SORT_TILE, 0, 2 * n * R, s);
   hipError_t e = hipErrorInvalidValue;
   // one tile: the smallest network that holds the n records (1000 records of 8
@@ -1556,12 +1560,12 @@ static hipError_t comparison_sort_t(void* buf0, void* buf1, uint64_t n, uint32_t
   uint32_t tn = ts;
   while (n <= ts && tn > 1024 && n <= tn / 2) tn /= 2;
   switch (tn) {
-    case 1024: e = launch_tile_sort_t<R, 10>(buf0, n, s, tsmp, tgate); break;
-    case 2048: e = launch_tile_sort_t<R, 11>(buf0, n, s, tsmp, tgate); break;
-    case 4096: e = launch_tile_sort_t<R, 12>(buf0, n, s, tsmp, tgate); break;
-    case 8192: e = launch_tile_sort_t<R, 13>(buf0, n, s, tsmp, tgate); break;
+    case 1024: e = launch_tile_sort_t<R, 10>(buf0, n, s, tsmp, gate); break;
+    case 2048: e = launch_tile_sort_t<R, 11>(buf0, n, s, tsmp, gate); break;
+    case 4096: e = launch_tile_sort_t<R, 12>(buf0, n, s, tsmp, gate); break;
+    case 8192: e = launch_tile_sort_t<R, 13>(buf0, n, s, tsmp, gate); break;
     default:
-      if constexpr (R == 8) e = launch_tile_sort_t<R, 14>(buf0, n, s, tsmp, tgate);
+      if constexpr (R == 8) e = launch_tile_sort_t<R, 14>(buf0, n, s, tsmp, gate);
       break;
   }
   prof_end(s);
