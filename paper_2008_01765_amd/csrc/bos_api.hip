@@ -53,6 +53,10 @@ hipError_t launch_pack_slots(int rec, const void* recs, const void* tags, void* 
                              uint32_t bits, hipStream_t s);
 hipError_t launch_unpack_slots(int rec, const void* in, void* recs, void* tags, uint64_t slots, uint32_t lu,
                                uint32_t bits, hipStream_t s);
+hipError_t launch_count_buckets(const void* tags, uint32_t* cnt, uint64_t nbk, uint64_t g0, uint32_t lz, uint32_t i0,
+                                uint32_t K, uint64_t B, hipStream_t s);
+hipError_t launch_count_check(const uint32_t* cnt, uint32_t i0, uint32_t K, uint64_t B, uint32_t Z,
+                              unsigned long long* status, hipStream_t s);
 hipError_t launch_chunk_words(const unsigned long long* status, const unsigned long long* counts, uint32_t nb,
                               unsigned long long* words, hipStream_t s);
 hipError_t launch_or_u64(unsigned long long* dst, const unsigned long long* src, hipStream_t s);
@@ -2195,10 +2199,11 @@ hipError_t ooc_copy_in(const Plan& pl, const OocTrip& o, uint64_t it0, const cha
   return e;
 }
 
-// The sorted runs that an attempt's last trip left in host memory (bos_sort),
-// run r at base + r * stride records.
+// The runs that an attempt's last trip left in host memory (bos_sort), run r at base
+// + r * stride records; sorted = false: stripped, not sorted yet.
 struct OocRuns {
   char* base = nullptr;
+  bool sorted = false;
   uint64_t stride = 0;
   std::vector<uint64_t> len;
 };
@@ -2208,8 +2213,14 @@ struct OocRuns {
 // device.  bos_sort: the last trip's chunks are whole bins, so their reals are
 // stripped and sorted where they are and leave the device as one sorted run per
 // chunk (the lone run of a one-chunk trip goes to `out`); the chunk's real count,
-// which the run's length is, is read after its routing.  An overflowed attempt's
-// runs are not formed.
+// which the run's length is, is read after its routing.  Nothing orders the records
+// of an attempt that overflows: with several chunks in the last trip, the trip
+// before it counts the loads of the buckets that the last levels will form
+// (launch_count_buckets), and the attempt ends there if one exceeds Z.  Where the
+// counters (4 K B bytes) do not fit behind the staging buffers, or K > kCountLevels,
+// the runs leave unsorted and ooc_merge_runs sorts them in a trip of their own.
+// (2^24 records of 8 bytes with 256 MB: 18.4 ms with the counters, 21.7 with runs
+// sorted apart.)
 hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, const char* in, char* hws,
                      const HostLayout& hl, char* dws, const DevLayout& dl, OocStreams* o,
                      const std::vector<OocTrip>& trips, uint64_t cap, char* out, OocRuns* runs) {
@@ -2220,11 +2231,19 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
   unsigned long long* err = reinterpret_cast<unsigned long long*>(dws + dl.off_err);
   uint32_t* loads = reinterpret_cast<uint32_t*>(dws + dl.off_loads);
   hipError_t e = launch_attempt_init(status, 2 + pl.nblocks_last, err, o->st[0]);
+  const OocTrip& lt = trips.back();
+  uint32_t* cnt = nullptr;
+  if (runs && pl.B >> lt.K > lt.cb && lt.K <= kCountLevels) {
+    const size_t at = align_up(4 * cap * (R + 4)), bytes = size_t(lt.K) * pl.B * 4;
+    if (at + bytes <= dl.stage) cnt = reinterpret_cast<uint32_t*>(dws + dl.off_stage + at);
+    if (cnt && e == hipSuccess)
+      e = launch_fill_u64(reinterpret_cast<unsigned long long*>(cnt), bytes / 8, 0ull, o->st[0]);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(o->st[0]);
   if (e != hipSuccess) return e;
   for (size_t g = 0; g < trips.size(); ++g) {
     const OocTrip& tr = trips[g];
-    const bool fuse = runs && g + 1 == trips.size();
+    const bool fuse = runs && g + 1 == trips.size(), count = cnt && g + 2 == trips.size();
     const uint64_t items = pl.B >> tr.K, nchunks = items / tr.cb, cslots = (tr.cb << tr.K) << pl.lz;
     const char* hin = hws + hl.off[(g + 1) & 1];
     char* hout = hws + hl.off[g & 1];
@@ -2234,6 +2253,7 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
     if (fuse) {
       runs->base = nchunks == 1 ? out : hout;
       runs->stride = cslots;
+      runs->sorted = nchunks == 1 || cnt;
       runs->len.assign(nchunks, 0);
     }
     // staging set b: two buffers of `cap` slots, records then tags; a chunk's
@@ -2301,6 +2321,8 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
         e = launch_route(int(R), a, first, last, uint32_t(tr.cb << (tr.K - k)), num_cus(), s, last);
         prof_end(s);
       }
+      if (count && e == hipSuccess)
+        e = launch_count_buckets(buf(b, x) + cap * R, cnt, cslots >> pl.lz, it0 << tr.K, pl.lz, lt.i0, lt.K, pl.B, s);
       if (bits && e == hipSuccess) {
         e = launch_pack_slots(int(R), buf(b, x), buf(b, x) + cap * R, buf(b, x + 1), cslots,
                               log2u(trips[g + 1].cb) + pl.lz, bits, s);
@@ -2332,7 +2354,7 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
           e = launch_strip(int(R), res, loads + (it0 << tr.K), bsum, coff, to, len, nblk, klast, pl.lz, pl.tile, s);
           prof_end(s);
           void* r = to;
-          if (e == hipSuccess && len > 1) {
+          if (e == hipSuccess && runs->sorted && len > 1) {
             e = launch_comparison_sort(int(R), to, buf(b, x), len, pl.tile, split, s, &r, status, true, false, true);
             if (e == hipSuccess) e = launch_or_u64(err, comparison_sort_err_word(split, len, int(R)), s);
           }
@@ -2345,6 +2367,13 @@ hipError_t ooc_route(const Plan& pl, const bos_params& q, uint32_t attempt, cons
       if (e != hipSuccess) return e;
     }
     e = sync3(o);
+    if (count) {
+      uint64_t word = kNoOverflow;
+      if (e == hipSuccess) e = launch_count_check(cnt, lt.i0, lt.K, pl.B, pl.Z, status, o->st[1]);
+      if (e == hipSuccess) e = d2h(&word, status, 8, o->st[1]);
+      if (e == hipSuccess) e = hipStreamSynchronize(o->st[1]);
+      if (e == hipSuccess && word != kNoOverflow) return hipSuccess;  // the caller reads the word too
+    }
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -2450,7 +2479,8 @@ bool host_rec_less(const char* a, const char* b, int R) {
 }
 
 // Merge of the out-of-core sort's runs (Section 3.3 applied to host arrays):
-// every q-th record of each run is a sample, the samples are ordered by (record,
+// runs that are not sorted yet are sorted on the device first; then every q-th
+// record of each run is a sample, the samples are ordered by (record,
 // run, position), every t-th opens an output segment, and each run is cut at each
 // splitter by binary search (a total order, so equal records split consistently).
 // A segment holds at most t q + m (q - 1) <= rl records; its run slices are
@@ -2480,6 +2510,25 @@ bos_status ooc_merge_runs(const Plan& pl, const OocRuns& runs, char* out, char* 
   hipError_t e = hipSuccess;
   const uint64_t m = runs.len.size();
   auto run_at = [&](uint64_t r) { return static_cast<const char*>(runs.base) + r * runs.stride * R; };
+  if (!runs.sorted) {
+    // (a run holds at most cap records, and rl >= cap: a set has no tags)
+    OocPipe pipe{o};
+    for (uint64_t r = 0; r < m; ++r) {
+      const int sb = int(r & 1u);
+      hipStream_t s = nullptr;
+      void* result = nullptr;
+      if (runs.len[r] > rl) return BOS_ERR_INTERNAL;
+      e = pipe.start(r, &s);
+      if (e == hipSuccess) e = h2d(dws + dl.off_stage + size_t(sb) * set_bytes, run_at(r), runs.len[r] * R, s);
+      if (e == hipSuccess) e = pipe.kernels(&s);
+      if (e == hipSuccess) e = sort_on_device(sb, runs.len[r], s, &result);
+      if (e == hipSuccess) e = pipe.out(&s);
+      if (e == hipSuccess) e = d2h(runs.base + r * runs.stride * R, result, runs.len[r] * R, s);
+      if (e == hipSuccess) e = pipe.done();
+      if (e != hipSuccess) return BOS_ERR_HIP;
+    }
+    if (sync3(o) != hipSuccess) return BOS_ERR_HIP;
+  }
   if (m > 1) {
     // samples every q records of every run, q the largest power of two with m q
     // <= rl / 2 (or 1: every record a sample, and segments of exactly t)

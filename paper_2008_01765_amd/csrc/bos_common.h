@@ -9,6 +9,7 @@ namespace bos {
 
 constexpr uint32_t kDummyTag = 0xFFFFFFFFu;  // tag of a dummy slot; real tags are labels < 2^31
 constexpr uint64_t kNoOverflow = ~0ull;      // status word when no MergeSplit overflowed
+constexpr uint32_t kCountLevels = 6;         // levels whose loads are counted ahead (out of core): a lane per value
 constexpr int kMaxThreads = 512;             // threads per routing block
 // Outputs per workgroup of a merge pass: 4096 records of 8 bytes, 2048 of 16
 // (the tile and its staging copy fit four workgroups' LDS per CU either way).

@@ -362,6 +362,69 @@ hipError_t launch_chunk_words(const unsigned long long* status, const unsigned l
   return hipGetLastError();
 }
 
+// Loads of the buckets that the last K <= kCountLevels levels will form, from the
+// slots that enter the first of them (out of core: the trip before the last), so
+// that an overflow of those levels is known before they run.  cnt[d * B + b] counts
+// the reals that level i0 + d puts into its output bucket b; of input bucket g = (m,
+// r), those whose label's low K bits start with the d + 1 bits p go to bucket ((m >>
+// (d + 1)) << (i0 + d + 1)) + (r << (d + 1)) + p.  A wave takes a bucket: lane v
+// counts value v of the K bits by ballots, and the lanes fold in pairs from one level
+// to the next, so that every address is a function of (bucket, K) only.  64 ballots
+// a line of tags at most: under 2 % of the time that the chunk takes on the link.
+__global__ __launch_bounds__(256) void count_buckets_kernel(const uint32_t* tags, uint32_t* cnt, uint64_t nbk,
+                                                            uint64_t g0, uint32_t lz, uint32_t i0, uint32_t K,
+                                                            uint64_t B) {
+  const uint32_t lane = threadIdx.x & 63u, Z = 1u << lz, nv = 1u << K;
+  const uint64_t u = uint64_t(blockIdx.x) * 4u + (threadIdx.x >> 6);
+  if (u >= nbk) return;
+  uint32_t c = 0;
+  for (uint32_t s0 = 0; s0 < Z; s0 += 64) {
+    uint32_t t = kDummyTag;
+    if (s0 + lane < Z) {
+      BOS_TR(0, 2, (u << lz) + s0 + lane);
+      t = tags[(u << lz) + s0 + lane];
+    }
+    t = int32_t(t) < 0 ? kDummyTag : t & (nv - 1u);
+    for (uint32_t v = 0; v < nv; ++v) {
+      const uint32_t n = uint32_t(__popcll(__ballot(t == v)));
+      c += lane == v ? n : 0u;
+    }
+  }
+  const uint64_t g = g0 + u, m = g >> i0, r = g & ((1ull << i0) - 1ull);
+  for (uint32_t d = K; d-- > 0;) {
+    if (lane < (2u << d)) {
+      const uint64_t at = d * B + (((m >> (d + 1)) << (i0 + d + 1)) | (r << (d + 1)) | lane);
+      BOS_TR(0, 54, at);
+      atomicAdd(&cnt[at], c);
+    }
+    c = uint32_t(__shfl(int(c), int((2u * lane) & 63u), 64)) + uint32_t(__shfl(int(c), int((2u * lane + 1u) & 63u), 64));
+  }
+}
+__global__ __launch_bounds__(256) void count_check_kernel(const uint32_t* cnt, uint64_t total, uint64_t B, uint32_t i0,
+                                                          uint32_t Z, unsigned long long* status) {
+  const uint64_t step = uint64_t(gridDim.x) * 256u;
+  for (uint64_t i = uint64_t(blockIdx.x) * 256u + threadIdx.x; i < total; i += step) {
+    BOS_TR(0, 54, i);
+    if (cnt[i] > Z) atomicMin(status, (unsigned long long)(((i0 + i / B) << 32) | ((i % B) >> 1)));
+  }
+}
+// Adds nbk buckets from global bucket g0 (tags as the level before i0 left them).
+hipError_t launch_count_buckets(const void* tags, uint32_t* cnt, uint64_t nbk, uint64_t g0, uint32_t lz, uint32_t i0,
+                                uint32_t K, uint64_t B, hipStream_t s) {
+  BOS_TRACE_BIND();
+  if (K == 0 || K > kCountLevels || nbk == 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(count_buckets_kernel, dim3(uint32_t((nbk + 3) / 4)), dim3(256), 0, s,
+                     static_cast<const uint32_t*>(tags), cnt, nbk, g0, lz, i0, K, B);
+  return hipGetLastError();
+}
+// Folds the first overflow among the counted levels into the overflow word.
+hipError_t launch_count_check(const uint32_t* cnt, uint32_t i0, uint32_t K, uint64_t B, uint32_t Z,
+                              unsigned long long* status, hipStream_t s) {
+  BOS_TRACE_BIND();
+  hipLaunchKernelGGL(count_check_kernel, dim3(1024), dim3(256), 0, s, cnt, K * B, B, i0, Z, status);
+  return hipGetLastError();
+}
+
 // Slots of an out-of-core trip as they cross the host link: units of 2^lu slots
 // (a segment of the next trip), each its records followed by its tags, so that a
 // segment is one copy.  A tag keeps the label bits that the next levels read, in

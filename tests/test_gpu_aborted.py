@@ -69,6 +69,45 @@ def test_overflowed_sort_orders_nothing(digests, rec, n, tile, sync):
     assert torch.equal(got[0][1], got[1][1])
 
 
+def _host(n, data_seed):
+    a = inputs.records(n, 8, data_seed)
+    t = bos.pinned_empty((n, 2), torch.int32)
+    t.numpy()[:] = a.view(np.int32)
+    return a, t
+
+
+# Out of core, four chunks in the last trip: the loads of its levels counted ahead
+# (k = 3), or too many of them and the runs sorted apart (k = 7).  Attempt 0 of these
+# seeds overflows once, in the trip's third chunk (313) or second (431).
+@pytest.mark.parametrize("k", [3, 7])
+@pytest.mark.parametrize("seed", [313, 431])
+def test_overflow_in_a_late_chunk_orders_nothing(digests, seed, k):
+    n, z = 1 << 19, 64
+    got = []
+    for data_seed in (42, 43):
+        _, t = _host(n, data_seed)
+        st, route, sort = digests(bos.sort_host, t, seed=seed, z=z, k=k, max_retries=0, min_security_bits=0)
+        assert st == bos.OVERFLOW
+        got.append((route, sort))
+    assert int(torch.count_nonzero(got[0][0])) > 0
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
+
+
+# seeds whose attempt 0 overflows in the first trip (109), in the last one (99, 313,
+# 431) or not at all
+@pytest.mark.parametrize("k", [3, 7])
+@pytest.mark.parametrize("seed", [99, 109, 313, 314, 431, 432])
+def test_overflow_found_out_of_core(seed, k):
+    n, z, L = 1 << 19, 64, 14
+    a, t = _host(n, 42)
+    want = cf.first_overflow(n, cf.labels(seed, 0, n, L), 1 << L, L, z)
+    got, rep = bos.sort_host(t, seed=seed, z=z, k=k, min_security_bits=0, report=True)
+    assert (rep["first_overflow_level"], rep["first_overflow_pair"]) == want
+    assert rep["attempts"] == (1 if want[0] < 0 else 2)
+    np.testing.assert_array_equal(got.numpy().view(np.uint32), cf.sorted_records(a))
+
+
 def test_retry_after_an_abandoned_attempt():
     # the next attempt's comparison sort runs
     a = inputs.records(1 << 14, 8, 42)
