@@ -966,6 +966,7 @@ __device__ __forceinline__ void finish_bins(const PassArgs& a, uint32_t blk, uin
   if (a.fin == 2u) {
     uint32_t tv[16];
     compact_bin<R, LZ, FULL, true>(srec, stag, spfx, swave, klev, outr, tv);
+    if (active) BOS_TR(0, 7, S);
     load = active ? sload[S] : 0u;
   } else {
     sort_bins<R, LZ, 0, FULL>(a, blk, klev, srec, stag, srhi, saux, sload, outr, &load);

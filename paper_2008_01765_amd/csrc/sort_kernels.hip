@@ -459,12 +459,16 @@ __device__ __forceinline__ void subtile_cross(typename TileOf<R>::E (&v)[16], ty
                                               uint32_t psub, bool mirror) {
   __syncthreads();  // the LDS regions are free (the last network stage read them)
 #pragma unroll
-  for (uint32_t e = 0; e < 16; ++e) s[sub * SP + 17u * lq + e] = v[e].r;
+  for (uint32_t e = 0; e < 16; ++e) {
+    BOS_TR(1, 4, sub * SP + 17u * lq + e);
+    s[sub * SP + 17u * lq + e] = v[e].r;
+  }
   __syncthreads();
   const uint32_t plq = mirror ? 255u - lq : lq;
   const bool keep_min = sub < psub;
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
+    BOS_TR(1, 4, psub * SP + 17u * plq + (mirror ? 15u - e : e));
     const typename TileOf<R>::E p{s[psub * SP + 17u * plq + (mirror ? 15u - e : e)]};
     const bool take = e_less(p, v[e]) == keep_min;
     v[e] = e_pick(take, p, v[e]);
@@ -492,12 +496,14 @@ __device__ __forceinline__ void tile_sort_big_one(void* buf, uint64_t n, uint64_
   const uint32_t tid = threadIdx.x, sub = tid / 256u, lq = tid % 256u;
   __builtin_amdgcn_s_setprio(1);  // lowered inside the network's selects
   const uint64_t t0 = (tile << TLOG) + uint64_t(sub) * kSub;
-  const typename TileOf<R>::L lds{s + sub * kSubPad};
+  typename TileOf<R>::L lds{s + sub * kSubPad};
+  lds.tw = 1;
   typename TileOf<R>::E v[16];
   // layout Q loads and stores, as the 4096-record tiles
 #pragma unroll
   for (uint32_t e = 0; e < 16; ++e) {
     const uint64_t gi = t0 + (e << 8) + lq;
+    if (gi < n) BOS_TR(1, 40, gi);
     v[e] = TileOf<R>::in(gi < n ? B[gi] : max_rec<T>());
   }
   if (gate_shut(gw)) return;
@@ -523,8 +529,12 @@ __device__ __forceinline__ void tile_sort_big_one(void* buf, uint64_t n, uint64_
   for (uint32_t e = 0; e < 16; ++e) {
     const uint64_t gi = t0 + (e << 8) + lq;
     if (gi < n) {
+      BOS_TR(1, 40, gi);
       B[gi] = TileOf<R>::out(v[e]);
-      if (smp && (gi & ((1ull << kSmpLog<R>) - 1)) == 0) static_cast<T*>(smp)[gi >> kSmpLog<R>] = TileOf<R>::out(v[e]);
+      if (smp && (gi & ((1ull << kSmpLog<R>) - 1)) == 0) {
+        BOS_TR(1, 41, gi >> kSmpLog<R>);
+        static_cast<T*>(smp)[gi >> kSmpLog<R>] = TileOf<R>::out(v[e]);
+      }
     }
   }
 }

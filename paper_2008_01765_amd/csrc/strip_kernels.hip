@@ -346,7 +346,10 @@ __global__ __launch_bounds__(256) void chunk_words_kernel(const unsigned long lo
                                                           unsigned long long* words) {
   __shared__ unsigned long long wsum[4];
   unsigned long long t = 0;
-  for (uint32_t i = threadIdx.x; i < nb; i += 256) t += counts[i];
+  for (uint32_t i = threadIdx.x; i < nb; i += 256) {
+    BOS_TR(0, 14, i);
+    t += counts[i];
+  }
 #pragma unroll
   for (uint32_t o = 32; o > 0; o >>= 1) t += __shfl_down(t, o, 64);
   if ((threadIdx.x & 63u) == 0) wsum[threadIdx.x >> 6] = t;
@@ -358,6 +361,7 @@ __global__ __launch_bounds__(256) void chunk_words_kernel(const unsigned long lo
 }
 hipError_t launch_chunk_words(const unsigned long long* status, const unsigned long long* counts, uint32_t nb,
                               unsigned long long* words, hipStream_t s) {
+  BOS_TRACE_BIND();
   hipLaunchKernelGGL(chunk_words_kernel, dim3(1), dim3(256), 0, s, status, counts, nb, words);
   return hipGetLastError();
 }
@@ -447,6 +451,9 @@ __global__ __launch_bounds__(256) void pack_slots_kernel(const char* rec_in, con
   const uint64_t unit = q >> lu, at = q & ((1ull << lu) - 1ull);
   const uint64_t r = (unit << lu) * (R + sizeof(TB)) + at * R;
   const uint64_t t = (unit << lu) * (R + sizeof(TB)) + (uint64_t(R) << lu) + at * sizeof(TB);
+  BOS_TR(0, 55, q);  // four slots
+  BOS_TR(0, 56, r);  // their packed records
+  BOS_TR(0, 57, t);  // and tags
   if constexpr (PACK) {
     const uint4 w = *reinterpret_cast<const uint4*>(tag_in + q * 4);
     const T* ri = reinterpret_cast<const T*>(rec_in) + q;
@@ -470,6 +477,7 @@ __global__ __launch_bounds__(256) void pack_slots_kernel(const char* rec_in, con
 template <int R, bool PACK>
 static hipError_t launch_slots(const void* rec_in, const void* tag_in, void* rec_out, void* tag_out, uint64_t slots,
                                uint32_t lu, uint32_t bits, hipStream_t s) {
+  BOS_TRACE_BIND();
   const uint32_t tb = packed_tag_bytes(bits), mask = (1u << bits) - 1u;
   const dim3 grid(uint32_t((slots / 4 + 255) / 256)), block(256);
   const char *ri = static_cast<const char*>(rec_in), *ti = static_cast<const char*>(tag_in);

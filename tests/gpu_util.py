@@ -1,4 +1,6 @@
 """Helpers shared by the GPU tests (no method arithmetic here)."""
+import contextlib
+
 import numpy as np
 
 
@@ -60,3 +62,32 @@ def torch_is_sorted(t):
         return True
     ok = (k[1:] > k[:-1]) | ((k[1:] == k[:-1]) & (p[1:] >= p[:-1]))
     return bool(ok.all())
+
+
+@contextlib.contextmanager
+def trace_digests(slots):
+    """With the digest build (see test_gpu_trace.py) loaded: a function that
+    calls fn with zeroed digest buffers of `slots` slots and returns (status,
+    routing digests, comparison-sort digests)."""
+    import torch
+    from paper_2008_01765_amd import bos
+    with bos.using_library(bos.TRACE_LIB_PATH) as L:
+        bufs = [torch.zeros(slots, dtype=torch.int64, device="cuda") for _ in range(2)]
+        assert L.bos_trace_bind(bufs[0].data_ptr(), bufs[1].data_ptr(), slots) == bos.OK
+
+        def run(fn, *args, **kw):
+            for b in bufs:
+                b.zero_()
+            torch.cuda.synchronize()
+            st = bos.OK
+            try:
+                fn(*args, **kw)
+            except bos.BosError as e:
+                st = e.status
+            torch.cuda.synchronize()
+            return st, bufs[0].clone(), bufs[1].clone()
+
+        try:
+            yield run
+        finally:
+            L.bos_trace_bind(None, None, 0)

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import closed_forms as cf
+from gpu_util import trace_digests
 from paper_2008_01765_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -25,26 +26,8 @@ SLOTS = 1 << 21  # at least one per thread of the largest launch
 
 @pytest.fixture(scope="module")
 def digests():
-    """Calls fn with zeroed digest buffers; returns (status, routing digests,
-    comparison-sort digests)."""
-    with bos.using_library(bos.TRACE_LIB_PATH) as L:
-        bufs = [torch.zeros(SLOTS, dtype=torch.int64, device="cuda") for _ in range(2)]
-        assert L.bos_trace_bind(bufs[0].data_ptr(), bufs[1].data_ptr(), SLOTS) == bos.OK
-
-        def run(fn, *args, **kw):
-            for b in bufs:
-                b.zero_()
-            torch.cuda.synchronize()
-            st = bos.OK
-            try:
-                fn(*args, **kw)
-            except bos.BosError as e:
-                st = e.status
-            torch.cuda.synchronize()
-            return st, bufs[0].clone(), bufs[1].clone()
-
+    with trace_digests(SLOTS) as run:
         yield run
-        L.bos_trace_bind(None, None, 0)
 
 
 # one rank launch (16 tiles), two- and four-way passes from narrow and wide tiles
