@@ -1378,15 +1378,19 @@ bos_status bos_sort_batched(const bos_instance* inst, uint32_t count, bos_rec re
 //
 // A step is a budget of device work, handed out in array order (the caller
 // puts its oldest job first).  The first unfinished job always runs at least
-// one phase (several if they are cheap: up to kStepMinQuantum); later jobs
-// backfill a budget of twice that, capped at kStepBackfillCap, each as many
-// phases as fit, so small requests run several phases next to one phase of a
-// large request, large requests keep their order, and a large head request
-// keeps at least two thirds of the device (its latency sets the tail).  The phase cost model is
-// n + kStepFixed records (kStepFixed stands for the launch overhead of a
-// phase, which the jobs of a sub-round share: 48 requests of 2^12..2^22 records of
-// 16 bytes took 17.5 ms at 2^17 records and a quantum of 2^21, 16.1 ms at 2^13 and
-// 2^22; p99 at half load the same).  The overflow check of an attempt is
+// one phase (several if they are cheap: up to the quantum); later jobs backfill a
+// budget of twice the larger of that phase and the quantum, capped at
+// kStepBackfillCap, each as many phases as fit, so small requests run several
+// phases next to one phase of a large request, large requests keep their order,
+// and a head request of 2^24 records keeps two thirds of the device (its latency
+// sets the tail).  The phase cost model is n + kStepFixed records (kStepFixed stands
+// for the launch overhead of a phase, which the jobs of a sub-round share).  The
+// quantum is kStepMinQuantum, and twice that, which makes the budget its cap, from
+// kStepDeep unfinished jobs on: a long step holds up the next arrival, a short one
+// leaves launches with few jobs.  Requests of 2^12..2^22 records of 16 bytes: at
+// half load p50 0.36 and p99 2.27 ms (always 2^22: 0.37 and 2.41); 48 at once 14.9
+// ms (always 2^22: 14.8; always 2^21: 14.9); 12 of 2^12..2^20 at once 1.45 ms
+// (1.45; 1.88).  The overflow check of an attempt is
 // speculative: a job that finished its routing passes goes on to the
 // comparison sort in the same step, and the status words of those jobs are
 // read once at the end of the step; a job whose attempt overflowed goes back
@@ -1394,7 +1398,8 @@ bos_status bos_sort_batched(const bos_instance* inst, uint32_t count, bos_rec re
 
 constexpr uint32_t kStepRounds = 32;           // sub-rounds per step at most
 constexpr uint64_t kStepFixed = 1ull << 13;    // launch overhead, in records
-constexpr uint64_t kStepMinQuantum = 1ull << 22;
+constexpr uint64_t kStepMinQuantum = 1ull << 21;
+constexpr uint32_t kStepDeep = 4;
 constexpr uint64_t kStepBackfillCap = 1ull << 23;
 
 size_t step_round_bytes(uint32_t count) {
@@ -1480,7 +1485,7 @@ bos_status step_impl(bos_job* jobs, uint32_t count, bos_rec rec, const bos_param
   std::vector<Plan> plans(count);
   std::vector<uint32_t> merges(count, 0), allowed(count, 0);
   std::vector<char> routed(count, 0);  // finished an attempt's routing in this step
-  uint64_t quantum = kStepMinQuantum;
+  uint32_t live = 0;  // unfinished jobs
   for (uint32_t i = 0; i < count; ++i) {
     bos_job& j = jobs[i];
     if (j.phase == BOS_PHASE_DONE) continue;
@@ -1495,8 +1500,10 @@ bos_status step_impl(bos_job* jobs, uint32_t count, bos_rec rec, const bos_param
     if (!j.ws || j.ws_bytes < plans[i].total) return BOS_ERR_WORKSPACE;
     merges[i] = comparison_sort_hbm_passes(R, j.n, plans[i].tile, true);
     if (j.phase > plans[i].P + merges[i] + (ctx ? 1u : 0u)) return BOS_ERR_INVALID_ARG;
+    ++live;
   }
   {
+    const uint64_t quantum = live >= kStepDeep ? 2 * kStepMinQuantum : kStepMinQuantum;
     bool head = true;
     uint64_t left = 0;
     for (uint32_t i = 0; i < count; ++i) {
@@ -1507,9 +1514,8 @@ bos_status step_impl(bos_job* jobs, uint32_t count, bos_rec rec, const bos_param
       if (remaining == 0) continue;  // every phase enqueued (pipelined), awaiting its result
       uint64_t k;
       if (head) {
-        quantum = std::max(quantum, c);
-        k = std::max<uint64_t>(1, kStepMinQuantum / c);
-        left = std::min<uint64_t>(2 * quantum, kStepBackfillCap);
+        k = std::max<uint64_t>(1, quantum / c);
+        left = std::min<uint64_t>(2 * std::max(quantum, c), kStepBackfillCap);
         head = false;
       } else {
         k = left / c;
