@@ -1061,6 +1061,7 @@ __device__ __forceinline__ void route_run(const PassArgs& a, uint32_t nitems, ui
   // there, so half of its slots move; layouts change word by word in the
   // wave's own kXWords words, with no barrier.
   constexpr bool WAVEX = HAS_B && TPM == 64 && (!LAST || SPLIT);
+  static_assert(!WAVEX || FULL, "a wave without slots would index past the block's LDS words");
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t klev = a.klev, NB = 1u << klev, m = Z << klev, mp = NB * ZP;
   T* srec = reinterpret_cast<T*>(smem);

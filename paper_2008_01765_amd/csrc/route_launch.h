@@ -76,10 +76,13 @@ hipError_t launch_route_bt(const PassArgs* segs, const uint32_t* blk_start, uint
   return hipGetLastError();
 }
 
-// The segments of a batched launch have the same klev, so blocks of at least
-// 1024 slots fill their waves as in a single launch: the unguarded kernels (256
-// sorts of 2^10..2^18 records of 16 bytes: the largest middle launch 442 us with
-// lane guards, 304 without).  From Z = 512 up every block does.
+// Blocks of at least 1024 slots (64 lanes of 16) fill their waves and run the
+// kernels without lane guards (256 sorts of 2^10..2^18 records of 16 bytes: the
+// largest middle launch 442 us with guards, 304 without).  From Z = 512 up every
+// block does, and no guarded kernel is built.
+template <int LZ>
+constexpr bool kAlwaysFull = LZ >= 9;
+
 template <int R, int LZ, bool FULL>
 hipError_t launch_route_bf(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs, uint32_t blocks,
                            uint32_t threads, uint32_t lds, int mode, hipStream_t s) {
@@ -92,32 +95,38 @@ hipError_t launch_route_bf(const PassArgs* segs, const uint32_t* blk_start, uint
     default: return launch_route_bt<R, LZ, F | 3>(segs, blk_start, nsegs, blocks, threads, lds, s);
   }
 }
+// (the segments of a batched launch have the same klev; below Z = 512 a launch of 64
+// threads, whose blocks may have fewer lanes, keeps the guards)
 template <int R, int LZ>
 hipError_t launch_route_bm(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs, uint32_t blocks,
                            uint32_t threads, uint32_t lds, int mode, hipStream_t s) {
-  if constexpr (LZ < 9)  // 64 lanes may be more than the block's slots fill
+  if constexpr (!kAlwaysFull<LZ>)
     if (threads <= 64)
       return launch_route_bf<R, LZ, false>(segs, blk_start, nsegs, blocks, threads, lds, mode, s);
   return launch_route_bf<R, LZ, true>(segs, blk_start, nsegs, blocks, threads, lds, mode, s);
 }
 
-template <int R, int LZ>
-hipError_t launch_route_m(const PassArgs& a, int mode, uint32_t nitems, uint32_t grid, hipStream_t s) {
-  // blocks of at least 1024 slots fill whole waves: the unguarded kernels
-  const bool full = ((uint32_t(1u << LZ) << a.klev) >> 4) >= 64u;
-  switch (mode | (full ? 16 : 0)) {
-    case 0: return launch_route_t<R, LZ, 0>(a, nitems, grid, s);
-    case 1: return launch_route_t<R, LZ, 1>(a, nitems, grid, s);
-    case 2: return launch_route_t<R, LZ, 2>(a, nitems, grid, s);
-    case 3: return launch_route_t<R, LZ, 3>(a, nitems, grid, s);
-    case 6: return launch_route_t<R, LZ, 6>(a, nitems, grid, s);
-    case 16: return launch_route_t<R, LZ, 16>(a, nitems, grid, s);
-    case 17: return launch_route_t<R, LZ, 17>(a, nitems, grid, s);
-    case 18: return launch_route_t<R, LZ, 18>(a, nitems, grid, s);
-    case 19: return launch_route_t<R, LZ, 19>(a, nitems, grid, s);
-    case 22: return launch_route_t<R, LZ, 22>(a, nitems, grid, s);
+template <int R, int LZ, bool FULL>
+hipError_t launch_route_f(const PassArgs& a, int mode, uint32_t nitems, uint32_t grid, hipStream_t s) {
+  constexpr int F = FULL ? 16 : 0;
+  switch (mode) {
+    case 0: return launch_route_t<R, LZ, F | 0>(a, nitems, grid, s);
+    case 1: return launch_route_t<R, LZ, F | 1>(a, nitems, grid, s);
+    case 2: return launch_route_t<R, LZ, F | 2>(a, nitems, grid, s);
+    case 3: return launch_route_t<R, LZ, F | 3>(a, nitems, grid, s);
+    case 6: return launch_route_t<R, LZ, F | 6>(a, nitems, grid, s);
     default: return hipErrorInvalidValue;
   }
+}
+template <int R, int LZ>
+hipError_t launch_route_m(const PassArgs& a, int mode, uint32_t nitems, uint32_t grid, hipStream_t s) {
+  const bool full = ((uint32_t(1u << LZ) << a.klev) >> 4) >= 64u;
+  if constexpr (kAlwaysFull<LZ>) {
+    if (!full) return hipErrorInvalidValue;  // a pass has at least one level
+  } else if (!full) {
+    return launch_route_f<R, LZ, false>(a, mode, nitems, grid, s);
+  }
+  return launch_route_f<R, LZ, true>(a, mode, nitems, grid, s);
 }
 
 // Per-bin finish of bos_orp (finish_impl.h): a persistent walk over groups of
