@@ -52,22 +52,6 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
   else if constexpr (X < 32) return swz_xor<X>(v);
   else return uint32_t(__shfl_xor(int(v), int(X), 64));
 }
-template <uint32_t X>
-__device__ __forceinline__ uint2 lane_xor(uint2 v) {
-  return make_uint2(lane_xor<X>(v.x), lane_xor<X>(v.y));
-}
-template <uint32_t X>
-__device__ __forceinline__ uint4 lane_xor(uint4 v) {
-  return make_uint4(lane_xor<X>(v.x), lane_xor<X>(v.y), lane_xor<X>(v.z), lane_xor<X>(v.w));
-}
-template <uint32_t X, typename T>
-__device__ __forceinline__ ElemR<T> e_xor(const ElemR<T>& a) {
-  return ElemR<T>{lane_xor<X>(a.r)};
-}
-template <uint32_t X, typename T>
-__device__ __forceinline__ ElemRK<T> e_xor(const ElemRK<T>& a) {
-  return ElemRK<T>{lane_xor<X>(a.r), lane_xor<X>(a.klo), lane_xor<X>(a.khi), lane_xor<X>(a.aux)};
-}
 
 template <uint32_t X>
 __device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {

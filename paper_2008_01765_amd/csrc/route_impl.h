@@ -371,10 +371,6 @@ template <typename T>
 __device__ __forceinline__ ElemR<T> e_sel(bool c, const ElemR<T>& a, const ElemR<T>& b) {
   return ElemR<T>{sel(c, a.r, b.r)};
 }
-template <typename T>
-__device__ __forceinline__ ElemRK<T> e_sel(bool c, const ElemRK<T>& a, const ElemRK<T>& b) {
-  return ElemRK<T>{sel(c, a.r, b.r), c ? a.klo : b.klo, c ? a.khi : b.khi, c ? a.aux : b.aux};
-}
 template <uint32_t CTRL, typename T>
 __device__ __forceinline__ ElemR<T> e_dpp(const ElemR<T>& a) {
   return ElemR<T>{dpp<CTRL>(a.r)};
@@ -397,12 +393,6 @@ __device__ __forceinline__ bool f_less(const FRec<8>& a, const FRec<8>& b) { ret
 __device__ __forceinline__ bool f_less(const FRec<16>& a, const FRec<16>& b) {
   return (a.k < b.k) | ((a.k == b.k) & (a.p < b.p));
 }
-__device__ __forceinline__ bool f_eq(const FRec<8>& a, const FRec<8>& b) { return a.k == b.k; }
-__device__ __forceinline__ bool f_eq(const FRec<16>& a, const FRec<16>& b) { return (a.k == b.k) & (a.p == b.p); }
-__device__ __forceinline__ FRec<8> f_sel(bool c, const FRec<8>& a, const FRec<8>& b) { return {c ? a.k : b.k}; }
-__device__ __forceinline__ FRec<16> f_sel(bool c, const FRec<16>& a, const FRec<16>& b) {
-  return {c ? a.k : b.k, c ? a.p : b.p};
-}
 __device__ __forceinline__ FRec<8> f_load(const uint2& r) { return {(uint64_t(r.x) << 32) | r.y}; }
 __device__ __forceinline__ FRec<16> f_load(const uint4& r) {
   return {uint64_t(r.x) | (uint64_t(r.y) << 32), uint64_t(r.z) | (uint64_t(r.w) << 32)};
@@ -421,8 +411,6 @@ struct FE1 {  // sort element: a record in record order
 };
 template <int R>
 __device__ __forceinline__ bool e_less(const FE1<R>& a, const FE1<R>& b) { return f_less(a.r, b.r); }
-template <int R>
-__device__ __forceinline__ FE1<R> e_sel(bool c, const FE1<R>& a, const FE1<R>& b) { return {f_sel(c, a.r, b.r)}; }
 __device__ __forceinline__ uint64_t msel64(uint32_t m, uint64_t a, uint64_t b) {
   return (uint64_t(msel(m, uint32_t(a >> 32), uint32_t(b >> 32))) << 32) | msel(m, uint32_t(a), uint32_t(b));
 }
@@ -647,22 +635,6 @@ __device__ __forceinline__ void bitonic_phase(E (&v)[16], const V& lds, const Bi
     p_stages<LZ, KK, (KK - 1 < 5 ? KK - 1 : 5)>(v, bl);
     bitonic_phase<LZ, KK + 1>(v, lds, bl);
   }
-}
-
-// Ascending bitonic merge of every bin (phase LZ only: stages LZ-1 .. 0), for
-// bins that hold a bitonic sequence; v holds layout P on entry and exit.
-template <int LZ, typename E, typename V>
-__device__ __forceinline__ void bin_bitonic_merge(E (&v)[16], const V& lds, uint32_t bbase, uint32_t lq, bool active) {
-  BinLane bl;
-  bl.active = active;
-  bl.bbase = bbase;
-  bl.pbase = bbase + 17u * lq;
-  bl.lq = lq;
-  bl.lb0 = lq & 1u;
-  bl.lb1 = (lq >> 1) & 1u;
-  const uint32_t rest = lq >> 2;
-  bl.lowQ = LZ >= 11 ? ((bl.lb1 << (LZ - 5)) | (bl.lb0 << (LZ - 6)) | rest) : (LZ >= 6 ? lq : 0u);
-  bitonic_phase<LZ, LZ>(v, lds, bl);
 }
 
 template <int LZ, typename E, typename V>
@@ -1727,7 +1699,7 @@ route_kernel_w3(PassArgs a, uint32_t nitems) {
 
 // Batched routing: segment s of the launch is one instance's pass; its blocks
 // are blockIdx.x in [blk_start[s], blk_start[s+1]).
-template <int R, int LZ, int MODE, bool W3>
+template <int R, int LZ, int MODE>
 __device__ __forceinline__ void route_b_body(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs) {
   uint32_t lo = 0, hi = nsegs;
   while (hi - lo > 1) {
@@ -1743,12 +1715,12 @@ __device__ __forceinline__ void route_b_body(const PassArgs* segs, const uint32_
 template <int R, int LZ, int MODE>
 __global__ __launch_bounds__(kMaxThreads) void route_kernel_b(const PassArgs* segs, const uint32_t* blk_start,
                                                               uint32_t nsegs) {
-  route_b_body<R, LZ, MODE, false>(segs, blk_start, nsegs);
+  route_b_body<R, LZ, MODE>(segs, blk_start, nsegs);
 }
 template <int R, int LZ, int MODE>
 __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<R, LZ>, 8))) void
 route_kernel_b_w3(const PassArgs* segs, const uint32_t* blk_start, uint32_t nsegs) {
-  route_b_body<R, LZ, MODE, true>(segs, blk_start, nsegs);
+  route_b_body<R, LZ, MODE>(segs, blk_start, nsegs);
 }
 
 }  // namespace bos

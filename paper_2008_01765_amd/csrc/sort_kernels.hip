@@ -55,31 +55,6 @@ __device__ __forceinline__ bool gate_shut(unsigned long long gw) {
           uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(gw >> 32))))) != ~0u;
 }
 
-__device__ __forceinline__ uint32_t lpad(uint32_t s) { return s + (s >> 5); }
-
-// In-LDS bitonic network over `cnt` (power of two) records.  Ascending when
-// dir_bit == 0, else the direction of element i is taken from bit dir_bit of
-// its global index g0 + i (standard bitonic direction rule).
-template <typename T>
-__device__ __forceinline__ void lds_bitonic(T* s, uint32_t cnt, uint32_t k2_first, uint32_t k2_last,
-                                            uint32_t j2_first, uint64_t g0) {
-  const uint32_t tid = threadIdx.x, nthr = blockDim.x;
-  for (uint32_t k2 = k2_first; k2 <= k2_last; k2 <<= 1) {
-    for (uint32_t j2 = (k2 == k2_first ? j2_first : (k2 >> 1)); j2 > 0; j2 >>= 1) {
-      for (uint32_t p = tid; p < (cnt >> 1); p += nthr) {
-        const uint32_t lo = ((p & ~(j2 - 1u)) << 1) | (p & (j2 - 1u));
-        const uint32_t hi = lo + j2;
-        const bool up = ((g0 + lo) & k2) == 0;
-        const T a = s[lpad(lo)], b = s[lpad(hi)];
-        const bool sw = up ? rec_less(b, a) : rec_less(a, b);
-        s[lpad(lo)] = sel(sw, b, a);
-        s[lpad(hi)] = sel(sw, a, b);
-      }
-      __syncthreads();
-    }
-  }
-}
-
 // Number of elements of A among the first d outputs of the stable merge of
 // A[0..la) and B[0..lb) (A wins ties).
 template <typename T>
@@ -1462,8 +1437,6 @@ static hipError_t allow_lds(K kernel) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                              160 * 1024);
 }
-
-uint32_t tile_lds_bytes(int rec, uint32_t ts) { return (ts + (ts >> 5)) * uint32_t(rec); }
 
 // LDS of the tile sort of 2^TLOG records (padded slots).
 template <int R, uint32_t TLOG>
