@@ -11,7 +11,11 @@
  * phase is a function of (n, Z, levels per pass) only.  The strip of dummies
  * reveals the bin loads, as Lemma 3.3 allows, and the final comparison sort of
  * bos_sort reveals only what a comparison sort of a uniformly permuted array
- * reveals (Section 3.3).
+ * reveals (Section 3.3).  It does not run on an attempt that overflowed, with one
+ * exception: bos_sort_batched (first attempts) and the step calls enqueue it before
+ * the outcome is known, so that with the probability which min_security_bits bounds
+ * (2^-80 by default) their addresses show order relations of whatever records the
+ * attempt left in its buffers.
  *
  * Records: little-endian array-of-structs {key, payload}, both unsigned, of
  * 4 + 4 bytes (BOS_REC_U32U32) or 8 + 8 bytes (BOS_REC_U64U64).  Record order is
@@ -66,7 +70,7 @@ typedef enum { BOS_REC_U32U32 = 8, BOS_REC_U64U64 = 16 } bos_rec;
                                   from one level to the next; the per-bin finish works
                                   on one bin's Z slots.  For a threat model in which
                                   the working set of a fused block is observable.
-                                  Slower (L passes instead of L/3); same outputs.  k
+                                  Slower (L passes instead of L/k); same outputs.  k
                                   must be 0 or 1 (else BOS_ERR_INVALID_ARG). */
 #define BOS_EXACT_FINISH 4u    /* test hook: run bos_orp's per-bin finish through its
                                   exact-comparator launch (otherwise taken only when two
@@ -81,15 +85,19 @@ typedef struct {
                                  the tuning table's, else 512 (the paper's
                                  choice) */
   uint32_t k;                 /* butterfly levels fused per pass; 0 = the tuning
-                                 table's, else the planner's choice (3), either
-                                 capped at what fits.  An explicit k whose block
+                                 table's, else the planner's choice (4 for 8-byte
+                                 records at Z = 512 from 2^20 records on, else
+                                 3), either capped at what fits.  An explicit k whose block
                                  of 2^k buckets does not fit in LDS (64 KiB..160
                                  KiB by Z and record size) or in one workgroup
                                  is rejected with BOS_ERR_UNSUPPORTED; k > 12
                                  with BOS_ERR_INVALID_ARG */
   uint32_t tile;              /* records per tile of the final sort: 1024, 2048,
                                  4096, 8192 or (8-byte records) 16384; 0 = the
-                                 tuning table's, else 4096 */
+                                 tuning table's, else 4096 (bos_sort then takes
+                                 the smallest tile from 4096 records up, never
+                                 above the table's, that makes at most 16 tiles
+                                 of the n records) */
   uint32_t max_retries;       /* extra attempts after an overflow (default 3) */
   uint32_t min_security_bits; /* reject Z when log2(B log2 B e^(-Z/6)) > -bits;
                                  0 disables the check (default 80) */
@@ -221,8 +229,9 @@ size_t bos_step_workspace_bytes(uint32_t count);
  * the tile sort and the merge passes of the comparison sort: phase values
  * 0..P-1, P, P+1.. (P = routing passes of the job's plan).  Array order is
  * priority: a step runs at least one phase of the first unfinished job and
- * hands a work budget of about twice that phase (at most 2^23 records'
- * worth) to the jobs after it, in order, each running as many phases as fit
+ * hands a work budget to the jobs after it (2^23 records' worth; with fewer than
+ * four unfinished jobs twice the first one's phase, at least 2^22 and at most
+ * 2^23), in order, each running as many phases as fit
  * (possibly none); jobs in the same
  * phase kind share launches, so requests admitted between steps run alongside
  * those already on the device.  The overflow check (Algorithm 3.1's abort) happens at the
@@ -281,17 +290,22 @@ bos_status bos_bitonic_sort(const void* in, void* out, uint64_t n, bos_rec rec, 
  * output is the one bos_orp gives for (input, seed, Z), bos_sort_host's is the
  * sorted input.
  *
- * The slot arrays of Algorithm 3.1 live in host memory (host_ws).  Every
- * routing pass streams them through the device once, in chunks of
- * consecutive routing blocks: a chunk reads one contiguous range of buckets
- * when it covers whole groups of 2^(i+k) buckets (2^k contiguous segments
- * otherwise) and writes one contiguous range, the consecutive-bucket
- * structure Section 4.3 builds its locality on.  The per-bin finish (ORP) or
- * the strip (sort) streams the bins once more; the sort's comparison phase
- * then sorts device-sized runs and merges them by sample splitters (one
- * further read and write of the records).  Host-memory addresses, like device
- * addresses, depend on (n, Z, k) in the routing phase, on the bin loads in the
- * strip, and on comparisons of the permuted records in the comparison phase.
+ * The slot arrays of Algorithm 3.1 live in host memory (host_ws) and cross to the
+ * device and back in as few trips as dev_ws allows: a chunk runs as many routing
+ * passes as its staging buffer holds whole blocks of 2^K buckets for (K levels)
+ * before it leaves.  A chunk reads a contiguous range of the records (first trip) or
+ * 2^K contiguous segments of buckets, and writes one contiguous range, the
+ * consecutive-bucket structure Section 4.3 builds its locality on; between trips a
+ * slot's tag keeps only the label bits of the levels still to come (1, 2 or 4
+ * bytes).  The ORP's per-bin finish streams the bins once more.  The sort strips the
+ * chunks of its last trip on the device, where the host reads each chunk's overflow
+ * word and real count; they leave as runs, sorted unless the attempt's outcome is not
+ * known by then (the loads of the last trip's buckets are counted one trip ahead,
+ * where the counters fit in dev_ws; otherwise the runs are sorted in a trip of their
+ * own), and are merged by sample splitters (one further read and write of the
+ * records).  Host-memory addresses, like device addresses, depend on (n, Z, k) in the
+ * routing phase, on the bin loads in the strip, and on comparisons of the permuted
+ * records of an attempt that did not overflow in the comparison phase.
  *
  * in, out: host, n records each (not overlapping).  host_ws: host,
  * bos_host_workspace_bytes(n, rec, p) bytes.  dev_ws: device, at least
@@ -319,7 +333,7 @@ bos_status bos_sort_host(const void* in, void* out, uint64_t n, bos_rec rec, con
 /* One autotuner result: for records of `rec` bytes and n in size class
  * `log2n` (the smallest c with 2^c >= n), use bucket capacity z, k levels per
  * pass and comparison-sort tile `tile` (as in bos_params).  A zero field
- * leaves the library default (Z = 512, k = 3, tile = 4096). */
+ * leaves the library default (Z = 512, the planner's k, tile = 4096). */
 typedef struct {
   uint32_t rec;
   uint32_t log2n;

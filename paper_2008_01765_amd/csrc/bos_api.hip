@@ -291,7 +291,8 @@ bos_status make_plan(uint64_t n, int rec, const bos_params& q, bool shuffle_last
   // so a workgroup holds one MergeSplit's 2Z slots and nothing across levels
   const bool strict = (q.flags & BOS_STRICT) != 0;
   if (strict && q.k > 1) return BOS_ERR_INVALID_ARG;
-  const uint32_t kreq = strict ? 1u : q.k ? q.k : (tuned && te.k && te.z == Z ? te.k : (rec == 8 && Z == 512u && n >= (1ull << 20)) ? 4u : 3u);
+  const uint32_t kdef = rec == 8 && Z == 512u && n >= (1ull << 20) ? 4u : 3u;
+  const uint32_t kreq = strict ? 1u : q.k ? q.k : tuned && te.k && te.z == Z ? te.k : kdef;
   const uint32_t k = std::min(kreq, kmid);
   pl->k = k;
   pl->tile = q.tile ? q.tile : (tuned && te.tile ? te.tile : kDefaultTile);
@@ -492,7 +493,7 @@ hipError_t enqueue_routing(const Plan& pl, const void* in, void* out, uint64_t s
     a.attempt = attempt;
     const bool split_pass = split && last;
     // the split last pass compacts every bin whatever the finish; the fused
-    // one permutes (fin 0) or sorts (fin 1) its bins itself
+    // one permutes (fin 0), sorts (fin 1) or compacts (fin 2) its bins itself
     a.fin = split_pass ? 1u : fin;
     if (split_pass) a.loads = reinterpret_cast<uint32_t*>(ws + pl.off_loads);
     const uint64_t slot_bytes = pl.B * pl.Z * (uint64_t(pl.rec) + 4), rec_bytes = pl.n * pl.rec;
@@ -2164,9 +2165,10 @@ struct OocTrip {
 // run back to back on the device, so a trip takes as many passes as 2^K buckets
 // fit the buffers: the link bounds a trip.  A sort of 2^24 records of 8 bytes
 // with 256 MB of staging took 51 ms with its four passes as four trips, 25 ms with
-// two and 18.5 ms with two of packed slots (launch_pack_slots).  After the first trip a chunk is read in
-// 2^K segments; they stay at 512 KB of records or more (9 us of the link, what a
-// copy costs to start), except that a trip has at least one pass.
+// two and 18.3-19.9 ms (by the box) with two of packed slots (launch_pack_slots).
+// After the first trip a chunk is read in 2^K segments; they stay at 512 KB of
+// records or more (9 us of the link, what a copy costs to start), except that a trip
+// has at least one pass.
 std::vector<OocTrip> ooc_trips(const Plan& pl, uint64_t cap) {
   std::vector<OocTrip> trips;
   for (uint32_t t = 0; t < pl.P;) {

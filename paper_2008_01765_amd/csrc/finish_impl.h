@@ -30,12 +30,18 @@
 //
 // Layout: lane lq of the bin's Z/16 lanes holds slots 16 lq + e (e = 0..15) in
 // registers, each record as the 64-bit word(s) that order it (key in the high
-// half for 8-byte records).  Stages on slot bits 0..3 pair registers; stages on higher bits
-// pair lanes lq ^ X through DPP (X = 1, 2), ds_swizzle (X = 4, 8, 16) or a
-// lane permute (X = 32).  Up to Z = 1024 a bin's lanes are one wave's and the
-// only LDS is the bin's record copy of step 4 (the routing kernel's padded
-// bin layout); Z = 2048 (two waves per bin) sorts through LDS with that
-// layout.
+// half for 8-byte records).  Up to Z = 1024 a bin's lanes are one wave's.  From
+// Z = 256 on both networks pair registers only: a phase whose stages reach slot
+// bits above 3 moves the bin through its LDS slots into layouts that have those
+// bits in the register index, and back.  Below that, and in the exact launch,
+// stages on slot bits above 3 pair lanes lq ^ X through DPP (X = 1, 2), ds_swizzle
+// (X = 4, 8, 16) or a lane permute (X = 32), and LDS holds the record copy of step
+// 4 alone.  Z = 2048 (two waves per bin) sorts through LDS slots.
+//
+// What bounds it: the compare-exchanges of the two networks (5.4 ms at n = 2^28
+// records of 8 bytes, Z = 512).  Sorted records and key words do not both fit the
+// 128 registers of four waves per SIMD: 176 bytes a lane go through scratch, 8.4e9
+// bytes of HBM traffic for 4.3e9 needed; at two waves without scratch 6.5 ms.
 #pragma once
 #include "route_impl.h"
 
