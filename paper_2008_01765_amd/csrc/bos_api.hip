@@ -2165,7 +2165,7 @@ struct OocTrip {
 // run back to back on the device, so a trip takes as many passes as 2^K buckets
 // fit the buffers: the link bounds a trip.  A sort of 2^24 records of 8 bytes
 // with 256 MB of staging took 51 ms with its four passes as four trips, 25 ms with
-// two and 18.3-19.9 ms (by the box) with two of packed slots (launch_pack_slots).
+// two and 18.3-19.9 ms (several cards) with two of packed slots (launch_pack_slots).
 // After the first trip a chunk is read in 2^K segments; they stay at 512 KB of
 // records or more (9 us of the link, what a copy costs to start), except that a trip
 // has at least one pass.
